@@ -363,6 +363,128 @@ __global__ void stamp_kernel(uint64_t *dst) {
   }
 }
 
+// fp32 to bf16, nearest-even; a NaN keeps its upper bits and turns quiet.
+__device__ __forceinline__ uint16_t bf16_rne(uint32_t u) {
+  if ((u & 0x7FFFFFFFu) > 0x7F800000u) return (uint16_t)((u >> 16) | 0x40u);
+  return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
+}
+
+typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+
+// 8 consecutive source elements from index i as bf16 bits.  VEC: the source is
+// 16-byte aligned (i is a multiple of 8 then), else element loads.
+template <bool F32, bool VEC>
+__device__ __forceinline__ u16x8 load8_bf16(const void *src, size_t i) {
+  u16x8 o;
+  if constexpr (F32) {
+    const uint32_t *p = (const uint32_t *)src + i;
+    if constexpr (VEC) {
+      const u32x4_t a = *(const u32x4_t *)p, b = *(const u32x4_t *)(p + 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        o[e] = bf16_rne(a[e]);
+        o[4 + e] = bf16_rne(b[e]);
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) o[e] = bf16_rne(p[e]);
+    }
+  } else {
+    const uint16_t *p = (const uint16_t *)src + i;
+    if constexpr (VEC) {
+      o = *(const u16x8 *)p;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) o[e] = p[e];
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e)  // signalling NaNs turn quiet, as from fp32
+      if ((o[e] & 0x7FFFu) > 0x7F80u) o[e] |= 0x40u;
+  }
+  return o;
+}
+
+// Prefix K/V into the stores (see PrefixArgs): bound by memory, each value read
+// and written once with 16-byte accesses.  It takes the place of a repacking
+// on the host (device to host copy, scalar loops, copy back): a new prefix and
+// its release together 11.10 -> 4.98 ms at batch 1 (18 layers, 816 keys, bf16)
+// and 52.8 -> 2.38 ms at 16 environments (6 layers, fp32), same machine.  K rows are copied; the V block goes
+// through LDS (rows padded by 16 bytes: the 64 lanes of a column read hit 64
+// banks) and leaves as [hd][32 keys permuted], vt_key_pos: the 8 keys of 16-byte
+// chunk g of a column are 4g..4g+3 and 16+4g..16+4g+3.
+template <int HD, bool F32, bool VEC>
+__global__ __launch_bounds__(256) void prefix_pack_kernel(PrefixArgs a) {
+  __shared__ __align__(16) uint16_t vs[32][HD + 8];
+  const int blk = a.blk0 + (int)(blockIdx.x % (unsigned)a.n_blk);
+  const int eh = (int)(blockIdx.x / (unsigned)a.n_blk);
+  const int b = eh / a.n_kv_heads, g = eh - b * a.n_kv_heads;
+  const size_t dst_eh = (size_t)(a.env0 + b) * a.n_kv_heads + g;
+  const size_t src = blockIdx.z * a.src_layer + b * a.src_env + (size_t)g * HD;
+  __bf16 *kd = a.kc + blockIdx.z * a.dst_layer + (dst_eh * a.s_alloc + (size_t)blk * 32) * HD;
+  __bf16 *vd = a.vtc + blockIdx.z * a.dst_layer + vt_index(dst_eh, blk * 32, 0, HD, a.s_alloc);
+#pragma unroll
+  for (int it = 0; it < HD / 64; ++it) {
+    const int q = it * 256 + threadIdx.x;
+    const int key = q / (HD / 8), c = (q % (HD / 8)) * 8;
+    const int s = blk * 32 + key;
+    u16x8 kv = {0, 0, 0, 0, 0, 0, 0, 0}, vv = kv;
+    if (s < a.n_keys) {
+      const size_t i = src + (size_t)(s - a.key0) * a.n_kv_heads * HD + c;
+      kv = load8_bf16<F32, VEC>(a.k, i);
+      vv = load8_bf16<F32, VEC>(a.v, i);
+    }
+    *(u16x8 *)(kd + key * HD + c) = kv;
+    *(u16x8 *)&vs[key][c] = vv;
+  }
+  __syncthreads();
+  for (int q = threadIdx.x; q < HD * 2; q += 256) {  // column pair q / 4, chunk q % 4
+    const int c = (q >> 2) * 2, ch = q & 3;
+    u16x8 o0, o1;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const uint32_t two = *(const uint32_t *)&vs[16 * (e >> 2) + 4 * ch + (e & 3)][c];
+      o0[e] = (uint16_t)two;
+      o1[e] = (uint16_t)(two >> 16);
+    }
+    *(u16x8 *)(vd + c * 32 + ch * 8) = o0;
+    *(u16x8 *)(vd + (c + 1) * 32 + ch * 8) = o1;
+  }
+}
+
+template <int HD>
+static hipError_t launch_prefix_hd(const PrefixArgs &a, bool f32, hipStream_t s) {
+  const dim3 grid((unsigned)(a.n_env * a.n_kv_heads * a.n_blk), 1, a.n_layers), wg(256);
+  const bool vec = (((uintptr_t)a.k | (uintptr_t)a.v) & 15) == 0;  // rows are multiples of 128 bytes
+  if (f32 && vec) hipLaunchKernelGGL((prefix_pack_kernel<HD, true, true>), grid, wg, 0, s, a);
+  else if (f32) hipLaunchKernelGGL((prefix_pack_kernel<HD, true, false>), grid, wg, 0, s, a);
+  else if (vec) hipLaunchKernelGGL((prefix_pack_kernel<HD, false, true>), grid, wg, 0, s, a);
+  else hipLaunchKernelGGL((prefix_pack_kernel<HD, false, false>), grid, wg, 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_prefix_pack(const PrefixArgs &a, int head_dim, bool f32, hipStream_t s) {
+  if (a.n_env < 1 || a.n_blk < 1 || a.n_layers < 1 || (a.blk0 + a.n_blk) * 32 > a.s_alloc ||
+      (int64_t)a.n_env * a.n_kv_heads * a.n_blk >= (int64_t)1 << 24)  // grid.x threads stay below 2^32
+    return hipErrorInvalidValue;
+  const size_t esz = f32 ? 4 : 2;
+  constexpr int kMaxZ = 32768;
+  for (int l = 0; l < a.n_layers; l += kMaxZ) {
+    PrefixArgs p = a;
+    p.n_layers = a.n_layers - l < kMaxZ ? a.n_layers - l : kMaxZ;
+    p.k = (const char *)a.k + l * a.src_layer * esz;
+    p.v = (const char *)a.v + l * a.src_layer * esz;
+    p.kc = a.kc + l * a.dst_layer;
+    p.vtc = a.vtc + l * a.dst_layer;
+    hipError_t e = hipErrorInvalidValue;
+    if (head_dim == 64) e = launch_prefix_hd<64>(p, f32, s);
+    else if (head_dim == 128) e = launch_prefix_hd<128>(p, f32, s);
+    else if (head_dim == 256) e = launch_prefix_hd<256>(p, f32, s);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 hipError_t launch_temb(const float *x, const float *t, int M, int Da, int d, const float *w_in,
                        const float *b_in, const float *freqs, op_t *te, unsigned *status, hipStream_t s,
                        hipEvent_t ev0, hipEvent_t ev1, const int32_t *env_map, int chunk) {

@@ -629,6 +629,16 @@ uad_status uad_load_weights(uad_ctx *c, const uad_tensor *ts, int32_t n) {
   return UAD_OK;
 }
 
+// Whether this context's kernels can read a caller's device pointer in place
+// (memory of this device or managed memory; not another device's).
+static bool reads_directly(const uad_ctx *c, const void *p) {
+  hipPointerAttribute_t pa{};
+  const bool ok = hipPointerGetAttributes(&pa, p) == hipSuccess &&
+                  ((pa.type == hipMemoryTypeDevice && pa.device == c->device) || pa.type == hipMemoryTypeManaged);
+  (void)hipGetLastError();
+  return ok;
+}
+
 uad_status uad_set_prefix_kv(uad_ctx *c, const void *k, const void *v, int32_t dtype, int32_t batch,
                              int32_t prefix_len, int32_t on_device) {
   if (!c) return UAD_E_INVALID;
@@ -641,32 +651,64 @@ uad_status uad_set_prefix_kv(uad_ctx *c, const void *k, const void *v, int32_t d
   // queued steps (a release's tail, say) may still read the K/V being replaced
   hipError_t se = hipStreamSynchronize(c->stream);
   if (se != hipSuccess) return hip_fail(c, se, "uad_set_prefix_kv: hipStreamSynchronize");
-  const int L = c->L, Hkv = c->Hkv, hd = c->hd, P = prefix_len, S = c->s_alloc;
-  const size_t per_layer_in = (size_t)batch * P * Hkv * hd;
-  std::string err;
-  std::vector<float> kf, vf;
-  std::vector<uint16_t> ks((size_t)batch * Hkv * S * hd), vs((size_t)batch * Hkv * hd * S);
-  const size_t esz = dtype == UAD_DTYPE_F32 ? 4 : 2;
-  for (int l = 0; l < L; ++l) {
-    if (!fetch_f32((const char *)k + l * per_layer_in * esz, dtype, on_device, per_layer_in, &kf, &err) ||
-        !fetch_f32((const char *)v + l * per_layer_in * esz, dtype, on_device, per_layer_in, &vf, &err))
-      return fail(c, UAD_E_HIP, "uad_set_prefix_kv: " + err);
-    std::fill(ks.begin(), ks.end(), 0);
-    std::fill(vs.begin(), vs.end(), 0);
-    for (int b = 0; b < batch; ++b)
-      for (int s = 0; s < P; ++s)
-        for (int g = 0; g < Hkv; ++g)
-          for (int cc = 0; cc < hd; ++cc) {
-            const size_t src = (((size_t)b * P + s) * Hkv + g) * hd + cc;
-            const size_t eh = (size_t)b * Hkv + g;
-            ks[(eh * S + s) * hd + cc] = f32_to_bf16_rne(kf[src]);
-            vs[vt_index(eh, s, cc, hd, S)] = f32_to_bf16_rne(vf[src]);
+  const int L = c->L, Hkv = c->Hkv, hd = c->hd, P = prefix_len;
+  const bool f32 = dtype == UAD_DTYPE_F32;
+  const size_t esz = f32 ? 4 : 2, row = (size_t)Hkv * hd;  // elements per key
+  PrefixArgs a{};
+  a.n_keys = P; a.n_kv_heads = Hkv; a.s_alloc = c->s_alloc; a.n_blk = c->s_alloc / 32; a.n_env = batch; a.n_layers = L;
+  a.dst_layer = c->kv_layer_elems; a.kc = c->kcache; a.vtc = c->vtcache;
+  a.src_env = (size_t)P * row; a.src_layer = batch * a.src_env;
+  // All on the null stream, as the copies of a caller's buffers always were:
+  // ordered after what the caller queued there.
+  hipError_t e = hipSuccess;
+  if (P == 0 || (on_device && reads_directly(c, k) && reads_directly(c, v))) {
+    a.k = k; a.v = v;
+    e = launch_prefix_pack(a, hd, f32, nullptr);
+  } else {
+    // Host memory (or another device's): through the split-K workspace, which
+    // no queued work uses now, in runs of whole environments, or of whole
+    // 32-key blocks of one where an environment does not fit.
+    size_t half = c->kx_ws_bytes / 2 & ~(size_t)15;
+    char *sk = (char *)c->kx_ws;
+    void *own = nullptr;  // hundreds of wide KV heads: one block exceeds the workspace
+    const size_t env_bytes = a.src_env * esz, blk_bytes = 32 * row * esz;
+    if (blk_bytes > half) {
+      half = blk_bytes;
+      if ((e = hipMalloc(&own, 2 * half)) != hipSuccess) return hip_fail(c, e, "uad_set_prefix_kv: hipMalloc(staging)");
+      sk = (char *)own;
+    }
+    char *sv = sk + half;
+    a.k = sk; a.v = sv; a.src_layer = 0; a.n_layers = 1;
+    const int envs = (int)std::min<size_t>(batch, half / env_bytes);  // 0: part of one
+    const int blks = envs ? a.n_blk : (int)std::min<size_t>(a.n_blk, half / blk_bytes);
+    for (int l = 0; l < L && e == hipSuccess; ++l) {
+      a.kc = c->kcache + l * c->kv_layer_elems;
+      a.vtc = c->vtcache + l * c->kv_layer_elems;
+      for (int b = 0; b < batch && e == hipSuccess; b += std::max(1, envs)) {
+        a.env0 = b;
+        a.n_env = std::min(std::max(1, envs), batch - b);
+        for (int q = 0; q < c->s_alloc / 32 && e == hipSuccess; q += blks) {
+          a.blk0 = q;
+          a.n_blk = std::min(blks, c->s_alloc / 32 - q);
+          a.key0 = 32 * q;
+          const int keys = envs ? P : std::min(32 * a.n_blk, P - 32 * q);
+          const size_t off = (((size_t)l * batch + b) * P + 32 * q) * row * esz;
+          const size_t bytes = envs ? a.n_env * env_bytes : (size_t)std::max(0, keys) * row * esz;
+          if (bytes) {
+            e = hipMemcpyAsync(sk, (const char *)k + off, bytes, hipMemcpyDefault, nullptr);
+            if (e == hipSuccess) e = hipMemcpyAsync(sv, (const char *)v + off, bytes, hipMemcpyDefault, nullptr);
           }
-    hipError_t e = hipMemcpy(c->kcache + l * c->kv_layer_elems, ks.data(), ks.size() * 2, hipMemcpyHostToDevice);
-    if (e == hipSuccess)
-      e = hipMemcpy(c->vtcache + l * c->kv_layer_elems, vs.data(), vs.size() * 2, hipMemcpyHostToDevice);
-    if (e != hipSuccess) return hip_fail(c, e, "uad_set_prefix_kv: hipMemcpy");
+          if (e == hipSuccess) e = launch_prefix_pack(a, hd, f32, nullptr);
+        }
+      }
+    }
+    if (own) {
+      (void)hipStreamSynchronize(nullptr);
+      (void)hipFree(own);
+    }
   }
+  if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+  if (e != hipSuccess) return hip_fail(c, e, "uad_set_prefix_kv");
   c->prefix_len = P;
   c->prefix_batch = batch;
   c->prefix_set = true;

@@ -288,6 +288,22 @@ struct TrArgs {
   int reconcile;         // 1: TR (ghosts continue), 0: plain early release (urgent frozen)
 };
 
+// Prefix K/V repacking: rows of the caller's [..][P][Hkv][hd] arrays into the
+// K / V^T stores, one 32-key block of one (layer, environment, KV head) per
+// workgroup.  Keys s >= n_keys of a block are written as zeros.
+struct PrefixArgs {
+  const void *k, *v;              // source rows, fp32 or bf16
+  size_t src_layer, src_env;      // source elements from one layer / environment to the next
+  int key0;                       // key of the source's first row
+  int n_keys;                     // keys of the prefix
+  int n_kv_heads, s_alloc;
+  int env0, n_env;                // destination environments
+  int blk0, n_blk;                // destination 32-key blocks
+  int n_layers;
+  size_t dst_layer;               // store elements per layer
+  __bf16 *kc, *vtc;               // stores of the first layer
+};
+
 // ---------------------------------------------------------------------------
 // Launchers (defined in the .hip translation units)
 // ---------------------------------------------------------------------------
@@ -319,6 +335,7 @@ hipError_t launch_time_features(const float *t, int M, int m_alloc, int n_steps,
                                 op_t *te, unsigned *status, hipStream_t s);
 hipError_t launch_final(const FinalArgs &f, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 hipError_t launch_stamp(uint64_t *dst, hipStream_t s);
+hipError_t launch_prefix_pack(const PrefixArgs &a, int head_dim, bool f32, hipStream_t s);
 hipError_t launch_tr_init(const TrArgs &a, hipStream_t s);     // x0 <- x, vsum <- 0
 hipError_t launch_tr_release(const TrArgs &a, hipStream_t s);  // urgent <- x_K; TR: x_K <- x0 + dt* vsum
 hipError_t launch_gac(const TrArgs &a, hipStream_t s);         // E and the corrected executed actions
