@@ -94,10 +94,16 @@ __device__ __forceinline__ void prefetch_share(const Prefetch &pf, int wg, unsig
 // registers: two waves per SIMD at HD = 256) instead of all up front.
 // NW waves (16 query rows each) per workgroup; NW > 4 only without split-KV
 // (a.qblocks counts blocks of 16 * NW rows).
-template <int HD, int NB, bool LOWREG, int NW>
+// KG key groups: wave w takes row tile w % (NW / KG) and every KG-th run of NB
+// blocks from run w / (NW / KG) on; the groups' results are merged through LDS
+// at the end, each group finishing its share of the output columns.
+template <int HD, int NB, bool LOWREG, int NW, int KG>
 __global__ __launch_bounds__(64 * NW) void attn_kernel(AttnArgs a) {
   extern __shared__ __align__(16) unsigned char attn_smem[];
-  AttnBlock<HD> *bufs = (AttnBlock<HD> *)attn_smem;  // [2][NB]
+  AttnBlock<HD> *bufs = (AttnBlock<HD> *)attn_smem;  // [2][KG * NB]
+  constexpr int RW = NW / KG;   // 16-row tiles per workgroup
+  constexpr int NBS = KG * NB;  // blocks per stage
+  static_assert(NW % KG == 0 && (KG == 1 || LOWREG), "key groups");
   constexpr int KS = HD / 32;   // k-steps of the QK^T product
   constexpr int NTO = HD / 16;  // 16-column output tiles
   constexpr int CPR = HD / 8;   // 16-byte chunks per K row
@@ -135,7 +141,8 @@ __global__ __launch_bounds__(64 * NW) void attn_kernel(AttnArgs a) {
   if (blk1 > n_blocks) blk1 = n_blocks;
 
   // This lane's query (as the B operand of S^T): packed row r0 + (lane & 15).
-  const int r0 = qblock * (16 * NW) + wave * 16;
+  const int kg = KG == 1 ? 0 : wave / RW;
+  const int r0 = qblock * (16 * RW) + (wave - kg * RW) * 16;
   const int my_r = r0 + (lane & 15);
   bf16x8 qf[KS];
   {
@@ -152,9 +159,9 @@ __global__ __launch_bounds__(64 * NW) void attn_kernel(AttnArgs a) {
   // (blocks past the split's end re-read its last block; never used).
   auto issue = [&](int c0, int which) {
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
+    for (int j = 0; j < NBS; ++j) {
       const int blk = min(c0 + j, blk1 - 1);
-      AttnBlock<HD> &dst = bufs[which * NB + j];
+      AttnBlock<HD> &dst = bufs[which * NBS + j];
       const __bf16 *kb = kbase + (size_t)blk * 32 * HD;
       const __bf16 *vb = vbase + (size_t)blk * 32 * HD;
       // wave w issues the contiguous instructions [w*TI/NW, (w+1)*TI/NW)
@@ -182,16 +189,17 @@ __global__ __launch_bounds__(64 * NW) void attn_kernel(AttnArgs a) {
   float l_run = 0.f;        // this lane's partial sum of exp2
 
   int which = 0;
-  for (int c0 = blk0; c0 < blk1; c0 += NB, which ^= 1) {
-    const int nb = min(NB, blk1 - c0);
+  for (int c0 = blk0; c0 < blk1; c0 += NBS, which ^= 1) {
+    const int cg = c0 + kg * NB;           // this key group's run of the stage
+    const int nb = min(NB, blk1 - cg);     // <= 0: past the split's end
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this chunk's LDS-direct loads (and q) landed
     __syncthreads();  // ... for every wave; the other buffer set is free again
-    if (c0 + NB < blk1) issue(c0 + NB, which ^ 1);
+    if (c0 + NBS < blk1) issue(c0 + NBS, which ^ 1);
 
 #pragma nounroll
     for (int j = 0; j < nb; ++j) {
-      const AttnBlock<HD> &blk = bufs[which * NB + j];
-      const int k0 = (c0 + j) * 32;
+      const AttnBlock<HD> &blk = bufs[which * NBS + kg * NB + j];
+      const int k0 = (cg + j) * 32;
       // S^T for two 16-key halves: s[h][r] = score(query lane&15, key k0+16h+4(lane>>4)+r).
       // All K and V fragments of the block are read up front.
       f32x4 s[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
@@ -288,7 +296,48 @@ __global__ __launch_bounds__(64 * NW) void attn_kernel(AttnArgs a) {
     }
   }
 
-  const float l_tot = sum_pair32(sum_pair16(l_run));
+  float l_tot = sum_pair32(sum_pair16(l_run));
+
+  // Output tiles [nt0, nt1) are this wave's to finish.
+  int nt0 = 0;
+  constexpr int NTW = NTO / KG;
+  if constexpr (KG == 2) {
+    // Each wave hands the other group's half of its output columns (fp32, as
+    // accumulated) and its rows' (max, sum) to its partner through the stages'
+    // LDS, and adds the partner's part of its own half, both rescaled to the
+    // larger max.  A group without a block holds max -inf, sum 0, output 0.
+    f32x4 *ox = (f32x4 *)attn_smem;                               // [NW][NTW][64]
+    float2 *mlx = (float2 *)(attn_smem + (size_t)NW * NTW * 1024);  // [NW][16]
+    static_assert((size_t)NW * NTW * 1024 + NW * 128 <= 2 * NBS * sizeof(AttnBlock<HD>), "exchange exceeds the stages");
+    __syncthreads();  // every wave is past its last fragment read
+#pragma unroll
+    for (int q = 0; q < NTW; ++q) {
+      const f32x4 give = kg ? o[q] : o[NTW + q];
+      ox[(wave * NTW + q) * 64 + lane] = give;
+    }
+    if (lane < 16) mlx[wave * 16 + lane] = float2{m_run, l_tot};
+    __syncthreads();
+    const int other = wave ^ RW;  // RW is a power of two
+    const float2 mlo = mlx[other * 16 + (lane & 15)];
+    const float m_new = fmaxf(m_run, mlo.x);
+    const float c_own = __builtin_amdgcn_exp2f(m_run - m_new), c_oth = __builtin_amdgcn_exp2f(mlo.x - m_new);
+    l_tot = c_own * l_tot + c_oth * mlo.y;
+    m_run = m_new;
+    float ca[4], cb[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      ca[r] = __shfl(c_own, (lane >> 4) * 4 + r);
+      cb[r] = __shfl(c_oth, (lane >> 4) * 4 + r);
+    }
+#pragma unroll
+    for (int q = 0; q < NTW; ++q) {
+      const f32x4 got = ox[(other * NTW + q) * 64 + lane];
+      const f32x4 own = kg ? o[NTW + q] : o[q];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o[q][r] = ca[r] * own[r] + cb[r] * got[r];
+    }
+    nt0 = kg * NTW;
+  }
 
   // Output rows of this lane: r0 + 4*(lane>>4) + r, column 16*nt + (lane&15)
   float lr[4];
@@ -305,8 +354,9 @@ __global__ __launch_bounds__(64 * NW) void attn_kernel(AttnArgs a) {
       const int orow = b * a.chunk + tok;
       const float inv = 1.0f / lr[r];
 #pragma unroll
-      for (int nt = 0; nt < NTO; ++nt)
-        store_op(a.o + afrag_index(orow, head * HD + nt * 16 + (lane & 15), a.ldo / kTileK), o[nt][r] * inv, bad);
+      for (int q = 0; q < NTW; ++q)
+        store_op(a.o + afrag_index(orow, head * HD + (nt0 + q) * 16 + (lane & 15), a.ldo / kTileK), o[q][r] * inv,
+                 bad);
     }
     flush_range(a.status, bad);
   } else {
@@ -319,13 +369,13 @@ __global__ __launch_bounds__(64 * NW) void attn_kernel(AttnArgs a) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) inv[r] = 1.0f / lr[r];
 #pragma unroll
-    for (int nt = 0; nt < NTO; ++nt) {
-      const float p0 = o[nt][0] * inv[0], p1 = o[nt][1] * inv[1], p2 = o[nt][2] * inv[2], p3 = o[nt][3] * inv[3];
-      *(f16x4 *)(op + nt * 256) = f16x4{(op_t)p0, (op_t)p1, (op_t)p2, (op_t)p3};
+    for (int q = 0; q < NTW; ++q) {
+      const float p0 = o[q][0] * inv[0], p1 = o[q][1] * inv[1], p2 = o[q][2] * inv[2], p3 = o[q][3] * inv[3];
+      *(f16x4 *)(op + (nt0 + q) * 256) = f16x4{(op_t)p0, (op_t)p1, (op_t)p2, (op_t)p3};
       check_op4(p0, p1, p2, p3, bad);
     }
     // lanes 0..15 hold the statistics of their own query row r0 + lane
-    if (lane < 16) *(float2 *)(a.mlpart + (tile * 16 + lane) * 2) = float2{m_run, l_tot};
+    if (kg == 0 && lane < 16) *(float2 *)(a.mlpart + (tile * 16 + lane) * 2) = float2{m_run, l_tot};
     flush_range(a.status, bad);
   }
 }
@@ -392,6 +442,26 @@ __global__ __launch_bounds__(64 * W) void attn_combine_kernel(AttnArgs a, int hd
 
 static int g_attn_cus = 256;  // compute units of the device (set by attention_init)
 
+// waves per workgroup of the split merge (see launch_hd)
+static int merge_waves(int splits) { return splits > 8 ? 4 : 1; }
+
+static bool attn_streamed(const AttnArgs &a, int nb) {
+  const int groups = a.n_eh * a.splits;
+  return a.blocks_per_split > 2 * nb ||
+         (a.blocks_per_split > nb && 4 * 8 * ((groups + 7) / 8) * a.qblocks > 3 * g_attn_cus);
+}
+// Long splits whose 4-wave workgroups would each have a CU to themselves (one
+// wave per SIMD walking the split's blocks, ~1.3 us a block at HD = 256, most of
+// it the latency of its read -> MFMA -> softmax chain): 8 waves instead, two key
+// groups of four.  The two waves of a SIMD hide each other's chains until the
+// LDS reads of their fragments bound them.  Same-machine, attention us per
+// layer: 1024-wide expert at 32 / 24 environments 36.5 / 36.3 -> 28.0 / 27.0,
+// 8 (with its merge) 27.8 -> 24.6; 1536-wide at 8 / 5 28.7 / 28.0 -> 21.4 /
+// 20.5.  Beyond one workgroup per CU two 4-wave ones share a CU already.
+static bool attn_two_groups(const AttnArgs &a, int nb) {
+  return attn_streamed(a, nb) && a.n_eh * a.splits * a.qblocks <= g_attn_cus;
+}
+
 template <int HD>
 static hipError_t launch_hd(const AttnArgs &a, int batch, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   constexpr int NB = attn_chunk_blocks<HD>();
@@ -401,11 +471,12 @@ static hipError_t launch_hd(const AttnArgs &a, int batch, hipStream_t s, hipEven
     return hipErrorInvalidValue;
   dim3 grid(8 * ((groups + 7) / 8) * a.qblocks + a.pre_attn.wgs);
   hipEvent_t end_attn = a.splits == 1 ? ev1 : nullptr;
-  // Long splits (batched steps, one split per query block): one 32-key block
-  // per stage and K/V fragments streamed in halves, so that two workgroups
-  // (8 waves) share a CU and hide each other's LDS reads and softmax; short
-  // splits (batch 1): NB blocks per stage, one memory round trip per split.
-  const bool streamed = a.blocks_per_split > 2 * NB;
+  // Long splits: one 32-key block per stage and K/V fragments streamed in
+  // halves, so that two workgroups (8 waves) share a CU and hide each other's
+  // LDS reads and softmax; short splits (batch 1): NB blocks per stage, one
+  // memory round trip per split.  Splits of two chunks count as long when the
+  // grid takes most of the CUs (two key groups: see below).
+  const bool streamed = attn_streamed(a, NB);
   const uint32_t lds = (uint32_t)(2 * (streamed ? 1 : NB) * sizeof(AttnBlock<HD>));
   if (streamed && a.splits == 1 && a.pre_attn.wgs == 0) {
     // Without split-KV every workgroup of a group re-reads the group's whole
@@ -430,18 +501,21 @@ static hipError_t launch_hd(const AttnArgs &a, int batch, hipStream_t s, hipEven
       constexpr int TB = attn_tall_blocks<HD>();
       const uint32_t lds_tall = (uint32_t)(2 * TB * sizeof(AttnBlock<HD>));
       if (best_nw == 6)
-        UAD_LAUNCH((attn_kernel<HD, TB, true, 6>), g2, dim3(384), lds_tall, s, ev0, end_attn, at);
+        UAD_LAUNCH((attn_kernel<HD, TB, true, 6, 1>), g2, dim3(384), lds_tall, s, ev0, end_attn, at);
       else if (best_nw == 7)
-        UAD_LAUNCH((attn_kernel<HD, TB, true, 7>), g2, dim3(448), lds_tall, s, ev0, end_attn, at);
+        UAD_LAUNCH((attn_kernel<HD, TB, true, 7, 1>), g2, dim3(448), lds_tall, s, ev0, end_attn, at);
       else
-        UAD_LAUNCH((attn_kernel<HD, TB, true, 8>), g2, dim3(512), lds_tall, s, ev0, end_attn, at);
+        UAD_LAUNCH((attn_kernel<HD, TB, true, 8, 1>), g2, dim3(512), lds_tall, s, ev0, end_attn, at);
       return hipGetLastError();
     }
   }
-  if (streamed)
-    UAD_LAUNCH((attn_kernel<HD, 1, true, 4>), grid, dim3(256), lds, s, ev0, end_attn, a);
+  if (attn_two_groups(a, NB)) {
+    constexpr uint32_t lds_kg = (uint32_t)(4 * sizeof(AttnBlock<HD>));
+    UAD_LAUNCH((attn_kernel<HD, 1, true, 8, 2>), grid, dim3(512), lds_kg, s, ev0, end_attn, a);
+  } else if (streamed)
+    UAD_LAUNCH((attn_kernel<HD, 1, true, 4, 1>), grid, dim3(256), lds, s, ev0, end_attn, a);
   else
-    UAD_LAUNCH((attn_kernel<HD, NB, false, 4>), grid, dim3(256), lds, s, ev0, end_attn, a);
+    UAD_LAUNCH((attn_kernel<HD, NB, false, 4, 1>), grid, dim3(256), lds, s, ev0, end_attn, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.splits == 1) return e;
   hipEvent_t none = nullptr;
@@ -451,7 +525,7 @@ static hipError_t launch_hd(const AttnArgs &a, int batch, hipStream_t s, hipEven
   // are ~900 one-wave workgroups at batch 1): same-machine, three pairs,
   // 0.7066 -> 0.7037 ms per step; at 8 environments (4 splits) one wave per
   // workgroup stays ahead (1.663 vs 1.677 ms).
-  const int W = a.splits > 8 ? 4 : 1;
+  const int W = merge_waves(a.splits);
   ac.pre_comb.wgs = a.pre_comb.wgs ? (a.rows_pad / 16) * (HD / (16 * W)) : 0;  // one extra z slice
   const dim3 cgrid(a.rows_pad / 16, HD / (16 * W), batch * a.n_kv_heads + (ac.pre_comb.wgs ? 1 : 0));
   if (a.splits <= 4)
@@ -471,22 +545,25 @@ template <int HD>
 static hipError_t init_hd() {
   constexpr int NB = attn_chunk_blocks<HD>();
   constexpr int streamed_lds = (int)(2 * sizeof(AttnBlock<HD>));
-  hipError_t e = hipFuncSetAttribute((const void *)attn_kernel<HD, NB, false, 4>,
+  hipError_t e = hipFuncSetAttribute((const void *)attn_kernel<HD, NB, false, 4, 1>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)(2 * NB * sizeof(AttnBlock<HD>)));
   if (e == hipSuccess)
-    e = hipFuncSetAttribute((const void *)attn_kernel<HD, 1, true, 4>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    e = hipFuncSetAttribute((const void *)attn_kernel<HD, 1, true, 4, 1>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             streamed_lds);
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute((const void *)attn_kernel<HD, 1, true, 8, 2>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            2 * streamed_lds);
   constexpr int TB = attn_tall_blocks<HD>();
   constexpr int tall_lds = (int)(2 * TB * sizeof(AttnBlock<HD>));
   static_assert(tall_lds <= 160 * 1024, "stages exceed the LDS of a CU");
   if (e == hipSuccess)
-    e = hipFuncSetAttribute((const void *)attn_kernel<HD, TB, true, 6>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    e = hipFuncSetAttribute((const void *)attn_kernel<HD, TB, true, 6, 1>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             tall_lds);
   if (e == hipSuccess)
-    e = hipFuncSetAttribute((const void *)attn_kernel<HD, TB, true, 7>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    e = hipFuncSetAttribute((const void *)attn_kernel<HD, TB, true, 7, 1>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             tall_lds);
   if (e == hipSuccess)
-    e = hipFuncSetAttribute((const void *)attn_kernel<HD, TB, true, 8>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    e = hipFuncSetAttribute((const void *)attn_kernel<HD, TB, true, 8, 1>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             tall_lds);
   return e;
 }
@@ -503,6 +580,26 @@ hipError_t attention_init() {
 }
 
 int attention_max_splits(int) { return 32; }
+
+// Below kBigM rows the launches that carry the read-ahead are short, so it stops
+// at about what its workgroups read meanwhile (~2.5 TB/s in all, 40 GB/s for one
+// workgroup, 0.07 GB/s a lane of the one-wave merge workgroups); past that the
+// launch waits for it.  Same-machine, us per joint step: 1536-wide expert of 4
+// layers at one environment 302 -> 256 (chunk 50, 1024 keys) and 300 -> 279
+// (chunk 90, 300 keys); 1024-wide at 12 environments of 17 tokens 453 -> 427.
+// From kBigM rows on the batched gate/up gains more from the whole read-ahead
+// than the attention loses (1536-wide, 3 environments: gate/up 40.7 -> 31.0 us,
+// attention 23.3 -> 25.5), so no cap there.
+void attention_read_ahead_caps(const AttnArgs &a, int head_dim, int wgs, size_t *attn, size_t *merge) {
+  const int nb = attention_chunk_blocks(head_dim);
+  const bool two = attn_two_groups(a, nb);
+  const int serial = two ? (a.blocks_per_split + 1) / 2 : a.blocks_per_split;
+  const size_t extra = (size_t)std::max(0, serial - nb), KB = 1024;
+  const size_t all = (22528 + 2560 * extra) * KB, per_wg = (288 + 56 * extra) * KB;
+  const size_t lanes = (size_t)(a.rows_pad / 16) * (head_dim / 16) * 64;
+  *attn = std::min(*attn, std::min(all, per_wg * (size_t)wgs));
+  *merge = std::min(*merge, lanes * 480);
+}
 
 int attention_chunk_blocks(int head_dim) {
   switch (head_dim) {

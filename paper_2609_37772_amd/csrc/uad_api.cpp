@@ -129,25 +129,13 @@ hipEvent_t pool_event(uad_ctx *c) {
 // extra workgroups (below that the read-ahead is not issued).
 constexpr int kReadAheadMinCus = 32;
 
-int attn_splits_nb(const uad_ctx *c, int B, int H, int n_blocks, int *bps) {
-  const int rows = (c->Hq / c->Hkv) * H;
-  const int qblocks = (rows + 63) / 64;
+// The most key splits that any call with these sizes takes: the workspace and
+// the limit of the no-allocation step are sized by it.  It fills one round of
+// workgroups (256) with query blocks x splits, one chunk (one memory round
+// trip) per split when that fits.
+int attn_splits_max(const uad_ctx *c, int B, int H, int n_blocks) {
+  const int qblocks = ((c->Hq / c->Hkv) * H + 63) / 64;
   const int wgs = qblocks * B * c->Hkv;
-  // Split the keys so that the query blocks x splits fill about one round of
-  // workgroups (256 CUs): one chunk (one memory round trip) per split when
-  // that fits (batch 1), else floor(256 / query blocks) splits (a few
-  // environments; measured best at 4 and 8 environments), none when the query
-  // blocks alone fill the chip.  Where the projections run on the batched
-  // kernels, fewer splits if the grid (its groups padded to a multiple of the
-  // 8 XCDs) would leave under kReadAheadMinCus CUs to the weight read-ahead:
-  // gate/up then streams its weights from HBM (~28.5 instead of ~22.5 us at
-  // 300-850 rows).  Same-machine, ms per joint step, 1024-wide expert: 6
-  // environments 1.616 -> 1.588 (6 -> 5 splits), 7 1.679 -> 1.608, 9 1.769 ->
-  // 1.695, 11 2.003 -> 1.924, 12 2.053 -> 1.947 (3 -> 2), 17 2.354 -> 2.276
-  // (2 -> 1); 1536-wide: 2 environments 2.683 -> 2.581, 5 3.395 -> 3.262.
-  // Below 256 rows (5 environments: 7 -> 6 splits, 1.442 -> 1.451 ms) the
-  // small-M projections gain less from the read-ahead than the attention
-  // loses.
   const int nb = attention_chunk_blocks(c->hd);
   int per = nb;
   if ((long)wgs * ((n_blocks + nb - 1) / nb) > 256) {
@@ -161,17 +149,46 @@ int attn_splits_nb(const uad_ctx *c, int B, int H, int n_blocks, int *bps) {
   const int smax = attention_max_splits(c->hd);
   if ((n_blocks + per - 1) / per > smax) per = (n_blocks + smax - 1) / smax;
   if (per > n_blocks) per = n_blocks;
-  *bps = per;
   return (n_blocks + per - 1) / per;
+}
+
+// Key splits of a call and the 32-key blocks of each.  One chunk per split
+// while the grid (its groups padded to a multiple of the 8 XCDs) fills at most
+// half the CUs: the others read weights ahead.  Beyond that two chunks or more
+// per split (longer splits run as two key groups inside the workgroup), as many
+// splits as leave kReadAheadMinCus CUs to the read-ahead, without which gate/up
+// streams its weights from HBM (~27.5 instead of ~22 us at 300-850 rows).
+// Same-machine, 1024-wide expert of 6 layers, us per joint step, 816 + 50 keys
+// (28 blocks), by splits:
+//   environments   14     10      7      5      4      3      2      1
+//        1         241    247    241    250    255    262    278    311
+//        2         350    325    325    334    335    341    357    389
+//        3         395    394    358    368    368    373    391    420
+//        4         442    453    409    417    417    427    442    464
+//        6         599    580    553    499    492    506    513    537
+//        8         674    665    601    606    544    548    562    573
+//       12         834    832    722    719    715    723    660    672
+//       20        1082   1065    888    894    872    859    879    783
+int attn_splits_nb(const uad_ctx *c, int B, int H, int n_blocks, int *bps) {
+  const int qblocks = ((c->Hq / c->Hkv) * H + 63) / 64;
+  const int nb = attention_chunk_blocks(c->hd);
+  auto grid = [&](int sp) { return 8L * (((long)B * c->Hkv * sp + 7) / 8) * qblocks; };
+  const int most = attn_splits_max(c, B, H, n_blocks);
+  int sp = std::min(most, (n_blocks + nb - 1) / nb);
+  if (2 * grid(sp) > c->n_cu) {
+    sp = std::min(most, (n_blocks + 2 * nb - 1) / (2 * nb));
+    while (sp > 1 && grid(sp) > c->n_cu - kReadAheadMinCus) --sp;
+  }
+  *bps = (n_blocks + sp - 1) / sp;
+  return (n_blocks + *bps - 1) / *bps;
 }
 
 int attn_splits(const uad_ctx *c, int B, int H, int P, int *bps) { return attn_splits_nb(c, B, H, (P + H + 31) / 32, bps); }
 
 // Split-KV partial rows (x head_dim) that a call with B environments, chunk H
-// and prefix P writes.
+// and prefix P may write.
 size_t attn_part_rows(const uad_ctx *c, int B, int H, int P) {
-  int bps;
-  const int sp = attn_splits(c, B, H, P, &bps);
+  const int sp = attn_splits_max(c, B, H, (P + H + 31) / 32);
   if (sp <= 1) return 0;
   const size_t rows_pad = (size_t)((c->Hq / c->Hkv) * H + 63) / 64 * 64;
   return (size_t)sp * B * c->Hkv * rows_pad;
@@ -354,8 +371,7 @@ uad_status uad_create(const uad_model_config *cfg, int32_t device, void *hip_str
   for (int B = 1; B <= m.max_batch; ++B)
     for (int H = 1; H <= m.max_chunk; ++H)
       for (int nb = (H + 31) / 32; nb <= (m.max_prefix + H + 31) / 32; ++nb) {
-        int bps;
-        const int sp = attn_splits_nb(c, B, H, nb, &bps);
+        const int sp = attn_splits_max(c, B, H, nb);
         if (sp > 1) {
           const size_t rows_pad = (size_t)((c->Hq / c->Hkv) * H + 63) / 64 * 64;
           part = std::max(part, (size_t)sp * B * c->Hkv * rows_pad);
@@ -871,16 +887,20 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
       at.pre_attn = Prefetch{};
       at.pre_comb = Prefetch{};
       if (spare_cus >= kReadAheadMinCus) {
+        const size_t wo_bytes = (size_t)d * c->q_dim * sizeof(op_t), wgu_bytes = (size_t)2 * F * d * sizeof(op_t);
+        const size_t wd_bytes = (size_t)d * F * sizeof(op_t), wq_bytes = (size_t)c->n_qkv * d * sizeof(op_t);
+        size_t cap = wo_bytes + wgu_bytes, cap_comb = wd_bytes + wq_bytes;
+        if (M < kBigM) attention_read_ahead_caps(at, c->hd, spare_cus, &cap, &cap_comb);
         at.pre_attn.p[0] = (const char *)lp.wo;
-        at.pre_attn.bytes[0] = (uint32_t)((size_t)d * c->q_dim * sizeof(op_t));
+        at.pre_attn.bytes[0] = (uint32_t)std::min(wo_bytes, cap);
         at.pre_attn.p[1] = (const char *)lp.wgu;
-        at.pre_attn.bytes[1] = (uint32_t)((size_t)2 * F * d * sizeof(op_t));
+        at.pre_attn.bytes[1] = (uint32_t)std::min(wgu_bytes, cap - at.pre_attn.bytes[0]);
         at.pre_attn.wgs = spare_cus;
         if (at.splits > 1) {
           at.pre_comb.p[0] = (const char *)lp.wdown;
-          at.pre_comb.bytes[0] = (uint32_t)((size_t)d * F * sizeof(op_t));
+          at.pre_comb.bytes[0] = (uint32_t)std::min(wd_bytes, cap_comb);
           at.pre_comb.p[1] = (const char *)c->layers[(l + 1) % c->L].wqkv;
-          at.pre_comb.bytes[1] = (uint32_t)((size_t)c->n_qkv * d * sizeof(op_t));
+          at.pre_comb.bytes[1] = (uint32_t)std::min(wq_bytes, cap_comb - at.pre_comb.bytes[0]);
           at.pre_comb.wgs = 1;
         }
       }

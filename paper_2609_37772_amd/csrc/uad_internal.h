@@ -316,6 +316,9 @@ hipError_t launch_attention(const AttnArgs &a, int batch, int head_dim, hipStrea
                             hipEvent_t ev1 = nullptr);
 hipError_t attention_init();             // once per context: raise the kernels' LDS limit
 hipError_t gemm_init();                  // once per context: raise the batched GEMM's LDS limit
+// lowers the read-ahead of the attention (by `wgs` workgroups) and of the split
+// merge to the weight bytes that they can read while those run
+void attention_read_ahead_caps(const AttnArgs &a, int head_dim, int wgs, size_t *attn, size_t *merge);
 int attention_chunk_blocks(int head_dim);  // 32-key blocks loaded per round trip
 int attention_max_splits(int head_dim);    // split-KV partials the combine accepts
 // env_map (compacted steps): token m of the step reads x and t of token
