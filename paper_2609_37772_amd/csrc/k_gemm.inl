@@ -65,7 +65,7 @@ __device__ __forceinline__ void epilogue_elem(const GemmArgs &g, int row, bool r
         const int r6 = col - l * per_layer;
         const int part = r6 / g.d_model, j = r6 - part * g.d_model;
         const int KBd = g.d_model / kTileK;
-        if (part == 1 || part == 4)
+        if (g.mod_shift_ops && (part == 1 || part == 4))
           store_op(g.mod_shift_ops + (size_t)(2 * l + (part == 4)) * g.shift_stride + afrag_index(row, j, KBd), mv, bad);
         else if (part == 0 && l == 0 && g.next)
           store_op(g.next + afrag_index(row, j, KBd), g.h_in[(size_t)row * g.d_model + j] * (1.0f + mv), bad);
@@ -125,7 +125,9 @@ static int g_n_cu = 256;  // compute units of the device (set by gemm_init)
 // double buffered, so the loads of pass p + 1 are in flight while the MFMAs
 // of pass p run and a launch pays one memory round trip instead of one per
 // pass.
-template <int EPI, int T, int KPW, bool DUAL, bool PIPE = false>
+// MAP: g.mod_row / g.m_dev are in use (batched adaptive norm; an instance of its
+// own, since the test alone cost the batch-1 residual projections 0.5 us each).
+template <int EPI, int T, int KPW, bool DUAL, bool PIPE, bool MAP>
 __global__ __launch_bounds__(512) void gemm_kernel(GemmArgs g) {
   static_assert(!(PIPE && DUAL), "double-buffered passes: single operand only");
   extern __shared__ float red[];  // [waves][4*T*4 slots][64 lanes]
@@ -142,6 +144,10 @@ __global__ __launch_bounds__(512) void gemm_kernel(GemmArgs g) {
   const int m0 = mt0 * 16;
   const int KB = g.K / kTileK;
   const int passes = KB / (KPW * waves);
+  if constexpr (MAP && EPI != EPI_RESID_F32) {
+    g.M = min(g.M, *g.m_dev);
+    if (m0 >= g.M) return;  // whole workgroup
+  }
 
   f32x4 acc[kMaxTilesPerGroup][T], acc2[kMaxTilesPerGroup][DUAL ? T : 1];
 #pragma unroll
@@ -227,7 +233,7 @@ __global__ __launch_bounds__(512) void gemm_kernel(GemmArgs g) {
       const int row = min(m0 + mt * 16 + (ln >> 4) * 4 + r, g.M - 1);
       const int col = min((tile0 + t) * 16 + (ln & 15), g.N - 1);
       const float *hp = (const float *)g.out + (size_t)row * g.ldo + col;
-      const size_t ro = (size_t)row * g.mod_ld + col;
+      const size_t ro = (size_t)(MAP ? g.mod_row[row] : row) * g.mod_ld + col;
       const float *sp = has_mod ? g.mod_scale_next + ro : (has_gain ? g.gain_next + col : hp);
       const float *gp = has_gate ? g.mod_gate + ro : hp;
       const float hv = *hp, sv = *sp, gv = *gp;
@@ -332,7 +338,7 @@ __global__ __launch_bounds__(512) void gemm_kernel(GemmArgs g) {
         if (it == k) { h0 = pre_h[k]; sc = pre_s[k]; gt = pre_g[k]; }
       if (it >= kEpiPrefetch && row_ok) {
         const int col = (tile0 + t) * 16 + (ln & 15);
-        const size_t ro = (size_t)row * g.mod_ld + col;
+        const size_t ro = (size_t)(MAP ? g.mod_row[row] : row) * g.mod_ld + col;
         h0 = g.bias ? 0.f : ((const float *)g.out)[(size_t)row * g.ldo + col];
         sc = g.mod_scale_next ? 1.0f + g.mod_scale_next[ro] : (g.gain_next ? g.gain_next[col] : 0.f);
         gt = g.mod_gate ? g.mod_gate[ro] : 1.0f;
@@ -351,7 +357,14 @@ static hipError_t launch_t(const GemmArgs &g, const GemmPlan &p, hipStream_t s, 
   if constexpr (EPI == EPI_QKV || EPI == EPI_GEGLU) {
     if (g.A2) {
       if (!g.use_rstd) return hipErrorInvalidValue;
-      UAD_LAUNCH((gemm_kernel<EPI, T, KPW, true>), grid, dim3(p.waves * 64), lds, s, ev0, ev1, g);
+      UAD_LAUNCH((gemm_kernel<EPI, T, KPW, true, false, false>), grid, dim3(p.waves * 64), lds, s, ev0, ev1, g);
+      return hipGetLastError();
+    }
+  }
+  if constexpr (EPI == EPI_RESID_F32 || EPI == EPI_BIAS_SILU || EPI == EPI_MOD) {
+    if (g.mod_row || g.m_dev) {
+      if ((EPI == EPI_RESID_F32) != (g.mod_row != nullptr)) return hipErrorInvalidValue;
+      UAD_LAUNCH((gemm_kernel<EPI, T, KPW, false, false, true>), grid, dim3(p.waves * 64), lds, s, ev0, ev1, g);
       return hipGetLastError();
     }
   }
@@ -360,9 +373,9 @@ static hipError_t launch_t(const GemmArgs &g, const GemmPlan &p, hipStream_t s, 
   // passes, O 2; step 0.700 -> 0.696 ms same-machine; at 8 environments, 448
   // workgroups, they lost 4% against two co-resident workgroups per CU).
   if (p.passes > 1 && (long)grid.x * grid.z <= g_n_cu)
-    UAD_LAUNCH((gemm_kernel<EPI, T, KPW, false, true>), grid, dim3(p.waves * 64), lds, s, ev0, ev1, g);
+    UAD_LAUNCH((gemm_kernel<EPI, T, KPW, false, true, false>), grid, dim3(p.waves * 64), lds, s, ev0, ev1, g);
   else
-    UAD_LAUNCH((gemm_kernel<EPI, T, KPW, false>), grid, dim3(p.waves * 64), lds, s, ev0, ev1, g);
+    UAD_LAUNCH((gemm_kernel<EPI, T, KPW, false, false, false>), grid, dim3(p.waves * 64), lds, s, ev0, ev1, g);
   return hipGetLastError();
 }
 
@@ -435,14 +448,16 @@ __device__ __forceinline__ void st4h(op_t *p, f32x4 v, unsigned &bad) {
 
 // Residual epilogue, store half, over NI row tiles starting at i0: h = h0 (or
 // bias) + gate * v, per-16-column sums of squares of h, next operand
-// fp16(h * scale).  ADA: gate and scale are per-token modulations ([NI][TB]),
-// else gate = 1 and scale = gain_next (one row [1][TB]).
+// fp16(h * scale), scale = gain_next (one row [TB]).  ADA: the gate is a
+// per-token modulation and the next norm a pass of its own (no next operand);
+// else gate = 1.
 template <int NI, bool ADA, int TA, int TB>
 __device__ __forceinline__ void big_resid_store(const GemmArgs &g, const f32x4 (&acc)[TA][TB], int i0, int mt, int nt,
                                                 int lane, const f32x4 (&h0)[NI][TB],
                                                 const f32x4 (&gt)[ADA ? NI : 1][TB],
-                                                const f32x4 (&sc)[ADA ? NI : 1][TB], bool has_next, unsigned &bad) {
+                                                const f32x4 (&sc)[TB], unsigned &bad) {
   float *h = (float *)g.out;
+  const bool has_next = !ADA && g.gain_next != nullptr;
   const int csub = 4 * (lane >> 4);
   const int KBn = g.N / kTileK;
 #pragma unroll
@@ -458,26 +473,29 @@ __device__ __forceinline__ void big_resid_store(const GemmArgs &g, const f32x4 (
       sq = sum_pair32(sum_pair16(sq));  // the 4 lanes holding this row's 16 columns
       if (row_ok) {
         if (lane < 16) g.ssq[(size_t)tile * g.m_alloc + row] = sq;
-        if (has_next) st4h(g.next + afrag_index(row, col, KBn), hv * sc[ADA ? ii : 0][j], bad);
+        if (has_next) st4h(g.next + afrag_index(row, col, KBn), hv * sc[j], bad);
       }
     }
   }
 }
 
 // Residual epilogue, load half: h0 (or the bias) of NI row tiles from i0, and
-// the scale (and, ADA, the gate) of the next operand.  Branch-free: every load
+// the next operand's scale or (ADA) the gate.  Branch-free: every load
 // comes from a valid address (an absent operand is stood in for by one that
 // exists) and the value is selected afterwards, so no load waits on another.
 template <int NI, bool ADA, int TB>
 __device__ __forceinline__ void big_resid_load(const GemmArgs &g, int i0, int mt, int nt, int lane,
-                                               f32x4 (&h0)[NI][TB], f32x4 (&gt)[ADA ? NI : 1][TB],
-                                               f32x4 (&sc)[ADA ? NI : 1][TB]) {
+                                               f32x4 (&h0)[NI][TB], f32x4 (&gt)[ADA ? NI : 1][TB], f32x4 (&sc)[TB]) {
   const int csub = 4 * (lane >> 4);
-  const bool has_next = ADA ? g.mod_scale_next != nullptr : g.gain_next != nullptr;
+  const bool has_next = g.gain_next != nullptr;
   const float *hb = g.bias ? g.bias : (const float *)g.out;
   const size_t hld = g.bias ? 0 : (size_t)g.ldo;
-  const float *sb = ADA ? (has_next ? g.mod_scale_next : g.mod_gate) : (has_next ? g.gain_next : hb);
-  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  const float *sb = has_next ? g.gain_next : hb;
+  size_t mr[ADA ? NI : 1];  // the rows' modulation rows, loaded ahead of what they address
+  if constexpr (ADA)
+#pragma unroll
+    for (int ii = 0; ii < NI; ++ii)
+      mr[ii] = (size_t)g.mod_row[min((mt + i0 + ii) * 16 + (lane & 15), g.M - 1)] * g.mod_ld;
 #pragma unroll
   for (int ii = 0; ii < NI; ++ii) {
     const int rowc = min((mt + i0 + ii) * 16 + (lane & 15), g.M - 1);
@@ -485,15 +503,11 @@ __device__ __forceinline__ void big_resid_load(const GemmArgs &g, int i0, int mt
     for (int j = 0; j < TB; ++j) {
       const int col = (nt + j) * 16 + csub;
       h0[ii][j] = ld4(hb + (size_t)rowc * hld + col);
-      if (ADA) {
-        const size_t ro = (size_t)rowc * g.mod_ld + col;
-        gt[ADA ? ii : 0][j] = ld4(g.mod_gate + ro);
-        const f32x4 sv = ld4(sb + ro);
-        sc[ADA ? ii : 0][j] = has_next ? sv + 1.0f : zero;
+      if constexpr (ADA) {
+        gt[ii][j] = ld4(g.mod_gate + mr[ii] + col);
       } else if (ii == 0) {
-        gt[0][j] = f32x4{1.f, 1.f, 1.f, 1.f};
         const f32x4 sv = ld4(sb + col);
-        sc[0][j] = has_next ? sv : zero;
+        sc[j] = has_next ? sv : f32x4{0.f, 0.f, 0.f, 0.f};
       }
     }
   }
@@ -505,10 +519,9 @@ __device__ __forceinline__ void big_resid_load(const GemmArgs &g, int i0, int mt
 template <int NI, bool ADA, int TA, int TB>
 __device__ __forceinline__ void big_resid_rows(const GemmArgs &g, f32x4 (&acc)[TA][TB], int i0, int mt, int nt,
                                                int lane, unsigned &bad) {
-  f32x4 h0[NI][TB], gt[ADA ? NI : 1][TB], sc[ADA ? NI : 1][TB];
+  f32x4 h0[NI][TB], gt[ADA ? NI : 1][TB], sc[TB];
   big_resid_load<NI, ADA, TB>(g, i0, mt, nt, lane, h0, gt, sc);
-  const bool has_next = ADA ? g.mod_scale_next != nullptr : g.gain_next != nullptr;
-  big_resid_store<NI, ADA, TA, TB>(g, acc, i0, mt, nt, lane, h0, gt, sc, has_next, bad);
+  big_resid_store<NI, ADA, TA, TB>(g, acc, i0, mt, nt, lane, h0, gt, sc, bad);
 }
 
 template <int EPI, int TA, int TB, int I0 = 0, int NI = TA>
@@ -517,8 +530,9 @@ __device__ __forceinline__ void big_epilogue(const GemmArgs &g, f32x4 (&acc)[TA]
   const int csub = 4 * (lane >> 4);
   if constexpr (EPI == EPI_RESID_F32) {
     if (g.mod_gate) {
+      constexpr int HB = NI % 2 == 0 ? 2 : 1;
 #pragma unroll
-      for (int i = I0; i < I0 + NI; ++i) big_resid_rows<1, true>(g, acc, i, mt, nt, lane, bad);
+      for (int i = I0; i < I0 + NI; i += HB) big_resid_rows<HB, true>(g, acc, i, mt, nt, lane, bad);
     } else {
       // the whole tile in two halves: all of its h0 at once would cost the
       // main loop its second wave per SIMD (a half tile goes in one piece)
@@ -611,11 +625,8 @@ __device__ __forceinline__ void big_epilogue(const GemmArgs &g, f32x4 (&acc)[TA]
         if (l < g.n_layers) {
           const int r6 = col - l * per_layer;
           const int part = r6 / g.d_model, jc = r6 - part * g.d_model;
-          if (part == 1 || part == 4)
+          if (g.mod_shift_ops && (part == 1 || part == 4))
             st4h(g.mod_shift_ops + (size_t)(2 * l + (part == 4)) * g.shift_stride + afrag_index(row, jc, KBd), mv,
-                 bad);
-          else if (part == 0 && l == 0 && g.next)
-            st4h(g.next + afrag_index(row, jc, KBd), ld4(g.h_in + (size_t)row * g.d_model + jc) * (mv + 1.0f),
                  bad);
         }
       }
@@ -623,27 +634,33 @@ __device__ __forceinline__ void big_epilogue(const GemmArgs &g, f32x4 (&acc)[TA]
   }
 }
 
-// DUAL (adaptive norm, QKV / gate-up): a second accumulator takes A2 W (the
-// norm's shift through the weights) and is added after the rows' rstd has
-// scaled the first: rstd * (A W) + A2 W.
 // KS = 2 (when the output tiles fill at most one round of CUs, so that a
 // 4-wave workgroup would leave each SIMD a single wave): 8 waves, waves
 // 4..7 take the odd k-blocks of the same tile; the two partial tiles are
 // summed through LDS and each k-half then runs the epilogue of half the
 // wave's row tiles.
-template <int EPI, int CT, bool DUAL = false, int KS = 1>
+template <int EPI, int CT, int KS = 1>
 __global__ __launch_bounds__(256 * KS) void gemm_big_kernel(GemmArgs g) {
   constexpr int TA = kBigRowTiles / 2, TB = CT / 2, PD = kBigPD;
   constexpr bool kRstd = (EPI == EPI_QKV || EPI == EPI_GEGLU);
-  static_assert(!DUAL || kRstd, "the second operand belongs to a normalised projection");
-  static_assert(KS == 1 || (KS == 2 && !DUAL && TA % 2 == 0), "k-halves: single operand, even row tiles");
+  static_assert(KS == 1 || (KS == 2 && TA % 2 == 0), "k-halves: even row tiles");
   typedef __attribute__((address_space(3))) void lds_void;
   // [ssq_tiles][128] sums of squares of the workgroup's rows when kRstd;
   // KS = 2: then the k-halves' exchange, [4 waves][2 halves][TA/2][TB][64] f32x4
   extern __shared__ __align__(16) float ssq_s[];
   __shared__ float rstd_s[128];
   int mt0, nt0;
-  if (!big_tile<CT>(g, mt0, nt0)) return;  // whole workgroup: padding of the grid
+  if ((EPI == EPI_MOD || EPI == EPI_BIAS_SILU) && g.m_dev) {
+    // row count known on the device only (usually one panel): panel-major over
+    // the XCDs, so that the existing rows' tiles use every CU
+    const int tn = g.N / (16 * CT), pm = (int)blockIdx.x / tn;
+    mt0 = pm * kBigRowTiles;
+    nt0 = ((int)blockIdx.x - pm * tn) * CT;
+    g.M = min(g.M, *g.m_dev);
+    if (mt0 * 16 >= g.M) return;
+  } else if (!big_tile<CT>(g, mt0, nt0)) {
+    return;  // whole workgroup: padding of the grid
+  }
   // wave index through readfirstlane: scalar per-wave addressing, up to 14 fewer VGPRs
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wq = wave & 3, kh = wave >> 2;  // position in the 2 x 2 wave grid, k-half
@@ -667,12 +684,7 @@ __global__ __launch_bounds__(256 * KS) void gemm_big_kernel(GemmArgs g) {
 #pragma unroll
   for (int j = 0; j < TB; ++j) pb[j] = g.W + ((size_t)(nt0 + wc * TB + j) * KB + kh) * kBlockElems + lane * 8;
   constexpr size_t kStep = (size_t)KS * kBlockElems;  // between this wave's consecutive k-blocks
-  constexpr int TA2 = DUAL ? TA : 1;
-  const op_t *pa2[TA2];
-#pragma unroll
-  for (int i = 0; i < TA2; ++i)
-    pa2[i] = DUAL ? g.A2 + (size_t)min(mt0 + wr * TA + i, mt_last) * KB * kBlockElems + lane * 8 : nullptr;
-  f16x8 ra[PD][TA], rb[PD][TB], ra2[PD][TA2];
+  f16x8 ra[PD][TA], rb[PD][TB];
 #pragma unroll
   for (int s = 0; s < PD; ++s) {
     const int kb = min(s, nkb - 1);
@@ -680,20 +692,12 @@ __global__ __launch_bounds__(256 * KS) void gemm_big_kernel(GemmArgs g) {
     for (int i = 0; i < TA; ++i) ra[s][i] = *(const f16x8 *)(pa[i] + kb * kStep);
 #pragma unroll
     for (int j = 0; j < TB; ++j) rb[s][j] = *(const f16x8 *)(pb[j] + kb * kStep);
-    if constexpr (DUAL)
-#pragma unroll
-      for (int i = 0; i < TA; ++i) ra2[s][i] = *(const f16x8 *)(pa2[i] + (size_t)kb * kBlockElems);
   }
-  f32x4 acc[TA][TB], acc2[TA2][DUAL ? TB : 1];
+  f32x4 acc[TA][TB];
 #pragma unroll
   for (int i = 0; i < TA; ++i)
 #pragma unroll
     for (int j = 0; j < TB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  if constexpr (DUAL)
-#pragma unroll
-    for (int i = 0; i < TA; ++i)
-#pragma unroll
-      for (int j = 0; j < TB; ++j) acc2[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   for (int k0 = 0; k0 < nkb; k0 += PD) {
 #pragma unroll
     for (int s = 0; s < PD; ++s) {
@@ -701,20 +705,14 @@ __global__ __launch_bounds__(256 * KS) void gemm_big_kernel(GemmArgs g) {
 #pragma unroll
         for (int i = 0; i < TA; ++i)
 #pragma unroll
-          for (int j = 0; j < TB; ++j) {
+          for (int j = 0; j < TB; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(rb[s][j], ra[s][i], acc[i][j], 0, 0, 0);
-            if constexpr (DUAL)
-              acc2[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(rb[s][j], ra2[s][i], acc2[i][j], 0, 0, 0);
-          }
       }
       const int kb = min(k0 + s + PD, nkb - 1);  // past the end: re-load the last block (never used)
 #pragma unroll
       for (int i = 0; i < TA; ++i) ra[s][i] = *(const f16x8 *)(pa[i] + kb * kStep);
 #pragma unroll
       for (int j = 0; j < TB; ++j) rb[s][j] = *(const f16x8 *)(pb[j] + kb * kStep);
-      if constexpr (DUAL)
-#pragma unroll
-        for (int i = 0; i < TA; ++i) ra2[s][i] = *(const f16x8 *)(pa2[i] + (size_t)kb * kBlockElems);
     }
   }
 
@@ -730,16 +728,7 @@ __global__ __launch_bounds__(256 * KS) void gemm_big_kernel(GemmArgs g) {
   }
 
   unsigned bad = 0;  // fp16 range flag of this thread's stores
-  if constexpr (DUAL) {
-    // lane l of tile (i, j) holds row l & 15 (swapped operands)
-#pragma unroll
-    for (int i = 0; i < TA; ++i) {
-      const float rs = rstd_s[wr * TA * 16 + i * 16 + (lane & 15)];
-#pragma unroll
-      for (int j = 0; j < TB; ++j) acc[i][j] = rs * acc[i][j] + acc2[i][j];
-    }
-    big_epilogue<EPI, TA, TB>(g, acc, mt0 + wr * TA, nt0 + wc * TB, lane, nullptr, bad);
-  } else if constexpr (KS == 2) {
+  if constexpr (KS == 2) {
     // Wave (wq, 0) keeps row tiles [0, H) and hands [H, TA) to wave (wq, 1),
     // which keeps [H, TA); each adds the other's partial of what it keeps.
     constexpr int H = TA / 2;
@@ -1174,7 +1163,7 @@ static hipError_t launch_big_ct(const GemmArgs &g, hipStream_t s, hipEvent_t ev0
   const int wgs = grid_tile_wgs(g.M, 16 * kBigRowTiles, g.N / (16 * CT));
   if constexpr (CT <= 8 && (EPI == EPI_RESID_F32 || EPI == EPI_QKV || EPI == EPI_BIAS_SILU)) {
     if (big_khalves<EPI, CT>(g)) {
-      UAD_LAUNCH((gemm_big_kernel<EPI, CT, false, 2>), dim3(wgs), dim3(512), (uint32_t)(lds + big_xch_bytes<CT>()), s,
+      UAD_LAUNCH((gemm_big_kernel<EPI, CT, 2>), dim3(wgs), dim3(512), (uint32_t)(lds + big_xch_bytes<CT>()), s,
                  ev0, ev1, g);
       return hipGetLastError();
     }
@@ -1185,15 +1174,6 @@ static hipError_t launch_big_ct(const GemmArgs &g, hipStream_t s, hipEvent_t ev0
 
 template <int EPI>
 static hipError_t launch_big(const GemmArgs &g, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-  if constexpr (EPI == EPI_QKV || EPI == EPI_GEGLU) {
-    if (g.A2) {  // the second accumulator: 128-column tiles keep the registers in bounds
-      if (!g.use_rstd) return hipErrorInvalidValue;
-      const size_t lds = (size_t)g.ssq_tiles * 128 * 4;
-      const int wgs = grid_tile_wgs(g.M, 16 * kBigRowTiles, g.N / (16 * 8));
-      UAD_LAUNCH((gemm_big_kernel<EPI, 8, true>), dim3(wgs), dim3(256), (uint32_t)lds, s, ev0, ev1, g);
-      return hipGetLastError();
-    }
-  }
   if constexpr (EPI == EPI_RESID_F32)
     if (resid_prefers_96(g)) return launch_big_ct<EPI, 6>(g, s, ev0, ev1);
   return launch_big_ct<EPI, big_ct<EPI>()>(g, s, ev0, ev1);
@@ -1207,9 +1187,9 @@ static hipError_t launch_big(const GemmArgs &g, hipStream_t s, hipEvent_t ev0, h
 // the projection shapes of the 1024- and 1536-wide experts (the rule picks
 // the faster kernel in 49 of 50 cases, the miss by 6%).
 static bool big_ok(int epi, const GemmArgs &g) {
-  const int ct = (epi == EPI_GEGLU && !g.A2) ? 16 : 8;
+  const int ct = epi == EPI_GEGLU ? 16 : 8;
   if (g.M < kBigM || g.N % (16 * ct) != 0 || g.ssq_tiles > kMaxSsqTiles || (epi == EPI_QKV && g.q_dim % 16 != 0) ||
-      (g.A2 && epi != EPI_QKV && epi != EPI_GEGLU))
+      g.A2 || g.mod_scale_next)
     return false;
   const int tiles = (g.M + 16 * kBigRowTiles - 1) / (16 * kBigRowTiles) * (g.N / (16 * ct));
   return tiles >= 90 && !(tiles < 128 && g.K > 4096);
@@ -1221,19 +1201,15 @@ static hipError_t big_attr() {
                                      hipFuncAttributeMaxDynamicSharedMemorySize, kMaxSsqTiles * 128 * 4);
   if constexpr (EPI == EPI_RESID_F32 || EPI == EPI_QKV || EPI == EPI_BIAS_SILU) {
     if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void *)gemm_big_kernel<EPI, 8, false, 2>,
+      e = hipFuncSetAttribute((const void *)gemm_big_kernel<EPI, 8, 2>,
                               hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)(kMaxSsqTiles * 128 * 4 + big_xch_bytes<8>()));
     if constexpr (EPI == EPI_RESID_F32)
       if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)gemm_big_kernel<EPI, 6, false, 2>,
+        e = hipFuncSetAttribute((const void *)gemm_big_kernel<EPI, 6, 2>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)(kMaxSsqTiles * 128 * 4 + big_xch_bytes<6>()));
   }
-  if constexpr (EPI == EPI_QKV || EPI == EPI_GEGLU)
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void *)gemm_big_kernel<EPI, 8, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              kMaxSsqTiles * 128 * 4);
   return e;
 }
 
@@ -1298,6 +1274,8 @@ GemmPlan plan_gemm(int epi, int M, int N, int K) {
 hipError_t launch_gemm(int epi, const GemmArgs &g, const GemmPlan &p, hipStream_t s, hipEvent_t ev0,
                        hipEvent_t ev1) {
   if (g.m_alloc < g.M || g.m_alloc % 16 != 0) return hipErrorInvalidValue;  // operand rows allocated
+  // the batched kernels gate by modulation row and leave the next norm to its own pass
+  if (g.M >= kBigM && g.mod_gate && (!g.mod_row || g.mod_scale_next)) return hipErrorInvalidValue;
   if (epi == EPI_GEGLU && ring_fits<EPI_GEGLU>(g)) return launch_ring<EPI_GEGLU>(g, s, ev0, ev1);
   if (epi == EPI_QKV && ring_fits<EPI_QKV>(g)) return launch_ring<EPI_QKV>(g, s, ev0, ev1);
   if (epi == EPI_RESID_F32) {

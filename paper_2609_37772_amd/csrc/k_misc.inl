@@ -179,7 +179,7 @@ __device__ __forceinline__ void euler_out(const FinalArgs &f, int mc, int a, flo
   }
 }
 
-template <int NC>
+template <int NC, bool MAP>
 __global__ __launch_bounds__(256) void final_kernel(FinalArgs f) {
   __shared__ float scratch[4];
   __shared__ float wsum[4][kFinalOuts];
@@ -196,13 +196,14 @@ __global__ __launch_bounds__(256) void final_kernel(FinalArgs f) {
     const float *__restrict__ hr = f.h + (size_t)m * d;
     float hv[NC], gv[NC], sv[NC], wv[kFinalOuts][NC];
     const bool ada = f.mod_scale != nullptr;
+    const size_t mrow = (size_t)(MAP ? f.mod_row[m] : m) * f.mod_ld;
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
       const int c = min(threadIdx.x + 256 * i, d - 1);
       hv[i] = hr[c];
       // adaptive norm: per-token scale (1 + a) and shift b; else the gain
-      gv[i] = ada ? 1.0f + f.mod_scale[(size_t)m * f.mod_ld + c] : f.gain[c];
-      sv[i] = ada ? f.mod_shift[(size_t)m * f.mod_ld + c] : 0.f;
+      gv[i] = ada ? 1.0f + f.mod_scale[mrow + c] : f.gain[c];
+      sv[i] = ada ? f.mod_shift[mrow + c] : 0.f;
 #pragma unroll
       for (int o = 0; o < kFinalOuts; ++o) wv[o][i] = f.w_out[(size_t)min(a0 + o, f.Da - 1) * d + c];
     }
@@ -235,7 +236,7 @@ __global__ __launch_bounds__(256) void final_kernel(FinalArgs f) {
   if (threadIdx.x < kFinalOuts && a0 + threadIdx.x < f.Da) euler_out(f, m, a0 + threadIdx.x, vs[threadIdx.x]);
 }
 
-// Batched steps (many tokens, no adaptive norm, no debug field): the
+// Batched steps (many tokens, no debug field): the
 // projection as a product on the fp32 MFMA (v_mfma_f32_16x16x4_f32), 16
 // tokens x all Da outputs per workgroup, the d columns split over its 4
 // waves: v = rstd * ((h * gain) W_out^T) + b_out.  The row-blocked form it
@@ -245,9 +246,12 @@ __global__ __launch_bounds__(256) void final_kernel(FinalArgs f) {
 // each lane reads 16-byte runs of h, gain and W_out and feeds the same
 // column to both operands.  The k-groups run in batches of 8 (uniform trip
 // count: the loop bound does not depend on kq), loads first.
-template <int NT>
+// ADA: the gain is the token's 1 + scale and its shift enters through a second
+// accumulator, v = rstd * ((h (1 + a)) W_out^T) + b W_out^T + b_out.
+template <int NT, bool ADA>
 __global__ __launch_bounds__(256) void final_mfma_kernel(FinalArgs f) {
   __shared__ f32x4 part[4][NT][64];  // per wave and output tile: each lane's accumulators
+  __shared__ f32x4 part2[ADA ? 4 : 1][ADA ? NT : 1][64];  // ... of the shift
   __shared__ float ssq[4][64];       // per wave and lane: partial sum of squares of the lane's row
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int m0 = blockIdx.x * 16, kq = lane >> 4;
@@ -256,18 +260,28 @@ __global__ __launch_bounds__(256) void final_mfma_kernel(FinalArgs f) {
 #pragma unroll
   for (int t = 0; t < NT; ++t) wr[t] = f.w_out + (size_t)min(16 * t + (lane & 15), f.Da - 1) * f.d;
   const int cpw = f.d >> 2;  // columns per wave (d % 512 == 0: whole batches)
-  f32x4 acc[NT];
+  f32x4 acc[NT], acc2[ADA ? NT : 1];
 #pragma unroll
   for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int t = 0; t < (ADA ? NT : 1); ++t) acc2[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const float *gr = f.gain, *sr = nullptr;
+  if constexpr (ADA) {
+    const int mc = min(m0 + (lane & 15), f.M - 1);
+    const size_t mr = (size_t)(f.mod_row ? f.mod_row[mc] : mc) * f.mod_ld;
+    gr = f.mod_scale + mr;
+    sr = f.mod_shift + mr;
+  }
   float ss = 0.f;
   // batches of 8 k-groups of 16 columns: all their loads go out before the first MFMA
   for (int b = 0; b < cpw; b += 128) {
     const int cb = wave * cpw + 4 * kq + b;
-    f32x4 hv[8], gv[8], wv[8][NT];
+    f32x4 hv[8], gv[8], sv[ADA ? 8 : 1], wv[8][NT];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       hv[u] = *(const f32x4 *)(hr + cb + 16 * u);
-      gv[u] = *(const f32x4 *)(f.gain + cb + 16 * u);
+      gv[u] = *(const f32x4 *)(gr + cb + 16 * u);
+      if constexpr (ADA) sv[u] = *(const f32x4 *)(sr + cb + 16 * u);
 #pragma unroll
       for (int t = 0; t < NT; ++t) wv[u][t] = *(const f32x4 *)(wr[t] + cb + 16 * u);
     }
@@ -277,13 +291,20 @@ __global__ __launch_bounds__(256) void final_mfma_kernel(FinalArgs f) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         ss += hv[u][e] * hv[u][e];
-        const float a = hv[u][e] * gv[u][e];
+        const float a = hv[u][e] * (ADA ? 1.0f + gv[u][e] : gv[u][e]);
 #pragma unroll
-        for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, wv[u][t][e], acc[t], 0, 0, 0);
+        for (int t = 0; t < NT; ++t) {
+          acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, wv[u][t][e], acc[t], 0, 0, 0);
+          if constexpr (ADA)
+            acc2[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(sv[u][e], wv[u][t][e], acc2[t], 0, 0, 0);
+        }
       }
   }
 #pragma unroll
-  for (int t = 0; t < NT; ++t) part[wave][t][lane] = acc[t];
+  for (int t = 0; t < NT; ++t) {
+    part[wave][t][lane] = acc[t];
+    if constexpr (ADA) part2[wave][t][lane] = acc2[t];
+  }
   ssq[wave][lane] = ss;
   __syncthreads();
   // thread (i, j): token m0 + i, outputs 16 t + j; D[i][j] of a tile sits in
@@ -302,9 +323,143 @@ __global__ __launch_bounds__(256) void final_mfma_kernel(FinalArgs f) {
     const int a = 16 * t + j;
     if (a < f.Da) {
       const float v = (part[0][t][src][cmp] + part[1][t][src][cmp]) + (part[2][t][src][cmp] + part[3][t][src][cmp]);
-      euler_out(f, m, a, rstd * v + f.b_out[a]);
+      float u = f.b_out[a];
+      if constexpr (ADA)
+        u += (part2[0][t][src][cmp] + part2[1][t][src][cmp]) + (part2[2][t][src][cmp] + part2[3][t][src][cmp]);
+      euler_out(f, m, a, rstd * v + u);
     }
   }
+}
+
+// Distinct flow times of a batched step's tokens, by bits (one workgroup): a
+// fleet's tokens share a handful of times, so the modulations (0.24 TFLOP and a
+// 1.4 GB result per step at 3200 tokens of the 1024-wide expert) are computed
+// once per time instead of once per token.  Keys go into an LDS hash table of
+// four times kMaxTimeClasses slots; a token reads its slot before it tries the
+// atomic, so equal times do not serialise.  More than kMaxTimeClasses distinct
+// times: every token its own class.
+constexpr int kMaxTimeClasses = 1024;
+__global__ __launch_bounds__(1024) void time_classes_kernel(const float *__restrict__ t, int M,
+                                                             int32_t *__restrict__ cls, float *__restrict__ cls_t,
+                                                             int *__restrict__ n_cls) {
+  constexpr unsigned SLOTS = 4 * kMaxTimeClasses, EMPTY = 0xFFFFFFFFu;
+  __shared__ unsigned keys[SLOTS];
+  __shared__ int ids[SLOTS];
+  __shared__ int count;
+  for (unsigned i = threadIdx.x; i < SLOTS; i += blockDim.x) keys[i] = EMPTY;
+  if (threadIdx.x == 0) count = 0;
+  __syncthreads();
+  auto key_of = [&](int m) {
+    const unsigned k = __float_as_uint(t[m]);
+    return k == EMPTY ? 0x7FC00000u : k;  // that NaN as another
+  };
+  auto slot_of = [&](unsigned k) { return (k * 2654435761u) >> 20; };  // 12 bits
+  static_assert(SLOTS == 4096, "slot_of");
+  for (int m = threadIdx.x; m < M; m += blockDim.x) {
+    const unsigned k = key_of(m);
+    unsigned sl = slot_of(k);
+    for (unsigned probe = 0; probe < SLOTS; ++probe, sl = (sl + 1) & (SLOTS - 1)) {
+      unsigned cur = __hip_atomic_load(&keys[sl], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      if (cur == EMPTY) {
+        if (__hip_atomic_load(&count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > kMaxTimeClasses) break;
+        cur = atomicCAS(&keys[sl], EMPTY, k);
+        if (cur == EMPTY) {
+          ids[sl] = atomicAdd(&count, 1);
+          break;
+        }
+      }
+      if (cur == k) break;
+    }
+  }
+  __syncthreads();
+  const int n = count;
+  if (n > kMaxTimeClasses) {
+    for (int m = threadIdx.x; m < M; m += blockDim.x) {
+      cls[m] = m;
+      cls_t[m] = t[m];
+    }
+  } else {
+    for (int m = threadIdx.x; m < M; m += blockDim.x) {
+      const unsigned k = key_of(m);
+      unsigned sl = slot_of(k);
+      while (keys[sl] != k) sl = (sl + 1) & (SLOTS - 1);  // every key is in the table
+      cls[m] = ids[sl];
+    }
+    for (unsigned i = threadIdx.x; i < SLOTS; i += blockDim.x)
+      if (keys[i] != EMPTY) cls_t[ids[i]] = __uint_as_float(keys[i]);
+  }
+  if (threadIdx.x == 0) *n_cls = n > kMaxTimeClasses ? M : n;
+}
+
+// Sinusoidal time features of the distinct flow times (see time_feat_kernel).
+__global__ __launch_bounds__(256) void class_feat_kernel(const float *__restrict__ cls_t, const int *__restrict__ n_cls,
+                                                          int d, const float *__restrict__ freqs,
+                                                          op_t *__restrict__ te, unsigned *status) {
+  const int r = blockIdx.x, n = blockIdx.y * blockDim.x + threadIdx.x, half = d >> 1;
+  if (r >= *n_cls || n >= half) return;
+  const float arg = freqs[n] * cls_t[r];
+  const int KB = d / kTileK;
+  float sv, cv;
+  sincosf(arg, &sv, &cv);
+  unsigned bad = 0;
+  store_op(te + afrag_index(r, n, KB), sv, bad);
+  store_op(te + afrag_index(r, half + n, KB), cv, bad);
+  flush_range(status, bad);
+}
+
+// Adaptive RMSNorm of a batched step as a pass of its own: the normalised
+// operand RMS(h) (1 + a) + b in fp16, so that QKV and gate/up are one product of
+// it instead of two (the scaled stream and the shift through the same weights).
+// Bound by reading h: a workgroup takes 16 rows (whole fragment blocks), each
+// thread 8 columns of one row at a time, h held in registers between the sum of
+// squares and the output.  NI = 256-column passes (d <= 256 NI).
+template <int NI>
+__global__ __launch_bounds__(512) void ada_norm_kernel(const float *__restrict__ h, int M, int d, float eps,
+                                                        const float *__restrict__ scale,
+                                                        const float *__restrict__ shift, int mod_ld,
+                                                        const int32_t *__restrict__ mod_row, op_t *__restrict__ next,
+                                                        unsigned *status) {
+  __shared__ float part[32][17];
+  const int r = threadIdx.x & 15, cg = threadIdx.x >> 4;
+  const int m = blockIdx.x * 16 + r, mc = min(m, M - 1);
+  const size_t mr = (size_t)mod_row[mc] * mod_ld;
+  f32x4 v[NI][2];
+  float ss = 0.f;
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int c = i * 256 + cg * 8;
+    const bool ok = c < d;
+    const float *p = h + (size_t)mc * d + (ok ? c : 0);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      v[i][q] = *(const f32x4 *)(p + 4 * q);
+      if (ok) ss += v[i][q][0] * v[i][q][0] + v[i][q][1] * v[i][q][1] + v[i][q][2] * v[i][q][2] + v[i][q][3] * v[i][q][3];
+    }
+  }
+  part[cg][r] = ss;
+  __syncthreads();
+  float s2 = 0.f;
+#pragma unroll
+  for (int q = 0; q < 32; ++q) s2 += part[q][r];
+  const float rstd = 1.0f / sqrtf(s2 / (float)d + eps);
+  unsigned bad = 0;
+  const int KB = d / kTileK;
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int c = i * 256 + cg * 8;
+    if (c >= d || m >= M) continue;
+    f16x8 o;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const f32x4 a = *(const f32x4 *)(scale + mr + c + 4 * q), b = *(const f32x4 *)(shift + mr + c + 4 * q);
+      const f32x4 n = v[i][q] * rstd * (a + 1.0f) + b;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[4 * q + e] = (op_t)n[e];
+      check_op4(n[0], n[1], n[2], n[3], bad);
+    }
+    *(f16x8 *)(next + afrag_index(m, c, KB)) = o;
+  }
+  flush_range(status, bad);
 }
 
 // Trajectory Reconciliation set-up: keep the initial noise x_0 and clear the
@@ -542,28 +697,81 @@ hipError_t launch_time_features(const float *t, int M, int m_alloc, int n_steps,
   return hipGetLastError();
 }
 
+hipError_t launch_time_classes(const float *t, int M, int32_t *cls, float *cls_t, int *n_cls, hipStream_t s,
+                               hipEvent_t ev0, hipEvent_t ev1) {
+  UAD_LAUNCH(time_classes_kernel, dim3(1), dim3(1024), 0, s, ev0, ev1, t, M, cls, cls_t, n_cls);
+  return hipGetLastError();
+}
+
+hipError_t launch_class_features(const float *cls_t, const int *n_cls, int M, int d, const float *freqs, op_t *te,
+                                 unsigned *status, hipStream_t s) {
+  hipLaunchKernelGGL(class_feat_kernel, dim3(M, (d / 2 + 255) / 256), dim3(256), 0, s, cls_t, n_cls, d, freqs, te,
+                     status);
+  return hipGetLastError();
+}
+
+hipError_t launch_ada_norm(const float *h, int M, int d, float eps, const float *scale, const float *shift, int mod_ld,
+                           const int32_t *mod_row, op_t *next, unsigned *status, hipStream_t s, hipEvent_t ev0,
+                           hipEvent_t ev1) {
+  if (d % 32 != 0) return hipErrorInvalidValue;
+  const dim3 grid((M + 15) / 16), wg(512);
+#define UAD_ADA_NORM(NI)                                                                                        \
+  case NI:                                                                                                      \
+    UAD_LAUNCH(ada_norm_kernel<NI>, grid, wg, 0, s, ev0, ev1, h, M, d, eps, scale, shift, mod_ld, mod_row, next, \
+               status);                                                                                         \
+    return hipGetLastError();
+  switch ((d + 255) / 256) {
+    UAD_ADA_NORM(1)
+    UAD_ADA_NORM(2)
+    UAD_ADA_NORM(3)
+    UAD_ADA_NORM(4)
+    UAD_ADA_NORM(5)
+    UAD_ADA_NORM(6)
+    UAD_ADA_NORM(7)
+    UAD_ADA_NORM(8)
+  }
+#undef UAD_ADA_NORM
+  return hipErrorInvalidValue;
+}
+
 hipError_t launch_final(const FinalArgs &f, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-  if (f.M >= 1024 && !f.debug_field && !f.mod_scale && f.d % 512 == 0 && f.Da <= 64) {
+  if (f.M >= 1024 && !f.debug_field && f.d % 512 == 0 && f.Da <= 64) {
     const dim3 gr((f.M + 15) / 16);
+    if (f.mod_scale) {
+      switch ((f.Da + 15) / 16) {
+        case 1: UAD_LAUNCH((final_mfma_kernel<1, true>), gr, dim3(256), 0, s, ev0, ev1, f); return hipGetLastError();
+        case 2: UAD_LAUNCH((final_mfma_kernel<2, true>), gr, dim3(256), 0, s, ev0, ev1, f); return hipGetLastError();
+        case 3: UAD_LAUNCH((final_mfma_kernel<3, true>), gr, dim3(256), 0, s, ev0, ev1, f); return hipGetLastError();
+        case 4: UAD_LAUNCH((final_mfma_kernel<4, true>), gr, dim3(256), 0, s, ev0, ev1, f); return hipGetLastError();
+      }
+    }
     switch ((f.Da + 15) / 16) {
-      case 1: UAD_LAUNCH(final_mfma_kernel<1>, gr, dim3(256), 0, s, ev0, ev1, f); return hipGetLastError();
-      case 2: UAD_LAUNCH(final_mfma_kernel<2>, gr, dim3(256), 0, s, ev0, ev1, f); return hipGetLastError();
-      case 3: UAD_LAUNCH(final_mfma_kernel<3>, gr, dim3(256), 0, s, ev0, ev1, f); return hipGetLastError();
-      case 4: UAD_LAUNCH(final_mfma_kernel<4>, gr, dim3(256), 0, s, ev0, ev1, f); return hipGetLastError();
+      case 1: UAD_LAUNCH((final_mfma_kernel<1, false>), gr, dim3(256), 0, s, ev0, ev1, f); return hipGetLastError();
+      case 2: UAD_LAUNCH((final_mfma_kernel<2, false>), gr, dim3(256), 0, s, ev0, ev1, f); return hipGetLastError();
+      case 3: UAD_LAUNCH((final_mfma_kernel<3, false>), gr, dim3(256), 0, s, ev0, ev1, f); return hipGetLastError();
+      case 4: UAD_LAUNCH((final_mfma_kernel<4, false>), gr, dim3(256), 0, s, ev0, ev1, f); return hipGetLastError();
     }
   }
   const dim3 grid(f.M, (f.Da + kFinalOuts - 1) / kFinalOuts);
+#define UAD_FINAL(NC)                                                                  \
+  case NC:                                                                             \
+    if (f.mod_row)                                                                     \
+      UAD_LAUNCH((final_kernel<NC, true>), grid, dim3(256), 0, s, ev0, ev1, f);        \
+    else                                                                               \
+      UAD_LAUNCH((final_kernel<NC, false>), grid, dim3(256), 0, s, ev0, ev1, f);       \
+    break;
   switch ((f.d + 255) / 256) {
-    case 1: UAD_LAUNCH(final_kernel<1>, grid, dim3(256), 0, s, ev0, ev1, f); break;
-    case 2: UAD_LAUNCH(final_kernel<2>, grid, dim3(256), 0, s, ev0, ev1, f); break;
-    case 3: UAD_LAUNCH(final_kernel<3>, grid, dim3(256), 0, s, ev0, ev1, f); break;
-    case 4: UAD_LAUNCH(final_kernel<4>, grid, dim3(256), 0, s, ev0, ev1, f); break;
-    case 5: UAD_LAUNCH(final_kernel<5>, grid, dim3(256), 0, s, ev0, ev1, f); break;
-    case 6: UAD_LAUNCH(final_kernel<6>, grid, dim3(256), 0, s, ev0, ev1, f); break;
-    case 7: UAD_LAUNCH(final_kernel<7>, grid, dim3(256), 0, s, ev0, ev1, f); break;
-    case 8: UAD_LAUNCH(final_kernel<8>, grid, dim3(256), 0, s, ev0, ev1, f); break;
+    UAD_FINAL(1)
+    UAD_FINAL(2)
+    UAD_FINAL(3)
+    UAD_FINAL(4)
+    UAD_FINAL(5)
+    UAD_FINAL(6)
+    UAD_FINAL(7)
+    UAD_FINAL(8)
     default: return hipErrorInvalidValue;
   }
+#undef UAD_FINAL
   return hipGetLastError();
 }
 

@@ -27,27 +27,27 @@ __global__ __launch_bounds__(256) void temb_kernel(const float *__restrict__ x, 
                                                     const float *__restrict__ b_in,
                                                     const float *__restrict__ freqs, op_t *__restrict__ te,
                                                     unsigned *status, const int32_t *env_map, int chunk);
-template <int EPI, int T, int KPW, bool DUAL, bool PIPE>
+template <int EPI, int T, int KPW, bool DUAL, bool PIPE, bool MAP>
 __global__ __launch_bounds__(512) void gemm_kernel(GemmArgs g);
 template <int HD, int NB, bool LOWREG, int NW, int KG>
 __global__ __launch_bounds__(64 * NW) void attn_kernel(AttnArgs a);
 template <int SMAX, int W>
 __global__ __launch_bounds__(64 * W) void attn_combine_kernel(AttnArgs a, int hd);
-template <int NC>
+template <int NC, bool MAP>
 __global__ __launch_bounds__(256) void final_kernel(FinalArgs f);
 
 template __global__ void temb_kernel<1>(const float *__restrict__, const float *__restrict__, int, int, int,
                                         const float *__restrict__, const float *__restrict__,
                                         const float *__restrict__, op_t *__restrict__, unsigned *, const int32_t *,
                                         int);
-template __global__ void gemm_kernel<EPI_BIAS_SILU, 1, 4, false, true>(GemmArgs);
-template __global__ void gemm_kernel<EPI_RESID_F32, 1, 4, false, false>(GemmArgs);
-template __global__ void gemm_kernel<EPI_QKV, 1, 4, false, false>(GemmArgs);
+template __global__ void gemm_kernel<EPI_BIAS_SILU, 1, 4, false, true, false>(GemmArgs);
+template __global__ void gemm_kernel<EPI_RESID_F32, 1, 4, false, false, false>(GemmArgs);
+template __global__ void gemm_kernel<EPI_QKV, 1, 4, false, false, false>(GemmArgs);
 template __global__ void attn_kernel<256, 2, false, 4, 1>(AttnArgs);
 template __global__ void attn_combine_kernel<16, 4>(AttnArgs, int);
-template __global__ void gemm_kernel<EPI_RESID_F32, 1, 4, false, true>(GemmArgs);
-template __global__ void gemm_kernel<EPI_GEGLU, 2, 4, false, false>(GemmArgs);
-template __global__ void final_kernel<4>(FinalArgs);
+template __global__ void gemm_kernel<EPI_RESID_F32, 1, 4, false, true, false>(GemmArgs);
+template __global__ void gemm_kernel<EPI_GEGLU, 2, 4, false, false, false>(GemmArgs);
+template __global__ void final_kernel<4, false>(FinalArgs);
 
 }  // namespace uad
 

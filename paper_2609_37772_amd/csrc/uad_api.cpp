@@ -110,9 +110,9 @@ struct Carve {
 
 // Kernel classes reported by the measurement hook.
 enum KClass { K_TEMB, K_GEMM_TIME_IN, K_GEMM_TIME_OUT, K_GEMM_QKV, K_ATTENTION, K_GEMM_O, K_GEMM_GATEUP,
-              K_GEMM_DOWN, K_FINAL, K_GEMM_MOD, K_NCLASS };
+              K_GEMM_DOWN, K_FINAL, K_GEMM_MOD, K_ADA_NORM, K_NCLASS };
 const char *kClassNames[K_NCLASS] = {"temb", "gemm_time_in", "gemm_time_out", "gemm_qkv", "attention",
-                                     "gemm_o", "gemm_gateup", "gemm_down", "final_euler", "gemm_mod"};
+                                     "gemm_o", "gemm_gateup", "gemm_down", "final_euler", "gemm_mod", "ada_norm"};
 
 hipEvent_t pool_event(uad_ctx *c) {
   if (!c->ev_pool.empty()) {
@@ -392,6 +392,7 @@ uad_status uad_create(const uad_model_config *cfg, int32_t device, void *hip_str
          o_pf = a.take<unsigned>(64), o_status = a.take<unsigned>(1),
          o_budt = a.take<float>(kMaxTrSteps * M), o_buddt = a.take<float>(kMaxTrSteps * M),
          o_budm = a.take<uint8_t>(kMaxTrSteps * M), o_budmap = a.take<int32_t>((size_t)kMaxTrSteps * m.max_batch),
+         o_mcls = a.take<int32_t>(c->ada ? M : 0), o_clst = a.take<float>(c->ada ? M : 0), o_ncls = a.take<int>(1),
          o_kxw = a.take<float>((size_t)2 * c->n_cu * kKxPartialFloats), o_kxc = a.take<unsigned>((size_t)c->n_cu);
   e = hipMalloc(&c->abuf, a.off);
   if (e == hipSuccess) e = hipMemset(c->abuf, 0, a.off);
@@ -417,6 +418,9 @@ uad_status uad_create(const uad_model_config *cfg, int32_t device, void *hip_str
   c->tr_mask = (uint8_t *)(ab + o_trm);
   c->mod = (float *)(ab + o_mod);
   c->mod_shift_ops = (op_t *)(ab + o_mshift);
+  c->mod_cls = (int32_t *)(ab + o_mcls);
+  c->cls_t = (float *)(ab + o_clst);
+  c->n_cls = (int *)(ab + o_ncls);
   c->pf_sink = (unsigned *)(ab + o_pf);
   c->status = (unsigned *)(ab + o_status);
   c->bud_t = (float *)(ab + o_budt);
@@ -766,6 +770,17 @@ struct StepScratch {
   float *mlpart;
 };
 
+// Adaptive norms from kBigM rows on: the modulations of the step's distinct flow
+// times only (a token's are row mod_cls[token]), and the norms as passes of
+// their own, so that QKV and gate/up take one operand.  Below that the passes
+// (~5 us each) cost more than the second operand does.  Same-machine, 6 layers of the
+// 1024-wide expert, us per joint step: 64 environments 2680 -> 1346 (gate/up 160
+// -> 56, QKV 60 -> 24, modulations 477 -> 33, two norms 13), 32 1779 -> 948, 16
+// 1128 -> 804, 8 759 -> 634, 6 696 -> 612.
+static bool ada_by_class(const uad_ctx *c, int M, bool schedule_level) {
+  return c->ada && !schedule_level && M >= kBigM;
+}
+
 static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float *t, const float *dt,
                                const uint8_t *mask, const uint8_t *next_mask, int is_last, int step, float *v_out,
                                float *released, int32_t *release_step, int B, int H, float *vsum = nullptr,
@@ -795,6 +810,7 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
       x.kx_ws = c->kx_ws; x.kx_cnt = c->kx_cnt; x.kx_ws_bytes = c->kx_ws_bytes; x.kx_tiles = c->n_cu;
     };
     const int n_mod = c->n_mod;
+    const bool ada_batched = ada_by_class(c, M, pre != nullptr);
     if (!c->ada) {
       UAD_CHECK_CLS(K_TEMB, launch_temb(x, t, M, c->Da, d, c->action_in_w, c->action_in_b, c->freqs, c->a_te, c->status, s,
                                         ea_, eb_, env_map, H));
@@ -816,6 +832,24 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
       UAD_CHECK_CLS(K_TEMB, launch_temb_ada(x, nullptr, M, c->Da, d, c->action_in_w, c->action_in_b, c->freqs,
                                             c->a_te, c->h, c->ssq, (int)MA, c->status, s, ea_, eb_, pre->mod, n_mod,
                                             c->a_n));
+    } else if (ada_batched) {
+      // batched adaptive norms: h_0, then the time MLP and the modulations of the
+      // step's distinct flow times; token m's are row mod_cls[m]
+      UAD_CHECK_CLS(K_TEMB, launch_temb_ada(x, nullptr, M, c->Da, d, c->action_in_w, c->action_in_b, c->freqs,
+                                            c->a_te, c->h, c->ssq, (int)MA, c->status, s, ea_, eb_));
+      UAD_CHECK_CLS(K_ADA_NORM, launch_time_classes(t, M, c->mod_cls, c->cls_t, c->n_cls, s, ea_, eb_));
+      e = launch_class_features(c->cls_t, c->n_cls, M, d, c->freqs, c->a_te, c->status, s);
+      if (e != hipSuccess) return hip_fail(c, e, "launch_class_features");
+      GemmArgs g{};
+      g.status = c->status; g.m_dev = c->n_cls;
+      g.M = M; g.m_alloc = (int)MA; g.A = c->a_te; g.W = c->t1_w; g.N = d; g.K = d; g.out = c->a_z; g.ldo = d;
+      g.bias = c->t1_b;
+      UAD_CHECK_CLS(K_GEMM_TIME_IN, launch_gemm(EPI_BIAS_SILU, g, plan_gemm(EPI_BIAS_SILU, M, d, d), s, ea_, eb_));
+      g.A = c->a_z; g.W = c->t2_w; g.out = c->a_te; g.bias = c->t2_b;
+      UAD_CHECK_CLS(K_GEMM_TIME_OUT, launch_gemm(EPI_BIAS_SILU, g, plan_gemm(EPI_BIAS_SILU, M, d, d), s, ea_, eb_));
+      g.A = c->a_te; g.W = c->w_mod; g.N = n_mod; g.out = c->mod; g.ldo = n_mod; g.bias = c->b_mod;
+      g.d_model = d; g.n_layers = c->L;
+      UAD_CHECK_CLS(K_GEMM_MOD, launch_gemm(EPI_MOD, g, plan_gemm(EPI_MOD, M, n_mod, d), s, ea_, eb_));
     } else {
       // adaptive norms: h_0 = W_in x + b_in, c = SiLU(W2 SiLU(W1 e(t) + b1) + b2), then every
       // modulation (a, b, g per norm site) in one GEMM whose epilogue also forms the
@@ -881,7 +915,14 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
       const float *mod_base = pre ? pre->mod : c->mod;
       const op_t *shift_base = pre ? pre->shift : c->mod_shift_ops;
       const size_t shift_stride = pre ? pre->shift_stride : MA * d;
-      if (c->ada) q.A2 = shift_base + (size_t)(2 * l) * shift_stride;
+      if (ada_batched) {
+        const float *ml = c->mod + (size_t)l * 6 * d;
+        UAD_CHECK_CLS(K_ADA_NORM, launch_ada_norm(c->h, M, d, c->cfg.rms_eps, ml, ml + d, n_mod, c->mod_cls, c->a_n,
+                                                  c->status, s, ea_, eb_));
+        q.use_rstd = 0;
+      } else if (c->ada) {
+        q.A2 = shift_base + (size_t)(2 * l) * shift_stride;
+      }
       UAD_CHECK_CLS(K_GEMM_QKV, launch_gemm(EPI_QKV, q, pq, s, ea_, eb_));
       at.kc = kc; at.vtc = vtc;
       at.pre_attn = Prefetch{};
@@ -913,13 +954,21 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
       if (c->ada) {
         const float *ml = mod_base + (size_t)l * 6 * d;
         o.mod_ld = n_mod; o.mod_gate = ml + 2 * d; o.mod_scale_next = ml + 3 * d; o.gain_next = nullptr;
+        if (ada_batched) { o.mod_row = c->mod_cls; o.mod_scale_next = nullptr; }
       }
       UAD_CHECK_CLS(K_GEMM_O, launch_gemm(EPI_RESID_F32, o, po, s, ea_, eb_));
       GemmArgs gu{};
       gu.status = c->status;
       gu.M = M; gu.A = c->a_n; gu.W = lp.wgu; gu.N = 2 * F; gu.K = d;
       gu.out = c->a_g; gu.ldo = F; norm_fields(gu); gu.use_rstd = 1;
-      if (c->ada) gu.A2 = shift_base + (size_t)(2 * l + 1) * shift_stride;
+      if (ada_batched) {
+        const float *ml = c->mod + (size_t)l * 6 * d + 3 * d;
+        UAD_CHECK_CLS(K_ADA_NORM, launch_ada_norm(c->h, M, d, c->cfg.rms_eps, ml, ml + d, n_mod, c->mod_cls, c->a_n,
+                                                  c->status, s, ea_, eb_));
+        gu.use_rstd = 0;
+      } else if (c->ada) {
+        gu.A2 = shift_base + (size_t)(2 * l + 1) * shift_stride;
+      }
       UAD_CHECK_CLS(K_GEMM_GATEUP, launch_gemm(EPI_GEGLU, gu, pg, s, ea_, eb_));
       GemmArgs dn{};
       dn.status = c->status;
@@ -930,6 +979,7 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
         const float *ml = mod_base + (size_t)l * 6 * d;
         dn.mod_ld = n_mod; dn.mod_gate = ml + 5 * d; dn.gain_next = nullptr;
         dn.mod_scale_next = (l + 1 < c->L) ? ml + 6 * d : nullptr;
+        if (ada_batched) { dn.mod_row = c->mod_cls; dn.mod_scale_next = nullptr; }
       }
       UAD_CHECK_CLS(K_GEMM_DOWN, launch_gemm(EPI_RESID_F32, dn, pd, s, ea_, eb_));
     }
@@ -943,17 +993,18 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
   if (c->ada) {
     f.mod_scale = (pre ? pre->mod : c->mod) + (size_t)c->L * 6 * d; f.mod_shift = f.mod_scale + d;
     f.mod_ld = c->n_mod;
+    if (!c->dbg && ada_by_class(c, M, pre != nullptr)) f.mod_row = c->mod_cls;
   }
   UAD_CHECK_CLS(K_FINAL, launch_final(f, s, ea_, eb_));
 #undef UAD_CHECK_CLS
   return UAD_OK;
 }
 
-// Schedule-level conditioning applies to small batches (projections bound by
+// Schedule-level conditioning applies below kBigM rows (projections bound by
 // the weight stream, where the modulation matrix would be read once per step)
 // when the buffers for n_steps x m_alloc rows are in place.
 static bool ada_schedule_level(const uad_ctx *c, size_t M, int n_steps) {
-  return c->ada && !c->dbg && M <= 256 && (size_t)n_steps * c->m_alloc <= c->pre_rows;
+  return c->ada && !c->dbg && M < kBigM && (size_t)n_steps * c->m_alloc <= c->pre_rows;
 }
 
 // Grow the schedule-level conditioning buffers to `rows` rows (no-op when they
@@ -1234,7 +1285,7 @@ uad_status uad_denoise_schedule(uad_ctx *c, float *x, const float *t_sched, cons
   if (st != UAD_OK) return st;
   if (n_steps < 1) return fail(c, UAD_E_INVALID, "uad_denoise_schedule: n_steps must be >= 1");
   (void)hipSetDevice(c->device);
-  if (c->ada && !c->dbg && (size_t)batch * chunk <= 256) ensure_ada_rows(c, (size_t)n_steps * c->m_alloc);
+  if (c->ada && !c->dbg && (size_t)batch * chunk < kBigM) ensure_ada_rows(c, (size_t)n_steps * c->m_alloc);
   GraphKey k{};
   k.kind = 0;
   k.is_schedule = true;
@@ -1366,7 +1417,7 @@ uad_status uad_denoise_release(uad_ctx *c, float *x, int32_t batch, int32_t chun
       host_dev = (float *)pa.devicePointer;
     (void)hipGetLastError();  // pageable memory: the query's error is expected
   }
-  if (c->ada && !c->dbg && M <= 256) ensure_ada_rows(c, (size_t)Nstar * c->m_alloc);
+  if (c->ada && !c->dbg && M < kBigM) ensure_ada_rows(c, (size_t)Nstar * c->m_alloc);
   GraphKey k{};
   k.kind = 1;
   k.x = x; k.B = batch; k.H = chunk; k.n_steps = Nstar; k.step_ticks = step_ticks;

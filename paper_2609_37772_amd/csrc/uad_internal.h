@@ -184,7 +184,7 @@ struct GemmArgs {
   int mod_ld;
   // EPI_MOD destinations: fp32 [M][N] row-major (out), the shifts as fp16
   // operands, and the first attention norm's operand fp16(h * (1 + scale))
-  op_t *mod_shift_ops;    // [L][2][m_alloc*d] fragment order
+  op_t *mod_shift_ops;    // [L][2][m_alloc*d] fragment order (nullptr: not kept)
   const float *h_in;      // [M][d] residual stream
   int d_model, n_layers;
   size_t shift_stride;    // elements per shift operand
@@ -211,6 +211,11 @@ struct GemmArgs {
   size_t kx_ws_bytes;
   int kx_tiles;  // counters available
   int kx;
+  // batched adaptive norm: token row r's modulations are row mod_row[r] of the
+  // modulation matrix (null: row r), and only the first *m_dev rows of the
+  // launch exist (null: all M); workgroups past them return at once
+  const int32_t *mod_row;
+  const int *m_dev;
 };
 
 // Up to two byte ranges (weights of the next projections) that otherwise idle
@@ -271,6 +276,7 @@ struct FinalArgs {
   // compacted steps: token m of the step (h row m) is token
   // env_map[m / chunk] * chunk + m % chunk of x, t, dt, masks and outputs
   const int32_t *env_map;
+  const int32_t *mod_row;  // token row's row of mod_scale / mod_shift (null: its own)
 };
 
 // Urgency-aware release with Trajectory Reconciliation and Ghost Action
@@ -336,6 +342,17 @@ hipError_t launch_temb_ada(const float *x, const float *t, int M, int Da, int d,
 // sinusoidal time features of n_steps x m_alloc rows (rows past M in a step: time 0)
 hipError_t launch_time_features(const float *t, int M, int m_alloc, int n_steps, int d, const float *freqs,
                                 op_t *te, unsigned *status, hipStream_t s);
+// distinct flow times of M tokens: *n_cls of them at cls_t, token m's index at
+// cls[m]; beyond kMaxTimeClasses every token is its own class
+hipError_t launch_time_classes(const float *t, int M, int32_t *cls, float *cls_t, int *n_cls, hipStream_t s,
+                               hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// time features of the *n_cls first rows of cls_t (at most M)
+hipError_t launch_class_features(const float *cls_t, const int *n_cls, int M, int d, const float *freqs, op_t *te,
+                                 unsigned *status, hipStream_t s);
+// next = fp16(RMS(h) (1 + scale[row]) + shift[row]), row = mod_row[m], fragment order
+hipError_t launch_ada_norm(const float *h, int M, int d, float eps, const float *scale, const float *shift, int mod_ld,
+                           const int32_t *mod_row, op_t *next, unsigned *status, hipStream_t s,
+                           hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 hipError_t launch_final(const FinalArgs &f, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 hipError_t launch_stamp(uint64_t *dst, hipStream_t s);
 hipError_t launch_prefix_pack(const PrefixArgs &a, int head_dim, bool f32, hipStream_t s);
@@ -436,6 +453,10 @@ struct uad_ctx {
   float *b_mod = nullptr;             // [n_mod]
   float *mod = nullptr;               // [m_alloc][n_mod] per token: per layer (a,b,g)_attn (a,b,g)_mlp, then (a,b)_final
   uad::op_t *mod_shift_ops = nullptr; // [L][2][m_alloc*d] shifts as fp16 operands
+  // batched steps: the modulations of a step's distinct flow times only
+  int32_t *mod_cls = nullptr;         // [m_alloc] token's row of mod
+  float *cls_t = nullptr;             // [m_alloc] the distinct flow times
+  int *n_cls = nullptr;               // how many
   // schedule-level conditioning (small batches): the modulations depend on the
   // flow time only, so a schedule computes them for all its steps at once,
   // n_steps x m_alloc rows, and each step reads its slice
