@@ -268,7 +268,7 @@ __global__ __launch_bounds__(512) void gemm_kernel(GemmArgs g) {
     if (threadIdx.x < 64) {
       float ss = 0.f;
       for (int j = 0; j < g.ssq_tiles; ++j) ss += ssq_s[j][threadIdx.x];
-      rstd_s[threadIdx.x] = 1.0f / sqrtf(ss / (float)(g.ssq_tiles * kTileN) + g.eps);
+      rstd_s[threadIdx.x] = 1.0f / sqrtf(ss / (float)g.K + g.eps);
     }
     __syncthreads();
 #pragma unroll
@@ -295,7 +295,7 @@ __global__ __launch_bounds__(512) void gemm_kernel(GemmArgs g) {
   if (!DUAL && kRstd && g.use_rstd && threadIdx.x < 64) {
     float ss = 0.f;
     for (int j = 0; j < g.ssq_tiles; ++j) ss += ssq_s[j][threadIdx.x];
-    rstd_s[threadIdx.x] = 1.0f / sqrtf(ss / (float)(g.ssq_tiles * kTileN) + g.eps);
+    rstd_s[threadIdx.x] = 1.0f / sqrtf(ss / (float)g.K + g.eps);
   }
   __syncthreads();
 
@@ -447,7 +447,8 @@ __device__ __forceinline__ void st4h(op_t *p, f32x4 v, unsigned &bad) {
 }
 
 // Residual epilogue, store half, over NI row tiles starting at i0: h = h0 (or
-// bias) + gate * v, per-16-column sums of squares of h, next operand
+// bias) + gate * v, each row's sum of squares of h over the wave's columns (to
+// ssq[row - ssq_row0]), next operand
 // fp16(h * scale), scale = gain_next (one row [TB]).  ADA: the gate is a
 // per-token modulation and the next norm a pass of its own (no next operand);
 // else gate = 1.
@@ -455,7 +456,7 @@ template <int NI, bool ADA, int TA, int TB>
 __device__ __forceinline__ void big_resid_store(const GemmArgs &g, const f32x4 (&acc)[TA][TB], int i0, int mt, int nt,
                                                 int lane, const f32x4 (&h0)[NI][TB],
                                                 const f32x4 (&gt)[ADA ? NI : 1][TB],
-                                                const f32x4 (&sc)[TB], unsigned &bad) {
+                                                const f32x4 (&sc)[TB], float *ssq, int ssq_row0, unsigned &bad) {
   float *h = (float *)g.out;
   const bool has_next = !ADA && g.gain_next != nullptr;
   const int csub = 4 * (lane >> 4);
@@ -464,18 +465,18 @@ __device__ __forceinline__ void big_resid_store(const GemmArgs &g, const f32x4 (
   for (int ii = 0; ii < NI; ++ii) {
     const int row = (mt + i0 + ii) * 16 + (lane & 15);
     const bool row_ok = row < g.M;
+    float sq = 0.f;
 #pragma unroll
     for (int j = 0; j < TB; ++j) {
-      const int tile = nt + j, col = tile * 16 + csub;
+      const int col = (nt + j) * 16 + csub;
       const f32x4 hv = ADA ? h0[ii][j] + gt[ADA ? ii : 0][j] * acc[i0 + ii][j] : h0[ii][j] + acc[i0 + ii][j];
       if (row_ok) st4(h + (size_t)row * g.ldo + col, hv);
-      float sq = hv[0] * hv[0] + hv[1] * hv[1] + hv[2] * hv[2] + hv[3] * hv[3];
-      sq = sum_pair32(sum_pair16(sq));  // the 4 lanes holding this row's 16 columns
-      if (row_ok) {
-        if (lane < 16) g.ssq[(size_t)tile * g.m_alloc + row] = sq;
-        if (has_next) st4h(g.next + afrag_index(row, col, KBn), hv * sc[j], bad);
-      }
+      sq += hv[0] * hv[0] + hv[1] * hv[1] + hv[2] * hv[2] + hv[3] * hv[3];
+      if (row_ok && has_next) st4h(g.next + afrag_index(row, col, KBn), hv * sc[j], bad);
     }
+    // this wave's columns of the row: the 4 lanes holding them
+    sq = sum_pair32(sum_pair16(sq));
+    if (row_ok && lane < 16) ssq[row - ssq_row0] = sq;
   }
 }
 
@@ -518,27 +519,29 @@ __device__ __forceinline__ void big_resid_load(const GemmArgs &g, int i0, int mt
 // h0 loads of other rows, so the compiler would not hoist them).
 template <int NI, bool ADA, int TA, int TB>
 __device__ __forceinline__ void big_resid_rows(const GemmArgs &g, f32x4 (&acc)[TA][TB], int i0, int mt, int nt,
-                                               int lane, unsigned &bad) {
+                                               int lane, float *ssq, int ssq_row0, unsigned &bad) {
   f32x4 h0[NI][TB], gt[ADA ? NI : 1][TB], sc[TB];
   big_resid_load<NI, ADA, TB>(g, i0, mt, nt, lane, h0, gt, sc);
-  big_resid_store<NI, ADA, TA, TB>(g, acc, i0, mt, nt, lane, h0, gt, sc, bad);
+  big_resid_store<NI, ADA, TA, TB>(g, acc, i0, mt, nt, lane, h0, gt, sc, ssq, ssq_row0, bad);
 }
 
 template <int EPI, int TA, int TB, int I0 = 0, int NI = TA>
 __device__ __forceinline__ void big_epilogue(const GemmArgs &g, f32x4 (&acc)[TA][TB], int mt, int nt, int lane,
-                                             const float *rstd, unsigned &bad) {
+                                             const float *rstd, unsigned &bad, float *ssq_lds = nullptr,
+                                             int ssq_row0 = 0) {
   const int csub = 4 * (lane >> 4);
   if constexpr (EPI == EPI_RESID_F32) {
+    float *ssq = ssq_lds ? ssq_lds : g.ssq + (size_t)(nt / TB) * g.m_alloc;
     if (g.mod_gate) {
       constexpr int HB = NI % 2 == 0 ? 2 : 1;
 #pragma unroll
-      for (int i = I0; i < I0 + NI; i += HB) big_resid_rows<HB, true>(g, acc, i, mt, nt, lane, bad);
+      for (int i = I0; i < I0 + NI; i += HB) big_resid_rows<HB, true>(g, acc, i, mt, nt, lane, ssq, ssq_row0, bad);
     } else {
       // the whole tile in two halves: all of its h0 at once would cost the
       // main loop its second wave per SIMD (a half tile goes in one piece)
       constexpr int HB = NI == TA ? TA / 2 : NI;
 #pragma unroll
-      for (int i = I0; i < I0 + NI; i += HB) big_resid_rows<HB, false>(g, acc, i, mt, nt, lane, bad);
+      for (int i = I0; i < I0 + NI; i += HB) big_resid_rows<HB, false>(g, acc, i, mt, nt, lane, ssq, ssq_row0, bad);
     }
   } else if constexpr (EPI == EPI_QKV) {
     const int kvd = g.n_kv_heads * g.head_dim;
@@ -722,7 +725,7 @@ __global__ __launch_bounds__(256 * KS) void gemm_big_kernel(GemmArgs g) {
     if (threadIdx.x < 128) {
       float ss = 0.f;
       for (int t = 0; t < g.ssq_tiles; ++t) ss += ssq_s[t * 128 + threadIdx.x];
-      rstd_s[threadIdx.x] = 1.0f / sqrtf(ss / (float)(g.ssq_tiles * kTileN) + g.eps);
+      rstd_s[threadIdx.x] = 1.0f / sqrtf(ss / (float)g.K + g.eps);
     }
     __syncthreads();
   }
@@ -879,17 +882,35 @@ __global__ __launch_bounds__(512) void gemm_ring_kernel(GemmArgs g) {
                                        0);
     }
   };
+  // per-row sums of squares: TPR threads share row (tid % ROWS), each summing a
+  // slice of its partial sums.  The first kPre go out ahead of the ring's loads,
+  // so that their use waits for none of those.
+  constexpr bool kNorm = EPI != EPI_RESID_F32;
+  constexpr int kPre = kNorm ? 4 : 1;
+  float pre[kPre];
+  int t0 = 0, t1 = 0;
+  const float *sp = g.ssq;
+  const bool norm = kNorm && g.use_rstd && (TPR * ROWS == 512 || (int)threadIdx.x < TPR * ROWS);
+  if (norm) {
+    const int part = threadIdx.x / ROWS;
+    sp += min(mt0 * 16 + (int)(threadIdx.x % ROWS), g.M - 1);
+    t0 = part * g.ssq_tiles / TPR;
+    t1 = (part + 1) * g.ssq_tiles / TPR;
+#pragma unroll
+    for (int q = 0; q < kPre; ++q) pre[q] = sp[(size_t)min(t0 + q, g.ssq_tiles - 1) * g.m_alloc];
+  }
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int s = 0; s < NS - 1; ++s)
     if (s < KB) issue(s, s);
+  __builtin_amdgcn_sched_barrier(0);
 
-  if (g.use_rstd && (TPR * ROWS == 512 || (int)threadIdx.x < TPR * ROWS)) {
-    // per-row sums of squares: TPR threads share row (tid % ROWS), each summing a slice of its tiles
-    const int row = min(mt0 * 16 + (int)(threadIdx.x % ROWS), g.M - 1), part = threadIdx.x / ROWS;
-    const int t0 = part * g.ssq_tiles / TPR, t1 = (part + 1) * g.ssq_tiles / TPR;
+  if (norm) {
     float ss = 0.f;
-    for (int q = t0; q < t1; ++q) ss += g.ssq[(size_t)q * g.m_alloc + row];
-    rpart[part][threadIdx.x % ROWS] = ss;
+#pragma unroll
+    for (int q = 0; q < kPre; ++q) ss += t0 + q < t1 ? pre[q] : 0.f;
+    for (int q = t0 + kPre; q < t1; ++q) ss += sp[(size_t)q * g.m_alloc];
+    rpart[threadIdx.x / ROWS][threadIdx.x % ROWS] = ss;
   }
 
   f32x4 acc[TA][TB];
@@ -974,13 +995,26 @@ __global__ __launch_bounds__(512) void gemm_ring_kernel(GemmArgs g) {
       float ss = 0.f;
 #pragma unroll
       for (int p = 0; p < TPR; ++p) ss += rpart[p][threadIdx.x];
-      rstd_s[threadIdx.x] = 1.0f / sqrtf(ss / (float)(g.ssq_tiles * kTileN) + g.eps);
+      rstd_s[threadIdx.x] = 1.0f / sqrtf(ss / (float)g.K + g.eps);
     }
     __syncthreads();
   }
   unsigned bad = 0;  // fp16 range flag of this thread's stores
-  big_epilogue<EPI, TA, TB>(g, acc, mt0 + wr * TA, nt0 + wc * TB, lane, g.use_rstd ? rstd_s + wr * TA * 16 : nullptr,
-                            bad);
+  if constexpr (EPI == EPI_RESID_F32) {
+    // one sum of squares per row of the tile: the wave columns' sums meet in LDS
+    static_assert(WC <= TPR, "a row of rpart per wave column");
+    big_epilogue<EPI, TA, TB>(g, acc, mt0 + wr * TA, nt0 + wc * TB, lane, nullptr, bad, rpart[wc], mt0 * 16);
+    __syncthreads();
+    if ((int)threadIdx.x < min(ROWS, g.M - mt0 * 16)) {
+      float ss = 0.f;
+#pragma unroll
+      for (int q = 0; q < WC; ++q) ss += rpart[q][threadIdx.x];
+      g.ssq[(size_t)pn * g.m_alloc + mt0 * 16 + threadIdx.x] = ss;
+    }
+  } else {
+    big_epilogue<EPI, TA, TB>(g, acc, mt0 + wr * TA, nt0 + wc * TB, lane,
+                              g.use_rstd ? rstd_s + wr * TA * 16 : nullptr, bad);
+  }
   flush_range(g.status, bad);
 }
 
@@ -1195,6 +1229,33 @@ static bool big_ok(int epi, const GemmArgs &g) {
   return tiles >= 90 && !(tiles < 128 && g.K > 4096);
 }
 
+// Which kernel a residual projection takes (kx: its split over K).
+enum ResidPath { RESID_SMALL, RESID_BIG, RESID_RING, RESID_RING96 };
+static ResidPath resid_path(const GemmArgs &g, int *kx) {
+  const bool p96 = resid_prefers_96(g);
+  *kx = p96 ? resid_ksplit<RingResid96>(g) : resid_ksplit<RingShape<EPI_RESID_F32>>(g);
+  if (*kx > 1) return p96 ? RESID_RING96 : RESID_RING;
+  if (ring96_fits(g)) return RESID_RING96;
+  if (ring_fits<EPI_RESID_F32>(g)) return RESID_RING;
+  return big_ok(EPI_RESID_F32, g) ? RESID_BIG : RESID_SMALL;
+}
+
+// Sums of squares per row that the projection leaves for the norm: one per
+// output tile of the ring kernels, per wave's columns of the register-streamed
+// one, per 16 columns of the small-M one.  The consumers re-read all of them for
+// every tile.  Same-machine, 64 -> 8 a row: QKV 28.0 -> 25.0 us and gate/up 65.4 ->
+// 59.4 at 3200 rows (64 environments 3.845 -> 3.655 ms per joint step), 96 -> 16:
+// gate/up 80.9 -> 72.5 us on the 1536-wide expert (1.836 -> 1.748 ms, 8 layers).
+int resid_ssq_tiles(const GemmArgs &g) {
+  int kx;
+  switch (resid_path(g, &kx)) {
+    case RESID_RING: return g.N / (16 * RingShape<EPI_RESID_F32>::CT);
+    case RESID_RING96: return g.N / (16 * RingResid96::CT);
+    case RESID_BIG: return g.N / (resid_prefers_96(g) ? 48 : 64);
+    default: return g.N / kTileN;
+  }
+}
+
 template <int EPI>
 static hipError_t big_attr() {
   hipError_t e = hipFuncSetAttribute((const void *)gemm_big_kernel<EPI, big_ct<EPI>()>,
@@ -1279,19 +1340,18 @@ hipError_t launch_gemm(int epi, const GemmArgs &g, const GemmPlan &p, hipStream_
   if (epi == EPI_GEGLU && ring_fits<EPI_GEGLU>(g)) return launch_ring<EPI_GEGLU>(g, s, ev0, ev1);
   if (epi == EPI_QKV && ring_fits<EPI_QKV>(g)) return launch_ring<EPI_QKV>(g, s, ev0, ev1);
   if (epi == EPI_RESID_F32) {
+    using S8 = RingShape<EPI_RESID_F32>;
     GemmArgs gk = g;
-    if (resid_prefers_96(g)) {
-      gk.kx = resid_ksplit<RingResid96>(g);
-      if (gk.kx > 1) return launch_ring_ns<EPI_RESID_F32, RingResid96::NS, RingResid96, true>(gk, s, ev0, ev1);
-    } else {
-      using S8 = RingShape<EPI_RESID_F32>;
-      gk.kx = resid_ksplit<S8>(g);
-      if (gk.kx > 1) return launch_ring_ns<EPI_RESID_F32, S8::NS, S8, true>(gk, s, ev0, ev1);
+    switch (resid_path(g, &gk.kx)) {
+      case RESID_RING96:
+        if (gk.kx > 1) return launch_ring_ns<EPI_RESID_F32, RingResid96::NS, RingResid96, true>(gk, s, ev0, ev1);
+        return launch_ring_ns<EPI_RESID_F32, RingResid96::NS, RingResid96>(g, s, ev0, ev1);
+      case RESID_RING:
+        if (gk.kx > 1) return launch_ring_ns<EPI_RESID_F32, S8::NS, S8, true>(gk, s, ev0, ev1);
+        return launch_ring<EPI_RESID_F32>(g, s, ev0, ev1);
+      default: break;
     }
   }
-  if (epi == EPI_RESID_F32 && ring96_fits(g))
-    return launch_ring_ns<EPI_RESID_F32, RingResid96::NS, RingResid96>(g, s, ev0, ev1);
-  if (epi == EPI_RESID_F32 && ring_fits<EPI_RESID_F32>(g)) return launch_ring<EPI_RESID_F32>(g, s, ev0, ev1);
   if (big_ok(epi, g)) {
     switch (epi) {
       case EPI_BIAS_SILU: return launch_big<EPI_BIAS_SILU>(g, s, ev0, ev1);

@@ -804,9 +804,10 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
     if (prof) c->prof_pending.push_back({cls, ea_, eb_}); \
   } while (0)
   if (!c->dbg) {
+    int ssq_tiles = d / 16;  // sums of squares per row of the last writer of ssq
     // RMSNorm folding: residual GEMMs write ssq and the next operand; consumers scale by rstd
     auto norm_fields = [&](GemmArgs &x) {
-      x.ssq = c->ssq; x.ssq_tiles = d / 16; x.m_alloc = (int)MA; x.eps = c->cfg.rms_eps;
+      x.ssq = c->ssq; x.ssq_tiles = ssq_tiles; x.m_alloc = (int)MA; x.eps = c->cfg.rms_eps;
       x.kx_ws = c->kx_ws; x.kx_cnt = c->kx_cnt; x.kx_ws_bytes = c->kx_ws_bytes; x.kx_tiles = c->n_cu;
     };
     const int n_mod = c->n_mod;
@@ -826,6 +827,7 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
       g2.out = c->h; g2.ldo = d; g2.bias = c->t2_b; norm_fields(g2);
       g2.gain_next = c->layers[0].attn_norm; g2.next = c->a_n;
       UAD_CHECK_CLS(K_GEMM_TIME_OUT, launch_gemm(EPI_RESID_F32, g2, plan_gemm(EPI_RESID_F32, M, d, d), s, ea_, eb_));
+      ssq_tiles = resid_ssq_tiles(g2);
     } else if (pre) {
       // conditioning computed for the whole schedule: h_0 = W_in x + b_in and the
       // first attention norm's operand h_0 (1 + a) from this step's modulations
@@ -957,6 +959,7 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
         if (ada_batched) { o.mod_row = c->mod_cls; o.mod_scale_next = nullptr; }
       }
       UAD_CHECK_CLS(K_GEMM_O, launch_gemm(EPI_RESID_F32, o, po, s, ea_, eb_));
+      ssq_tiles = resid_ssq_tiles(o);
       GemmArgs gu{};
       gu.status = c->status;
       gu.M = M; gu.A = c->a_n; gu.W = lp.wgu; gu.N = 2 * F; gu.K = d;
@@ -982,6 +985,7 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
         if (ada_batched) { dn.mod_row = c->mod_cls; dn.mod_scale_next = nullptr; }
       }
       UAD_CHECK_CLS(K_GEMM_DOWN, launch_gemm(EPI_RESID_F32, dn, pd, s, ea_, eb_));
+      ssq_tiles = resid_ssq_tiles(dn);
     }
   }
   FinalArgs f{};

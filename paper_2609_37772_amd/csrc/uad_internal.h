@@ -167,10 +167,11 @@ struct GemmPlan {
 
 struct GemmArgs {
   const op_t *A;    // activations, fragment order [rows/16][K/32][64][8]
-  // RMSNorm folded into the GEMMs: a residual GEMM writes ssq[tile][row] (sum of
-  // squares of h over its 16 columns) and the next operand fp16(h * gain_next);
+  // RMSNorm folded into the GEMMs: a residual GEMM writes ssq[tile][row] (sums of
+  // squares of h over runs of columns, resid_ssq_tiles of them) and the next
+  // operand fp16(h * gain_next);
   // a consuming GEMM scales its accumulator by rstd[row] from those sums.
-  float *ssq;             // [d/16][m_alloc]
+  float *ssq;             // [<= d/16][m_alloc]
   int ssq_tiles;
   int m_alloc;            // rows allocated in every operand / output buffer (>= M, multiple of 16)
   float eps;
@@ -314,6 +315,7 @@ struct PrefixArgs {
 // Launchers (defined in the .hip translation units)
 // ---------------------------------------------------------------------------
 GemmPlan plan_gemm(int epi, int M, int N, int K);
+int resid_ssq_tiles(const GemmArgs &g);  // sums of squares per row that this residual projection writes
 // ev0 / ev1: optional events recorded at the start / end of the launched
 // kernel(s) (nullptr for none).
 hipError_t launch_gemm(int epi, const GemmArgs &g, const GemmPlan &p, hipStream_t s, hipEvent_t ev0 = nullptr,
