@@ -645,13 +645,10 @@ __device__ __forceinline__ void big_epilogue(const GemmArgs &g, f32x4 (&acc)[TA]
 template <int EPI, int CT, int KS = 1>
 __global__ __launch_bounds__(256 * KS) void gemm_big_kernel(GemmArgs g) {
   constexpr int TA = kBigRowTiles / 2, TB = CT / 2, PD = kBigPD;
-  constexpr bool kRstd = (EPI == EPI_QKV || EPI == EPI_GEGLU);
+  static_assert(EPI == EPI_BIAS_SILU || EPI == EPI_RESID_F32 || EPI == EPI_MOD, "QKV and gate/up run on the ring");
   static_assert(KS == 1 || (KS == 2 && TA % 2 == 0), "k-halves: even row tiles");
-  typedef __attribute__((address_space(3))) void lds_void;
-  // [ssq_tiles][128] sums of squares of the workgroup's rows when kRstd;
-  // KS = 2: then the k-halves' exchange, [4 waves][2 halves][TA/2][TB][64] f32x4
-  extern __shared__ __align__(16) float ssq_s[];
-  __shared__ float rstd_s[128];
+  // KS = 2: the k-halves' exchange, [4 waves][2 halves][TA/2][TB][64] f32x4
+  extern __shared__ __align__(16) float xch_s[];
   int mt0, nt0;
   if ((EPI == EPI_MOD || EPI == EPI_BIAS_SILU) && g.m_dev) {
     // row count known on the device only (usually one panel): panel-major over
@@ -671,15 +668,6 @@ __global__ __launch_bounds__(256 * KS) void gemm_big_kernel(GemmArgs g) {
   const int KB = g.K / kTileK;
   const int nkb = KB / KS;  // this wave's k-blocks kh, kh + KS, ... (the host checks KB % KS == 0)
   const int mt_last = g.m_alloc / 16 - 1;  // allocated row tiles (rows >= M are computed, never stored)
-  if (kRstd && g.use_rstd) {
-    // this workgroup's 128 rows' per-tile sums of squares, straight to LDS
-    for (int j = wave; j < 2 * g.ssq_tiles; j += 4 * KS) {
-      const int tile = j >> 1, half = j & 1;
-      const int row = min(mt0 * 16 + half * 64 + lane, g.M - 1);
-      __builtin_amdgcn_global_load_lds((const void *)(g.ssq + (size_t)tile * g.m_alloc + row),
-                                       (lds_void *)(ssq_s + tile * 128 + half * 64), 4, 0, 0);
-    }
-  }
   const op_t *pa[TA], *pb[TB];
 #pragma unroll
   for (int i = 0; i < TA; ++i)
@@ -719,23 +707,12 @@ __global__ __launch_bounds__(256 * KS) void gemm_big_kernel(GemmArgs g) {
     }
   }
 
-  if (kRstd && g.use_rstd) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's statistics landed
-    __syncthreads();                                  // ... every wave's
-    if (threadIdx.x < 128) {
-      float ss = 0.f;
-      for (int t = 0; t < g.ssq_tiles; ++t) ss += ssq_s[t * 128 + threadIdx.x];
-      rstd_s[threadIdx.x] = 1.0f / sqrtf(ss / (float)g.K + g.eps);
-    }
-    __syncthreads();
-  }
-
   unsigned bad = 0;  // fp16 range flag of this thread's stores
   if constexpr (KS == 2) {
     // Wave (wq, 0) keeps row tiles [0, H) and hands [H, TA) to wave (wq, 1),
     // which keeps [H, TA); each adds the other's partial of what it keeps.
     constexpr int H = TA / 2;
-    f32x4 *xch = (f32x4 *)(ssq_s + (kRstd && g.use_rstd ? g.ssq_tiles * 128 : 0));
+    f32x4 *xch = (f32x4 *)xch_s;
     f32x4 *mine = xch + (size_t)(wq * 2 + kh) * (H * TB * 64) + lane;
     const f32x4 *other = xch + (size_t)(wq * 2 + (kh ^ 1)) * (H * TB * 64) + lane;
     if (kh == 0) {
@@ -750,23 +727,21 @@ __global__ __launch_bounds__(256 * KS) void gemm_big_kernel(GemmArgs g) {
         for (int j = 0; j < TB; ++j) mine[(i * TB + j) * 64] = acc[i][j];
     }
     __syncthreads();
-    const float *rs = (kRstd && g.use_rstd) ? rstd_s + wr * TA * 16 : nullptr;
     if (kh == 0) {
 #pragma unroll
       for (int i = 0; i < H; ++i)
 #pragma unroll
         for (int j = 0; j < TB; ++j) acc[i][j] = acc[i][j] + other[(i * TB + j) * 64];
-      big_epilogue<EPI, TA, TB, 0, H>(g, acc, mt0 + wr * TA, nt0 + wc * TB, lane, rs, bad);
+      big_epilogue<EPI, TA, TB, 0, H>(g, acc, mt0 + wr * TA, nt0 + wc * TB, lane, nullptr, bad);
     } else {
 #pragma unroll
       for (int i = 0; i < H; ++i)
 #pragma unroll
         for (int j = 0; j < TB; ++j) acc[H + i][j] = other[(i * TB + j) * 64] + acc[H + i][j];
-      big_epilogue<EPI, TA, TB, H, H>(g, acc, mt0 + wr * TA, nt0 + wc * TB, lane, rs, bad);
+      big_epilogue<EPI, TA, TB, H, H>(g, acc, mt0 + wr * TA, nt0 + wc * TB, lane, nullptr, bad);
     }
   } else {
-    big_epilogue<EPI, TA, TB>(g, acc, mt0 + wr * TA, nt0 + wc * TB, lane,
-                              (kRstd && g.use_rstd) ? rstd_s + wr * TA * 16 : nullptr, bad);
+    big_epilogue<EPI, TA, TB>(g, acc, mt0 + wr * TA, nt0 + wc * TB, lane, nullptr, bad);
   }
   flush_range(g.status, bad);
 }
@@ -802,11 +777,11 @@ template <int EPI>
 struct RingShape;
 template <>
 struct RingShape<EPI_GEGLU> {
-  static constexpr int RT = 8, CT = 16, WR = 2, WC = 4, NS = 3, MinM = 1024;
+  static constexpr int RT = 8, CT = 16, WR = 2, WC = 4, NS = 3;
 };
 template <>
 struct RingShape<EPI_QKV> {
-  static constexpr int RT = 8, CT = 8, WR = 2, WC = 4, NS = 4, MinM = 2560;
+  static constexpr int RT = 8, CT = 8, WR = 2, WC = 4, NS = 4;
 };
 template <>
 struct RingShape<EPI_RESID_F32> {
@@ -816,12 +791,24 @@ struct RingShape<EPI_RESID_F32> {
 // 144 x 256 gate/up tiles, 1 x 8 waves of 144 x 32 (one gate/up pair each):
 // fewer tiles where 128-row ones would leave some CUs a fourth tile
 struct RingGeGlu144 {
-  static constexpr int RT = 9, CT = 16, WR = 1, WC = 8, NS = 3, MinM = 1024;
+  static constexpr int RT = 9, CT = 16, WR = 1, WC = 8, NS = 3;
 };
 // 160 x 256 gate/up tiles, 2 x 4 waves of 80 x 64 (two stages only: two
 // workgroups' three stages and row statistics exceed the 160 KiB of LDS)
 struct RingGeGlu160 {
-  static constexpr int RT = 10, CT = 16, WR = 2, WC = 4, NS = 3, MinM = 1024;
+  static constexpr int RT = 10, CT = 16, WR = 2, WC = 4, NS = 3;
+};
+
+// Tiles for a few hundred rows, where 128-row tiles leave CUs idle: 64 x 64 (2 x 4
+// waves of 32 x 16), 64 x 128 (32 x 32) and, for gate/up, 128 x 128 (64 x 32)
+struct Ring64x64 {
+  static constexpr int RT = 4, CT = 4, WR = 2, WC = 4, NS = 4;
+};
+struct Ring64x128 {
+  static constexpr int RT = 4, CT = 8, WR = 2, WC = 4, NS = 4;
+};
+struct Ring128x128 {
+  static constexpr int RT = 8, CT = 8, WR = 2, WC = 4, NS = 4;
 };
 
 // 128 x 96 tiles: the residual projections where 96-column tiles are preferred
@@ -886,7 +873,7 @@ __global__ __launch_bounds__(512) void gemm_ring_kernel(GemmArgs g) {
   // slice of its partial sums.  The first kPre go out ahead of the ring's loads,
   // so that their use waits for none of those.
   constexpr bool kNorm = EPI != EPI_RESID_F32;
-  constexpr int kPre = kNorm ? 4 : 1;
+  constexpr int kPre = kNorm ? 16 : 1;  // 64 sums (small-M producer) over 4 threads
   float pre[kPre];
   int t0 = 0, t1 = 0;
   const float *sp = g.ssq;
@@ -1031,35 +1018,56 @@ static bool resid_prefers_96(const GemmArgs &g) {
   return g.N % 96 == 0 && per_cu(6) < per_cu(8);
 }
 
-template <int EPI, int CT>
-static bool big_khalves(const GemmArgs &g);
+// Output tiles of rows x cols.
+static int tiles_of(const GemmArgs &g, int rows, int cols) { return (g.M + rows - 1) / rows * (g.N / cols); }
 
-// Below MinM rows the ring still wins for QKV where the register-streamed
-// kernel would not take its k-halves (K < 1536) once its tiles reach 3/8 of
-// the CUs, and for the residual projections once they fill half the CUs.
-// Same-machine A/B on the 1024-wide expert (ms per joint step): 15 environments
-// 2.079 -> 2.054, 20 2.451 -> 2.364, 24 2.803 -> 2.733, 32 3.326 -> 3.262,
-// 40 3.548 -> 3.321, 48 3.964 -> 3.780; QKV at 750 / 1000 / 2000 rows
-// 21.4 / 25.0 / 33.4 -> 19.5 /
-// 20.2 / 26.4 us, down at 2000 rows 50.6 -> 46.6 us. The ring lost for QKV
-// at 60-80 tiles (300-500 rows), for the residual projections at 80-104
-// tiles (the k-halves win there), for gate/up below 1024 rows, and on the
-// 1536-wide expert.
-template <int EPI>
-static bool ring_rows_ok(const GemmArgs &g) {
-  using S = RingShape<EPI>;
-  if (g.M >= S::MinM) return true;
-  const int tiles = (g.M + 16 * S::RT - 1) / (16 * S::RT) * (g.N / (16 * S::CT));
-  if constexpr (EPI == EPI_QKV) return 8 * tiles >= 3 * g_n_cu && !big_khalves<EPI_QKV, 8>(g);
-  if constexpr (EPI == EPI_RESID_F32) return 2 * tiles >= g_n_cu;
-  return false;
+// Residual projections on 128 x 128 ring tiles: from 2560 rows, below that once
+// the tiles fill half the CUs (the register-streamed kernel's k-halves win with
+// fewer: 80-104 tiles).
+static bool ring_resid_fits(const GemmArgs &g) {
+  using S = RingShape<EPI_RESID_F32>;
+  return (g.M >= S::MinM || 2 * tiles_of(g, 128, 128) >= g_n_cu) && g.N % 128 == 0 && g.A2 == nullptr &&
+         !resid_prefers_96(g);
 }
 
-template <int EPI>
-static bool ring_fits(const GemmArgs &g) {
-  using S = RingShape<EPI>;
-  return ring_rows_ok<EPI>(g) && g.N % (16 * S::CT) == 0 && g.A2 == nullptr && g.K / kTileK >= 1 &&
-         !(EPI == EPI_QKV && g.q_dim % 16 != 0) && !(EPI == EPI_RESID_F32 && resid_prefers_96(g));
+// Tile of the QKV and gate/up projections on the ring, rows * 1000 + columns, or
+// 0 for the small-M kernel.  A tile walks all of K in one workgroup, so at a few
+// hundred rows 128-row tiles leave most CUs idle and the rest waiting on their
+// own load latency; smaller tiles re-read more of the operands for the same
+// products.  Same-machine, us per launch by tile (tiles in brackets; "small" is
+// the small-M kernel, "before" what the launch took until then):
+//   QKV 1024 -> 2560      64 x 64       64 x 128    128 x 128   small / before
+//     200 rows             8.5 (160)    11.6 (80)    14.2 (40)    8.8 /  9.9
+//     400                  9.9 (280)    12.0 (140)   14.8 (80)   13.0 / 14.9
+//     800                 13.0 (520)    14.6 (260)   15.1 (140)       / 18.3
+//     1600                19.0 (1000)   17.8 (500)   20.2 (260)       / 20.2
+//     2000                24.4 (1280)   23.6 (640)   22.9 (320)       / 22.9
+//   QKV 1536 -> 2048: 384 rows 11.0 (192) 15.5 18.8, before 15.6; 1024 rows 15.2
+//     (512) 16.7 19.0, before 23.0; 2048 rows 25.8 (1024) 23.0 21.2, before 23.9
+//   gate/up 1024 -> 8192  64 x 128      128 x 128   128 x 256   small / before
+//     111 rows            10.9 (128)    12.1 (64)    18.7 (32)    9.8 / 11.4
+//     200                 11.8 (256)    12.6 (128)   19.1 (64)   16.8 / 19.5
+//     400                 13.9 (448)    13.3 (256)   19.4 (128)       / 21.9
+//     800                 25.3 (832)    19.0 (448)   20.5 (224)       / 22.8
+//     1050                29.2 (1088)   28.8 (576)   27.3 (288)       / 30.0
+//   gate/up 1536 -> 12288: 128 rows 15.7 (192) 17.3 26.7, before 26.3; 640 rows
+//     36.4 (960) 27.8 (480) 28.9 (240), before 31.4
+static int ring_tile_qkv(const GemmArgs &g) {
+  if (g.A2 || g.M <= 64 || g.N % 64 != 0 || g.q_dim % 16 != 0) return 0;
+  const int t64 = tiles_of(g, 64, 64);
+  if (16 * t64 < 9 * g_n_cu) return 0;
+  if (4 * t64 <= 11 * g_n_cu || g.N % 128 != 0) return 64064;
+  // just past one round of 128 x 128 tiles, and smaller ones fit two a CU
+  if (tiles_of(g, 128, 128) > g_n_cu && tiles_of(g, 64, 128) <= 2 * g_n_cu) return 64128;
+  return 128128;
+}
+
+static int ring_tile_geglu(const GemmArgs &g) {
+  if (g.A2 || g.M <= 64 || g.N % 128 != 0) return 0;
+  const int t = tiles_of(g, 64, 128);
+  if (16 * t < 9 * g_n_cu) return 0;
+  if (t <= g_n_cu) return 64128;
+  return tiles_of(g, 128, 128) <= 2 * g_n_cu || g.N % 256 != 0 ? 128128 : 128256;
 }
 
 // The residual projections where 96-column tiles are preferred, on the
@@ -1072,6 +1080,29 @@ static bool ring96_fits(const GemmArgs &g) {
   const int tiles = (g.M + 16 * RingResid96::RT - 1) / (16 * RingResid96::RT) * (g.N / (16 * RingResid96::CT));
   return g.M >= RingResid96::MinM && (4 * tiles >= 3 * g_n_cu || g.K >= 4096) && resid_prefers_96(g) &&
          g.A2 == nullptr && g.K / kTileK >= 1;
+}
+
+// The residual projections on 64 x 64 ring tiles (kx: split over K), 0 when they
+// don't take them.  Short K (O, time MLP): from 9/16 of the CUs in tiles to two
+// tiles a CU.  K >= 4096 (down): fewer tiles, split over K four ways up to 2/3 of
+// the CUs and two ways up to 27/32.  Same-machine, us per launch (tiles of 64 x 64):
+//   O 2048 -> 1024     800 rows (208) 16.0 -> 13.4, 1050 (272) 19.1 -> 15.2, 1600
+//     (400) 20.2 -> 16.5, 2000 (512) 21.6 -> 20.4, 2400 (608) 25.5 -> 25.5; 400
+//     rows (112) 9.5 -> 12.9, hence the bounds
+//   O 1536 -> 1536     384 (144) 13.7 -> 11.1, 640 (240) 18.3 -> 11.4, 1024 (384)
+//     17.0 -> 13.7, 2048 (768) 23.0 -> 23.4
+//   down 4096 -> 1024  by splits 1 / 2 / 4: 300 rows (80) 14.1 -> 22.0 / 15.7 / 13.1,
+//     400 (112) 15.0 -> 22.0 / 15.8 / 13.0, 600 (160) 20.4 -> 22.3 / 18.4 / 17.0, 800
+//     (208) 26.0 -> 22.7 / 18.4 / 20.6, 1050 (272) 23.3 -> 28.5
+//   down 6144 -> 1536  256 (96) 21.3 -> 31.1 / 20.8 / 15.9, 384 (144) 30.4 -> 31.4 /
+//     23.4 / 20.7, 640 (240) 27.5 -> 40.6 / 31.5; 128 (48) 14.8 -> - / 23.6 / 15.8
+static int resid_ring64(const GemmArgs &g) {
+  if (g.A2 || g.mod_scale_next || (g.mod_gate && !g.mod_row) || g.M <= 64 || g.N % 64 != 0) return 0;
+  const int t = tiles_of(g, 64, 64);
+  if (g.K < 4096) return 16 * t >= 9 * g_n_cu && t <= 2 * g_n_cu ? 1 : 0;
+  if (16 * t < 5 * g_n_cu || 32 * t > 27 * g_n_cu || !g.kx_ws || !g.kx_cnt || t > g.kx_tiles) return 0;
+  const int kx = 3 * t <= 2 * g_n_cu ? 4 : 2;
+  return (size_t)t * kx * 64 * 64 * sizeof(float) <= g.kx_ws_bytes ? kx : 0;
 }
 
 // Split-K of the batched residual projections on the ring: kx = CUs / tiles
@@ -1132,18 +1163,23 @@ static int geglu_tile_rows(const GemmArgs &g) {
   return 128;
 }
 
-template <int EPI>
-static hipError_t launch_ring(const GemmArgs &g, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-  if constexpr (EPI == EPI_GEGLU) {
-    const int rows = geglu_tile_rows(g);
-    if (rows == 160) return launch_ring_ns<EPI, 2, RingGeGlu160>(g, s, ev0, ev1);
-    if (rows == 144) {
-      if (g.K <= 1024) return launch_ring_ns<EPI, 2, RingGeGlu144>(g, s, ev0, ev1);
-      return launch_ring_ns<EPI, RingGeGlu144::NS, RingGeGlu144>(g, s, ev0, ev1);
-    }
-    if (g.K <= 1024) return launch_ring_ns<EPI, 2>(g, s, ev0, ev1);
+static hipError_t launch_ring_geglu(const GemmArgs &g, int tile, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+  if (tile == 64128) return launch_ring_ns<EPI_GEGLU, Ring64x128::NS, Ring64x128>(g, s, ev0, ev1);
+  if (tile == 128128) return launch_ring_ns<EPI_GEGLU, Ring128x128::NS, Ring128x128>(g, s, ev0, ev1);
+  const int rows = geglu_tile_rows(g);
+  if (rows == 160) return launch_ring_ns<EPI_GEGLU, 2, RingGeGlu160>(g, s, ev0, ev1);
+  if (rows == 144) {
+    if (g.K <= 1024) return launch_ring_ns<EPI_GEGLU, 2, RingGeGlu144>(g, s, ev0, ev1);
+    return launch_ring_ns<EPI_GEGLU, RingGeGlu144::NS, RingGeGlu144>(g, s, ev0, ev1);
   }
-  return launch_ring_ns<EPI, RingShape<EPI>::NS>(g, s, ev0, ev1);
+  if (g.K <= 1024) return launch_ring_ns<EPI_GEGLU, 2>(g, s, ev0, ev1);
+  return launch_ring_ns<EPI_GEGLU, RingShape<EPI_GEGLU>::NS>(g, s, ev0, ev1);
+}
+
+static hipError_t launch_ring_qkv(const GemmArgs &g, int tile, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+  if (tile == 64064) return launch_ring_ns<EPI_QKV, Ring64x64::NS, Ring64x64>(g, s, ev0, ev1);
+  if (tile == 64128) return launch_ring_ns<EPI_QKV, Ring64x128::NS, Ring64x128>(g, s, ev0, ev1);
+  return launch_ring_ns<EPI_QKV, RingShape<EPI_QKV>::NS>(g, s, ev0, ev1);
 }
 
 template <int EPI, int NS, class S = RingShape<EPI>, bool KSPLIT = false>
@@ -1151,22 +1187,6 @@ static hipError_t ring_attr_ns() {
   return hipFuncSetAttribute((const void *)gemm_ring_kernel<EPI, NS, S, KSPLIT>, hipFuncAttributeMaxDynamicSharedMemorySize,
                              NS * (S::RT + S::CT) * kBlockElems * (int)sizeof(op_t));
 }
-
-template <int EPI>
-static hipError_t ring_attr() {
-  hipError_t e = ring_attr_ns<EPI, RingShape<EPI>::NS>();
-  if constexpr (EPI == EPI_GEGLU) {
-    if (e == hipSuccess) e = ring_attr_ns<EPI, 2>();
-    if (e == hipSuccess) e = ring_attr_ns<EPI, 2, RingGeGlu144>();
-    if (e == hipSuccess) e = ring_attr_ns<EPI, RingGeGlu144::NS, RingGeGlu144>();
-    if (e == hipSuccess) e = ring_attr_ns<EPI, 2, RingGeGlu160>();
-  }
-  return e;
-}
-
-// 16*CT columns per workgroup: 256 for gate/up (the widest projection), 128 otherwise
-template <int EPI>
-constexpr int big_ct() { return EPI == EPI_GEGLU ? 16 : 8; }
 
 // LDS of the k-halves' exchange (gemm_big_kernel with KS = 2)
 template <int CT>
@@ -1182,7 +1202,7 @@ constexpr size_t big_xch_bytes() { return (size_t)4 * 2 * (kBigRowTiles / 4) * (
 // K bound.
 template <int EPI, int CT>
 static bool big_khalves(const GemmArgs &g) {
-  if constexpr (CT > 8 || !(EPI == EPI_RESID_F32 || EPI == EPI_QKV || EPI == EPI_BIAS_SILU)) {
+  if constexpr (EPI == EPI_MOD) {
     return false;
   } else {
     const int tiles = (g.M + 16 * kBigRowTiles - 1) / (16 * kBigRowTiles) * (g.N / (16 * CT));
@@ -1192,17 +1212,15 @@ static bool big_khalves(const GemmArgs &g) {
 
 template <int EPI, int CT>
 static hipError_t launch_big_ct(const GemmArgs &g, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-  const bool rstd = (EPI == EPI_QKV || EPI == EPI_GEGLU) && g.use_rstd;
-  const size_t lds = rstd ? (size_t)g.ssq_tiles * 128 * 4 : 0;
   const int wgs = grid_tile_wgs(g.M, 16 * kBigRowTiles, g.N / (16 * CT));
-  if constexpr (CT <= 8 && (EPI == EPI_RESID_F32 || EPI == EPI_QKV || EPI == EPI_BIAS_SILU)) {
+  if constexpr (EPI != EPI_MOD) {
     if (big_khalves<EPI, CT>(g)) {
-      UAD_LAUNCH((gemm_big_kernel<EPI, CT, 2>), dim3(wgs), dim3(512), (uint32_t)(lds + big_xch_bytes<CT>()), s,
+      UAD_LAUNCH((gemm_big_kernel<EPI, CT, 2>), dim3(wgs), dim3(512), (uint32_t)big_xch_bytes<CT>(), s,
                  ev0, ev1, g);
       return hipGetLastError();
     }
   }
-  UAD_LAUNCH((gemm_big_kernel<EPI, CT>), dim3(wgs), dim3(256), (uint32_t)lds, s, ev0, ev1, g);
+  UAD_LAUNCH((gemm_big_kernel<EPI, CT>), dim3(wgs), dim3(256), 0, s, ev0, ev1, g);
   return hipGetLastError();
 }
 
@@ -1210,7 +1228,7 @@ template <int EPI>
 static hipError_t launch_big(const GemmArgs &g, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   if constexpr (EPI == EPI_RESID_F32)
     if (resid_prefers_96(g)) return launch_big_ct<EPI, 6>(g, s, ev0, ev1);
-  return launch_big_ct<EPI, big_ct<EPI>()>(g, s, ev0, ev1);
+  return launch_big_ct<EPI, 8>(g, s, ev0, ev1);
 }
 
 // The batched kernel serves M >= kBigM when the columns divide into its tiles,
@@ -1221,22 +1239,20 @@ static hipError_t launch_big(const GemmArgs &g, hipStream_t s, hipEvent_t ev0, h
 // the projection shapes of the 1024- and 1536-wide experts (the rule picks
 // the faster kernel in 49 of 50 cases, the miss by 6%).
 static bool big_ok(int epi, const GemmArgs &g) {
-  const int ct = epi == EPI_GEGLU ? 16 : 8;
-  if (g.M < kBigM || g.N % (16 * ct) != 0 || g.ssq_tiles > kMaxSsqTiles || (epi == EPI_QKV && g.q_dim % 16 != 0) ||
-      g.A2 || g.mod_scale_next)
-    return false;
-  const int tiles = (g.M + 16 * kBigRowTiles - 1) / (16 * kBigRowTiles) * (g.N / (16 * ct));
+  if (epi == EPI_QKV || epi == EPI_GEGLU || g.M < kBigM || g.N % 128 != 0 || g.mod_scale_next) return false;
+  const int tiles = tiles_of(g, 128, 128);
   return tiles >= 90 && !(tiles < 128 && g.K > 4096);
 }
 
 // Which kernel a residual projection takes (kx: its split over K).
-enum ResidPath { RESID_SMALL, RESID_BIG, RESID_RING, RESID_RING96 };
+enum ResidPath { RESID_SMALL, RESID_BIG, RESID_RING, RESID_RING96, RESID_RING64 };
 static ResidPath resid_path(const GemmArgs &g, int *kx) {
+  if ((*kx = resid_ring64(g)) > 0) return RESID_RING64;
   const bool p96 = resid_prefers_96(g);
   *kx = p96 ? resid_ksplit<RingResid96>(g) : resid_ksplit<RingShape<EPI_RESID_F32>>(g);
   if (*kx > 1) return p96 ? RESID_RING96 : RESID_RING;
   if (ring96_fits(g)) return RESID_RING96;
-  if (ring_fits<EPI_RESID_F32>(g)) return RESID_RING;
+  if (ring_resid_fits(g)) return RESID_RING;
   return big_ok(EPI_RESID_F32, g) ? RESID_BIG : RESID_SMALL;
 }
 
@@ -1251,27 +1267,16 @@ int resid_ssq_tiles(const GemmArgs &g) {
   switch (resid_path(g, &kx)) {
     case RESID_RING: return g.N / (16 * RingShape<EPI_RESID_F32>::CT);
     case RESID_RING96: return g.N / (16 * RingResid96::CT);
+    case RESID_RING64: return g.N / 64;
     case RESID_BIG: return g.N / (resid_prefers_96(g) ? 48 : 64);
     default: return g.N / kTileN;
   }
 }
 
-template <int EPI>
+template <int EPI, int CT>
 static hipError_t big_attr() {
-  hipError_t e = hipFuncSetAttribute((const void *)gemm_big_kernel<EPI, big_ct<EPI>()>,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, kMaxSsqTiles * 128 * 4);
-  if constexpr (EPI == EPI_RESID_F32 || EPI == EPI_QKV || EPI == EPI_BIAS_SILU) {
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void *)gemm_big_kernel<EPI, 8, 2>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)(kMaxSsqTiles * 128 * 4 + big_xch_bytes<8>()));
-    if constexpr (EPI == EPI_RESID_F32)
-      if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)gemm_big_kernel<EPI, 6, 2>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)(kMaxSsqTiles * 128 * 4 + big_xch_bytes<6>()));
-  }
-  return e;
+  return hipFuncSetAttribute((const void *)gemm_big_kernel<EPI, CT, 2>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)big_xch_bytes<CT>());
 }
 
 hipError_t gemm_init() {
@@ -1279,17 +1284,25 @@ hipError_t gemm_init() {
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&g_n_cu, hipDeviceAttributeMultiprocessorCount, dev);
   if (e == hipSuccess && g_n_cu < 1) e = hipErrorInvalidDevice;
-  if (e == hipSuccess) e = ring_attr<EPI_GEGLU>();
-  if (e == hipSuccess) e = ring_attr<EPI_QKV>();
-  if (e == hipSuccess) e = ring_attr<EPI_RESID_F32>();
+  if (e == hipSuccess) e = ring_attr_ns<EPI_GEGLU, RingShape<EPI_GEGLU>::NS>();
+  if (e == hipSuccess) e = ring_attr_ns<EPI_GEGLU, 2>();
+  if (e == hipSuccess) e = ring_attr_ns<EPI_GEGLU, 2, RingGeGlu144>();
+  if (e == hipSuccess) e = ring_attr_ns<EPI_GEGLU, RingGeGlu144::NS, RingGeGlu144>();
+  if (e == hipSuccess) e = ring_attr_ns<EPI_GEGLU, 2, RingGeGlu160>();
+  if (e == hipSuccess) e = ring_attr_ns<EPI_GEGLU, Ring64x128::NS, Ring64x128>();
+  if (e == hipSuccess) e = ring_attr_ns<EPI_GEGLU, Ring128x128::NS, Ring128x128>();
+  if (e == hipSuccess) e = ring_attr_ns<EPI_QKV, RingShape<EPI_QKV>::NS>();
+  if (e == hipSuccess) e = ring_attr_ns<EPI_QKV, Ring64x128::NS, Ring64x128>();
+  if (e == hipSuccess) e = ring_attr_ns<EPI_QKV, Ring64x64::NS, Ring64x64>();
+  if (e == hipSuccess) e = ring_attr_ns<EPI_RESID_F32, RingShape<EPI_RESID_F32>::NS>();
+  if (e == hipSuccess) e = ring_attr_ns<EPI_RESID_F32, Ring64x64::NS, Ring64x64>();
+  if (e == hipSuccess) e = ring_attr_ns<EPI_RESID_F32, Ring64x64::NS, Ring64x64, true>();
   if (e == hipSuccess) e = ring_attr_ns<EPI_RESID_F32, RingResid96::NS, RingResid96>();
   if (e == hipSuccess) e = ring_attr_ns<EPI_RESID_F32, RingShape<EPI_RESID_F32>::NS, RingShape<EPI_RESID_F32>, true>();
   if (e == hipSuccess) e = ring_attr_ns<EPI_RESID_F32, RingResid96::NS, RingResid96, true>();
-  if (e == hipSuccess) e = big_attr<EPI_BIAS_SILU>();
-  if (e == hipSuccess) e = big_attr<EPI_RESID_F32>();
-  if (e == hipSuccess) e = big_attr<EPI_GEGLU>();
-  if (e == hipSuccess) e = big_attr<EPI_QKV>();
-  if (e == hipSuccess) e = big_attr<EPI_MOD>();
+  if (e == hipSuccess) e = big_attr<EPI_BIAS_SILU, 8>();
+  if (e == hipSuccess) e = big_attr<EPI_RESID_F32, 8>();
+  if (e == hipSuccess) e = big_attr<EPI_RESID_F32, 6>();
   return e;
 }
 
@@ -1337,8 +1350,10 @@ hipError_t launch_gemm(int epi, const GemmArgs &g, const GemmPlan &p, hipStream_
   if (g.m_alloc < g.M || g.m_alloc % 16 != 0) return hipErrorInvalidValue;  // operand rows allocated
   // the batched kernels gate by modulation row and leave the next norm to its own pass
   if (g.M >= kBigM && g.mod_gate && (!g.mod_row || g.mod_scale_next)) return hipErrorInvalidValue;
-  if (epi == EPI_GEGLU && ring_fits<EPI_GEGLU>(g)) return launch_ring<EPI_GEGLU>(g, s, ev0, ev1);
-  if (epi == EPI_QKV && ring_fits<EPI_QKV>(g)) return launch_ring<EPI_QKV>(g, s, ev0, ev1);
+  if (epi == EPI_GEGLU)
+    if (const int tile = ring_tile_geglu(g)) return launch_ring_geglu(g, tile, s, ev0, ev1);
+  if (epi == EPI_QKV)
+    if (const int tile = ring_tile_qkv(g)) return launch_ring_qkv(g, tile, s, ev0, ev1);
   if (epi == EPI_RESID_F32) {
     using S8 = RingShape<EPI_RESID_F32>;
     GemmArgs gk = g;
@@ -1348,7 +1363,10 @@ hipError_t launch_gemm(int epi, const GemmArgs &g, const GemmPlan &p, hipStream_
         return launch_ring_ns<EPI_RESID_F32, RingResid96::NS, RingResid96>(g, s, ev0, ev1);
       case RESID_RING:
         if (gk.kx > 1) return launch_ring_ns<EPI_RESID_F32, S8::NS, S8, true>(gk, s, ev0, ev1);
-        return launch_ring<EPI_RESID_F32>(g, s, ev0, ev1);
+        return launch_ring_ns<EPI_RESID_F32, S8::NS, S8>(g, s, ev0, ev1);
+      case RESID_RING64:
+        if (gk.kx > 1) return launch_ring_ns<EPI_RESID_F32, Ring64x64::NS, Ring64x64, true>(gk, s, ev0, ev1);
+        return launch_ring_ns<EPI_RESID_F32, Ring64x64::NS, Ring64x64>(g, s, ev0, ev1);
       default: break;
     }
   }
@@ -1356,8 +1374,6 @@ hipError_t launch_gemm(int epi, const GemmArgs &g, const GemmPlan &p, hipStream_
     switch (epi) {
       case EPI_BIAS_SILU: return launch_big<EPI_BIAS_SILU>(g, s, ev0, ev1);
       case EPI_RESID_F32: return launch_big<EPI_RESID_F32>(g, s, ev0, ev1);
-      case EPI_GEGLU: return launch_big<EPI_GEGLU>(g, s, ev0, ev1);
-      case EPI_QKV: return launch_big<EPI_QKV>(g, s, ev0, ev1);
       case EPI_MOD: return launch_big<EPI_MOD>(g, s, ev0, ev1);
     }
     return hipErrorInvalidValue;
