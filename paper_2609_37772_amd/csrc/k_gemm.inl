@@ -362,8 +362,7 @@ static hipError_t launch_t(const GemmArgs &g, const GemmPlan &p, hipStream_t s, 
     }
   }
   if constexpr (EPI == EPI_RESID_F32 || EPI == EPI_BIAS_SILU || EPI == EPI_MOD) {
-    if (g.mod_row || g.m_dev) {
-      if ((EPI == EPI_RESID_F32) != (g.mod_row != nullptr)) return hipErrorInvalidValue;
+    if (EPI == EPI_RESID_F32 ? g.mod_row != nullptr : g.m_dev != nullptr) {
       UAD_LAUNCH((gemm_kernel<EPI, T, KPW, false, false, true>), grid, dim3(p.waves * 64), lds, s, ev0, ev1, g);
       return hipGetLastError();
     }

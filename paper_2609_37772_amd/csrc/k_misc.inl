@@ -184,6 +184,8 @@ __global__ __launch_bounds__(256) void final_kernel(FinalArgs f) {
   __shared__ float scratch[4];
   __shared__ float wsum[4][kFinalOuts];
   __shared__ float vs[kFinalOuts];
+  const int32_t *mod_row = f.mod_row;
+  if (MAP) f.env_map = nullptr;
   const int m = blockIdx.x;
   const int a0 = blockIdx.y * kFinalOuts;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -196,7 +198,7 @@ __global__ __launch_bounds__(256) void final_kernel(FinalArgs f) {
     const float *__restrict__ hr = f.h + (size_t)m * d;
     float hv[NC], gv[NC], sv[NC], wv[kFinalOuts][NC];
     const bool ada = f.mod_scale != nullptr;
-    const size_t mrow = (size_t)(MAP ? f.mod_row[m] : m) * f.mod_ld;
+    const size_t mrow = (size_t)(MAP ? mod_row[m] : m) * f.mod_ld;
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
       const int c = min(threadIdx.x + 256 * i, d - 1);
@@ -268,7 +270,8 @@ __global__ __launch_bounds__(256) void final_mfma_kernel(FinalArgs f) {
   const float *gr = f.gain, *sr = nullptr;
   if constexpr (ADA) {
     const int mc = min(m0 + (lane & 15), f.M - 1);
-    const size_t mr = (size_t)(f.mod_row ? f.mod_row[mc] : mc) * f.mod_ld;
+    const size_t mr = (size_t)f.mod_row[mc] * f.mod_ld;  // from 1024 rows on always by class
+    f.env_map = nullptr;
     gr = f.mod_scale + mr;
     sr = f.mod_shift + mr;
   }
@@ -734,9 +737,11 @@ hipError_t launch_ada_norm(const float *h, int M, int d, float eps, const float 
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_final(const FinalArgs &f, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+hipError_t launch_final(const FinalArgs &f, bool mapped, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+  if (mapped && (!f.mod_scale || !f.mod_row)) return hipErrorInvalidValue;
   if (f.M >= 1024 && !f.debug_field && f.d % 512 == 0 && f.Da <= 64) {
     const dim3 gr((f.M + 15) / 16);
+    if (f.mod_scale && !mapped) return hipErrorInvalidValue;
     if (f.mod_scale) {
       switch ((f.Da + 15) / 16) {
         case 1: UAD_LAUNCH((final_mfma_kernel<1, true>), gr, dim3(256), 0, s, ev0, ev1, f); return hipGetLastError();
@@ -755,7 +760,7 @@ hipError_t launch_final(const FinalArgs &f, hipStream_t s, hipEvent_t ev0, hipEv
   const dim3 grid(f.M, (f.Da + kFinalOuts - 1) / kFinalOuts);
 #define UAD_FINAL(NC)                                                                  \
   case NC:                                                                             \
-    if (f.mod_row)                                                                     \
+    if (mapped)                                                                        \
       UAD_LAUNCH((final_kernel<NC, true>), grid, dim3(256), 0, s, ev0, ev1, f);        \
     else                                                                               \
       UAD_LAUNCH((final_kernel<NC, false>), grid, dim3(256), 0, s, ev0, ev1, f);       \

@@ -994,12 +994,14 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
   f.is_last_step = is_last; f.step = step; f.v_out = v_out; f.released = released; f.release_step = release_step;
   f.debug_field = c->dbg ? 1 : 0; f.dbg_alpha = c->dbg_alpha; f.dbg_beta = c->dbg_beta;
   f.vsum = vsum; f.vsum_tokens = vsum_tokens; f.chunk = H; f.env_map = env_map;
+  const bool by_class = !c->dbg && ada_by_class(c, M, pre != nullptr);
+  if (by_class && env_map) return fail(c, UAD_E_STATE, "adaptive norms: a compacted step");
   if (c->ada) {
     f.mod_scale = (pre ? pre->mod : c->mod) + (size_t)c->L * 6 * d; f.mod_shift = f.mod_scale + d;
     f.mod_ld = c->n_mod;
-    if (!c->dbg && ada_by_class(c, M, pre != nullptr)) f.mod_row = c->mod_cls;
+    if (by_class) f.mod_row = c->mod_cls;
   }
-  UAD_CHECK_CLS(K_FINAL, launch_final(f, s, ea_, eb_));
+  UAD_CHECK_CLS(K_FINAL, launch_final(f, by_class, s, ea_, eb_));
 #undef UAD_CHECK_CLS
   return UAD_OK;
 }

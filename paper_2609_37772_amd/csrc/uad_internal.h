@@ -199,9 +199,20 @@ struct GemmArgs {
   __bf16 *vtc;  // layer V^T store, 32-key blocks (vt_index)
   int chunk, prefix, s_alloc, n_kv_heads, head_dim, q_dim;
   unsigned *status;  // context status word (range bit of the fp16 operand stores)
-  // compacted steps: environment j of this step is environment env_map[j] of
-  // the caller's batch (its K/V store slot); null when every environment runs
-  const int32_t *env_map;
+  // One index per kind of epilogue (8 bytes more of arguments cost the batch-1
+  // step 0.2%):
+  union {
+    // EPI_QKV, compacted steps: environment j of this step is environment
+    // env_map[j] of the caller's batch (its K/V store slot); null when every
+    // environment runs
+    const int32_t *env_map;
+    // EPI_RESID_F32, batched adaptive norm: token row r's modulations are row
+    // mod_row[r] of the modulation matrix (null: row r)
+    const int32_t *mod_row;
+    // EPI_BIAS_SILU, EPI_MOD: only the first *m_dev rows of the launch exist
+    // (null: all M); workgroups past them return at once
+    const int32_t *m_dev;
+  };
   // Split-K of the batched residual projections when their tiles leave most
   // CUs idle (null workspace: never).  kx_ws holds the fp32 partial tiles
   // (kx_ws_bytes), kx_cnt one arrival counter per output tile, zero between
@@ -212,11 +223,6 @@ struct GemmArgs {
   size_t kx_ws_bytes;
   int kx_tiles;  // counters available
   int kx;
-  // batched adaptive norm: token row r's modulations are row mod_row[r] of the
-  // modulation matrix (null: row r), and only the first *m_dev rows of the
-  // launch exist (null: all M); workgroups past them return at once
-  const int32_t *mod_row;
-  const int *m_dev;
 };
 
 // Up to two byte ranges (weights of the next projections) that otherwise idle
@@ -275,9 +281,13 @@ struct FinalArgs {
   float *vsum;          // [M][Da] or null
   int vsum_tokens, chunk;
   // compacted steps: token m of the step (h row m) is token
-  // env_map[m / chunk] * chunk + m % chunk of x, t, dt, masks and outputs
-  const int32_t *env_map;
-  const int32_t *mod_row;  // token row's row of mod_scale / mod_shift (null: its own)
+  // env_map[m / chunk] * chunk + m % chunk of x, t, dt, masks and outputs.
+  // Adaptive norms by class (mapped): the token row's row of mod_scale / mod_shift
+  // instead; such steps are not compacted.
+  union {
+    const int32_t *env_map;
+    const int32_t *mod_row;
+  };
 };
 
 // Urgency-aware release with Trajectory Reconciliation and Ghost Action
@@ -355,7 +365,9 @@ hipError_t launch_class_features(const float *cls_t, const int *n_cls, int M, in
 hipError_t launch_ada_norm(const float *h, int M, int d, float eps, const float *scale, const float *shift, int mod_ld,
                            const int32_t *mod_row, op_t *next, unsigned *status, hipStream_t s,
                            hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
-hipError_t launch_final(const FinalArgs &f, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// mapped: f.mod_row is in use
+hipError_t launch_final(const FinalArgs &f, bool mapped, hipStream_t s, hipEvent_t ev0 = nullptr,
+                        hipEvent_t ev1 = nullptr);
 hipError_t launch_stamp(uint64_t *dst, hipStream_t s);
 hipError_t launch_prefix_pack(const PrefixArgs &a, int head_dim, bool f32, hipStream_t s);
 hipError_t launch_tr_init(const TrArgs &a, hipStream_t s);     // x0 <- x, vsum <- 0
