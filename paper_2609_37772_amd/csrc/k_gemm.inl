@@ -66,7 +66,8 @@ __device__ __forceinline__ void epilogue_elem(const GemmArgs &g, int row, bool r
         const int part = r6 / g.d_model, j = r6 - part * g.d_model;
         const int KBd = g.d_model / kTileK;
         if (g.mod_shift_ops && (part == 1 || part == 4))
-          store_op(g.mod_shift_ops + (size_t)(2 * l + (part == 4)) * g.shift_stride + afrag_index(row, j, KBd), mv, bad);
+          store_op(g.mod_shift_ops + (size_t)(2 * l + (part == 4)) * g.m_alloc * g.d_model + afrag_index(row, j, KBd),
+                   mv, bad);
         else if (part == 0 && l == 0 && g.next)
           store_op(g.next + afrag_index(row, j, KBd), g.h_in[(size_t)row * g.d_model + j] * (1.0f + mv), bad);
       }
@@ -628,8 +629,8 @@ __device__ __forceinline__ void big_epilogue(const GemmArgs &g, f32x4 (&acc)[TA]
           const int r6 = col - l * per_layer;
           const int part = r6 / g.d_model, jc = r6 - part * g.d_model;
           if (g.mod_shift_ops && (part == 1 || part == 4))
-            st4h(g.mod_shift_ops + (size_t)(2 * l + (part == 4)) * g.shift_stride + afrag_index(row, jc, KBd), mv,
-                 bad);
+            st4h(g.mod_shift_ops + (size_t)(2 * l + (part == 4)) * g.m_alloc * g.d_model + afrag_index(row, jc, KBd),
+                 mv, bad);
         }
       }
     }
@@ -1238,7 +1239,8 @@ static hipError_t launch_big(const GemmArgs &g, hipStream_t s, hipEvent_t ev0, h
 // the projection shapes of the 1024- and 1536-wide experts (the rule picks
 // the faster kernel in 49 of 50 cases, the miss by 6%).
 static bool big_ok(int epi, const GemmArgs &g) {
-  if (epi == EPI_QKV || epi == EPI_GEGLU || g.M < kBigM || g.N % 128 != 0 || g.mod_scale_next) return false;
+  if (epi == EPI_QKV || epi == EPI_GEGLU || g.M < kBigM || g.N % 128 != 0) return false;
+  if (epi == EPI_RESID_F32 && g.mod_scale_next) return false;
   const int tiles = tiles_of(g, 128, 128);
   return tiles >= 90 && !(tiles < 128 && g.K > 4096);
 }
@@ -1348,7 +1350,8 @@ hipError_t launch_gemm(int epi, const GemmArgs &g, const GemmPlan &p, hipStream_
                        hipEvent_t ev1) {
   if (g.m_alloc < g.M || g.m_alloc % 16 != 0) return hipErrorInvalidValue;  // operand rows allocated
   // the batched kernels gate by modulation row and leave the next norm to its own pass
-  if (g.M >= kBigM && g.mod_gate && (!g.mod_row || g.mod_scale_next)) return hipErrorInvalidValue;
+  if (epi == EPI_RESID_F32 && g.M >= kBigM && g.mod_gate && (!g.mod_row || g.mod_scale_next))
+    return hipErrorInvalidValue;
   if (epi == EPI_GEGLU)
     if (const int tile = ring_tile_geglu(g)) return launch_ring_geglu(g, tile, s, ev0, ev1);
   if (epi == EPI_QKV)

@@ -808,6 +808,9 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
     // RMSNorm folding: residual GEMMs write ssq and the next operand; consumers scale by rstd
     auto norm_fields = [&](GemmArgs &x) {
       x.ssq = c->ssq; x.ssq_tiles = ssq_tiles; x.m_alloc = (int)MA; x.eps = c->cfg.rms_eps;
+    };
+    auto resid_fields = [&](GemmArgs &x) {
+      norm_fields(x);
       x.kx_ws = c->kx_ws; x.kx_cnt = c->kx_cnt; x.kx_ws_bytes = c->kx_ws_bytes; x.kx_tiles = c->n_cu;
     };
     const int n_mod = c->n_mod;
@@ -824,7 +827,7 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
       GemmArgs g2{};
       g2.status = c->status;
       g2.M = M; g2.A = c->a_z; g2.W = c->t2_w; g2.N = d; g2.K = d;
-      g2.out = c->h; g2.ldo = d; g2.bias = c->t2_b; norm_fields(g2);
+      g2.out = c->h; g2.ldo = d; g2.bias = c->t2_b; resid_fields(g2);
       g2.gain_next = c->layers[0].attn_norm; g2.next = c->a_n;
       UAD_CHECK_CLS(K_GEMM_TIME_OUT, launch_gemm(EPI_RESID_F32, g2, plan_gemm(EPI_RESID_F32, M, d, d), s, ea_, eb_));
       ssq_tiles = resid_ssq_tiles(g2);
@@ -871,7 +874,7 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
       GemmArgs gm{};
       gm.status = c->status;
       gm.M = M; gm.m_alloc = (int)MA; gm.A = c->a_te; gm.W = c->w_mod; gm.N = n_mod; gm.K = d; gm.out = c->mod; gm.ldo = n_mod;
-      gm.bias = c->b_mod; gm.mod_shift_ops = c->mod_shift_ops; gm.shift_stride = MA * d; gm.h_in = c->h;
+      gm.bias = c->b_mod; gm.mod_shift_ops = c->mod_shift_ops; gm.h_in = c->h;
       gm.d_model = d; gm.n_layers = c->L; gm.next = c->a_n;
       UAD_CHECK_CLS(K_GEMM_MOD, launch_gemm(EPI_MOD, gm, plan_gemm(EPI_MOD, M, n_mod, d), s, ea_, eb_));
     }
@@ -951,7 +954,7 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
       GemmArgs o{};
       o.status = c->status;
       o.M = M; o.A = c->a_o; o.W = lp.wo; o.N = d; o.K = c->q_dim;
-      o.out = c->h; o.ldo = d; norm_fields(o);
+      o.out = c->h; o.ldo = d; resid_fields(o);
       o.gain_next = lp.mlp_norm; o.next = c->a_n;
       if (c->ada) {
         const float *ml = mod_base + (size_t)l * 6 * d;
@@ -976,7 +979,7 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
       GemmArgs dn{};
       dn.status = c->status;
       dn.M = M; dn.A = c->a_g; dn.W = lp.wdown; dn.N = d; dn.K = F;
-      dn.out = c->h; dn.ldo = d; norm_fields(dn);
+      dn.out = c->h; dn.ldo = d; resid_fields(dn);
       dn.gain_next = (l + 1 < c->L) ? c->layers[l + 1].attn_norm : nullptr; dn.next = c->a_n;
       if (c->ada) {
         const float *ml = mod_base + (size_t)l * 6 * d;
@@ -1082,7 +1085,7 @@ static uad_status enqueue_ada_schedule(uad_ctx *c, hipStream_t s, const GraphKey
   GemmArgs gm{};
   gm.status = c->status;
   gm.M = rows; gm.m_alloc = rows; gm.A = c->pre_te; gm.W = c->w_mod; gm.N = c->n_mod; gm.K = d; gm.out = c->pre_mod;
-  gm.ldo = c->n_mod; gm.bias = c->b_mod; gm.mod_shift_ops = c->pre_shift; gm.shift_stride = (size_t)rows * d;
+  gm.ldo = c->n_mod; gm.bias = c->b_mod; gm.mod_shift_ops = c->pre_shift;
   gm.h_in = nullptr; gm.next = nullptr; gm.d_model = d; gm.n_layers = c->L;
   UAD_PRE_CLS(K_GEMM_MOD, launch_gemm(EPI_MOD, gm, plan_gemm(EPI_MOD, rows, c->n_mod, d), s, ea_, eb_));
 #undef UAD_PRE_CLS

@@ -165,6 +165,8 @@ struct GemmPlan {
   bool ok;
 };
 
+// The arguments travel with every launch and a kernel starts by fetching them, so
+// the block is kept short: what only one kind of epilogue uses shares its bytes.
 struct GemmArgs {
   const op_t *A;    // activations, fragment order [rows/16][K/32][64][8]
   // RMSNorm folded into the GEMMs: a residual GEMM writes ssq[tile][row] (sums of
@@ -175,32 +177,46 @@ struct GemmArgs {
   int ssq_tiles;
   int m_alloc;            // rows allocated in every operand / output buffer (>= M, multiple of 16)
   float eps;
-  const float *gain_next; // EPI_RESID_F32: gain of the following RMSNorm (nullptr: none)
-  op_t *next;             // EPI_RESID_F32: next operand, fragment order (K = N)
   int use_rstd;           // EPI_QKV / EPI_GEGLU: scale by rstd from ssq
+  const float *gain_next; // EPI_RESID_F32: gain of the following RMSNorm (nullptr: none)
+  op_t *next;             // EPI_RESID_F32, EPI_MOD: next operand, fragment order
   // adaptive-norm conditioning
   const op_t *A2;         // EPI_QKV / EPI_GEGLU: second operand (the norm's shift), result rstd*(A W) + A2 W
-  const float *mod_gate;  // EPI_RESID_F32: h += gate[row * mod_ld + col] * acc (nullptr: gate 1)
-  const float *mod_scale_next;  // EPI_RESID_F32: next operand fp16(h * (1 + scale[row * mod_ld + col]))
-  int mod_ld;
-  // EPI_MOD destinations: fp32 [M][N] row-major (out), the shifts as fp16
-  // operands, and the first attention norm's operand fp16(h * (1 + scale))
-  op_t *mod_shift_ops;    // [L][2][m_alloc*d] fragment order (nullptr: not kept)
-  const float *h_in;      // [M][d] residual stream
-  int d_model, n_layers;
-  size_t shift_stride;    // elements per shift operand
   const op_t *W;    // packed weights, N/16 tiles x K/32 blocks
   int M, N, K;      // N counts packed output columns (2F for gate/up)
+  int ldo;          // row length of out (= K of the consuming GEMM for fragment-order outputs)
   void *out;        // epilogue destination
-  int ldo;          // its row length (= K of the consuming GEMM for fragment-order outputs)
   const float *bias;
-  // EPI_QKV destinations
-  __bf16 *kc;   // layer K store [B][Hkv][S_alloc][hd]
-  __bf16 *vtc;  // layer V^T store, 32-key blocks (vt_index)
-  int chunk, prefix, s_alloc, n_kv_heads, head_dim, q_dim;
   unsigned *status;  // context status word (range bit of the fp16 operand stores)
-  // One index per kind of epilogue (8 bytes more of arguments cost the batch-1
-  // step 0.2%):
+  union {  // the longest first: GemmArgs{} clears it
+    struct {  // EPI_RESID_F32
+      const float *mod_gate;        // h += gate[row * mod_ld + col] * acc (nullptr: gate 1)
+      const float *mod_scale_next;  // next operand fp16(h * (1 + scale[row * mod_ld + col]))
+      // Split-K of the batched residual projections when their tiles leave most
+      // CUs idle (null workspace: never).  kx_ws holds the fp32 partial tiles
+      // (kx_ws_bytes), kx_cnt one arrival counter per output tile, zero between
+      // launches (the last workgroup of a tile to arrive resets it); kx is the
+      // split count of the launch, set by the launcher.
+      float *kx_ws;
+      unsigned *kx_cnt;
+      size_t kx_ws_bytes;
+      int kx_tiles;  // counters available
+      int kx;
+      int mod_ld;
+    };
+    struct {  // EPI_QKV
+      __bf16 *kc;   // layer K store [B][Hkv][S_alloc][hd]
+      __bf16 *vtc;  // layer V^T store, 32-key blocks (vt_index)
+      int chunk, prefix, s_alloc, n_kv_heads, head_dim, q_dim;
+    };
+    struct {  // EPI_MOD: fp32 [M][N] row-major (out), the shifts as fp16 operands, and
+              // the first attention norm's operand fp16(h * (1 + scale))
+      op_t *mod_shift_ops;    // [L][2][m_alloc*d] fragment order (nullptr: not kept)
+      const float *h_in;      // [M][d] residual stream
+      int d_model, n_layers;
+    };
+  };
+  // One index per kind of epilogue:
   union {
     // EPI_QKV, compacted steps: environment j of this step is environment
     // env_map[j] of the caller's batch (its K/V store slot); null when every
@@ -213,16 +229,6 @@ struct GemmArgs {
     // (null: all M); workgroups past them return at once
     const int32_t *m_dev;
   };
-  // Split-K of the batched residual projections when their tiles leave most
-  // CUs idle (null workspace: never).  kx_ws holds the fp32 partial tiles
-  // (kx_ws_bytes), kx_cnt one arrival counter per output tile, zero between
-  // launches (the last workgroup of a tile to arrive resets it); kx is the
-  // split count of the launch, set by the launcher.
-  float *kx_ws;
-  unsigned *kx_cnt;
-  size_t kx_ws_bytes;
-  int kx_tiles;  // counters available
-  int kx;
 };
 
 // Up to two byte ranges (weights of the next projections) that otherwise idle
