@@ -6,10 +6,11 @@
 // * H + token), so one K/V tile read serves all of them.
 //
 // Per workgroup: one (environment, KV head), 64 packed query rows (4 waves x
-// 16), and a contiguous range of 32-key blocks (split-KV when the batch is
+// 16; long splits on few workgroups: two key groups of such waves; many
+// environments: up to 128 rows), and a contiguous range of 32-key blocks (split-KV when the batch is
 // small).  Keys are processed in chunks of NB blocks: a chunk's K and V^T
 // tiles go straight from global memory into LDS (LDS-direct loads, shared by
-// the 4 waves, double buffered), all issued at once, and the next chunk's
+// its waves, double buffered), all issued at once, and the next chunk's
 // loads are in flight while a chunk is used, so a split of at most NB blocks
 // costs one memory round trip.
 // Each wave computes S^T = K Q^T with v_mfma_f32_16x16x32_bf16 so that a

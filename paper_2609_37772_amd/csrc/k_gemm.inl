@@ -380,14 +380,15 @@ static hipError_t launch_t(const GemmArgs &g, const GemmPlan &p, hipStream_t s, 
 }
 
 // ---------------------------------------------------------------------------
-// Batched projections (M >= kBigM rows): a workgroup owns a 128-row x
+// Register-streamed kernel (time MLP in, modulations, and the residual
+// projections that no ring shape takes): a workgroup owns a 128-row x
 // 16*CT-column output tile over the full K; its 4 waves (2 x 2) each own
 // 64 rows x 8*CT columns (4 x CT/2 MFMA 16x16x32 tiles).  No LDS for the
 // operands: every wave streams its own fragment-order 1 KiB blocks straight
 // into registers, kBigPD k-blocks ahead of the MFMAs (one aligned 16-byte
 // load per lane and block; the two waves sharing a row or column panel find
-// it in L2).  Measured on 2048..3200-row projections this runs at 590-940
-// TFLOP/s, against ~150 for the same tiles staged through a double-buffered
+// it in L2).  On 2048..3200-row projections this runs at 590-940 TFLOP/s without
+// epilogue, against ~150 for the same tiles staged through a double-buffered
 // LDS ring: there every 32-deep k-step waited out a full memory round trip,
 // and __syncthreads' release fence drains all loads in flight, so deeper
 // rings need a raw barrier.  Tiles are dealt to the 8 XCDs in contiguous
@@ -746,14 +747,18 @@ __global__ __launch_bounds__(256 * KS) void gemm_big_kernel(GemmArgs g) {
   flush_range(g.status, bad);
 }
 
-// LDS-ring kernels for the widest batched projections: RT x CT 16-row /
+// LDS-ring kernels of the batched projections: RT x CT 16-row /
 // 16-column tiles per workgroup, 8 waves (WR x WC), operands staged through
 // an NS-stage LDS ring by LDS-direct loads (RT + CT fragment blocks per
 // 32-deep stage).  Each stage's wait is a raw s_barrier after a partial
 // vmcnt: __syncthreads' release fence would drain the next stages' loads
-// too.  The rows' norm statistics are loaded into registers after the ring
-// prologue (that wait is the prologue's own round trip) and folded into
-// rstd after the main loop.  Measured without epilogue (TFLOP/s):
+// too.  The rows' norm statistics are loaded into registers ahead of the ring
+// prologue and folded into rstd after the main loop.  What bounds them (gate/up
+// at 3200 rows, 59 us): the LDS-direct fills alone take 34-38 us (16-18 TB/s over
+// the chip, 30 bytes per clock and CU, about what L2 hits reach), the products
+// alone 41, the waits and barriers of the stages ~10 and the epilogue ~8; 256-row
+// tiles and register-pipelined fragments (fewer fills, fewer exposed reads) were
+// no faster.  Measured without epilogue (TFLOP/s):
 //   gate/up 256 x 128, 4 x 2 waves, 3 stages: 3200 x 8192 x 1024: 800 (vs
 //   711 register-streamed), 2048 x 12288 x 1536: 960 (vs 921); with the
 //   GeGLU epilogue, 128 x 256 tiles (2 x 4 waves, same LDS per stage) beat
@@ -1143,9 +1148,9 @@ static hipError_t launch_ring_ns(const GemmArgs &g, hipStream_t s, hipEvent_t ev
   return hipGetLastError();
 }
 
-// Gate/up with K <= 1024 on a 2-stage ring (48 KiB of LDS, three workgroups
-// per CU): same-machine A/B at 3200 x 8192 x 1024 68.6 -> 65.9 us; at K = 1536
-// (2048 x 12288) the 2-stage ring lost 84.2 -> 92.6 us, so 3 stages there.
+// Gate/up on 256-column tiles with K <= 1024: a 2-stage ring (48 KiB of LDS):
+// same-machine at 3200 x 8192 x 1024 58.7 us against 61.5 with 3 stages; at
+// K = 1536 (2048 x 12288) 2 stages lost 84.2 -> 92.6 us, so 3 there.
 // Gate/up on the shortest of 128-, 144- and 160-row tiles that fits one round
 // of co-resident ring workgroups (two per CU), 128 when none does: the tiles
 // past the round ran as a second, mostly single-workgroup wave.  Same-machine,
@@ -1194,12 +1199,10 @@ constexpr size_t big_xch_bytes() { return (size_t)4 * 2 * (kBigRowTiles / 4) * (
 
 // Whether a launch takes the k-halves (KS = 2): its tiles fill at most one
 // round of CUs (one 4-wave workgroup per CU would leave every SIMD a single
-// wave), K >= 1536 and the k-blocks split evenly.  Residual, QKV and
-// time-MLP-in epilogues only (128- or 96-column tiles, <= 256 registers at 8
-// waves).  Measured: the 1536-wide expert's QKV (2048 x 2048 x 1536, 256
-// tiles) 32.5 -> 25.5 us, its down 67.7 -> 65.2 us; the 1024-wide fleet's O
-// and down -2%; at K = 1024 (fleet time-MLP out) 18.8 -> 19.6 us, hence the
-// K bound.
+// wave), K >= 1536 and the k-blocks split evenly.  Not for the modulations.
+// Measured: down of the 1536-wide expert (2048 rows) 67.7 -> 65.2 us, O and down
+// of the 1024-wide at 3200 rows -2%; at K = 1024 (time-MLP out) 18.8 -> 19.6 us,
+// hence the K bound.
 template <int EPI, int CT>
 static bool big_khalves(const GemmArgs &g) {
   if constexpr (EPI == EPI_MOD) {

@@ -55,8 +55,9 @@ constexpr int kMaxTrSteps = 64;  // longest canonical schedule N* of the release
 constexpr size_t kKxPartialFloats = 128 * 128;
 constexpr int kTileN = 16;
 constexpr int kTileK = 32;
-// token rows from which the projections run on the batched (128-row tile)
-// kernels rather than the small-M weight-streaming one
+// token rows from which the register-streamed 128-row kernels, the split of the
+// large residual tiles and the adaptive norms by class apply (the ring's smaller
+// tiles go by tile count)
 constexpr int kBigM = 256;
 constexpr int kBlockElems = kTileN * kTileK;  // 512 fp16 = 1 KiB
 
