@@ -43,13 +43,6 @@ struct AttnBlock {
 // skip rescaling the accumulators; probabilities stay <= 2^8.
 constexpr float kRescaleThreshold = 8.0f;
 
-// Blocks per chunk (one memory round trip); two chunks are resident (double
-// buffer), 2 * NB * 32 * HD * 4 bytes of LDS.
-template <int HD>
-constexpr int attn_chunk_blocks() {
-  return HD == 256 ? 2 : 4;
-}
-
 // Blocks per stage of the tall batched workgroups (6-8 waves): the waves
 // meet once per stage.  Same-machine A/B per launch: HD = 128 (2048 tokens x 1152
 // keys) 33.2 -> 32.4 us with 2 blocks (4 blocks: 33.2); HD = 256 (3200 tokens x
@@ -446,26 +439,9 @@ static int g_attn_cus = 256;  // compute units of the device (set by attention_i
 // waves per workgroup of the split merge (see launch_hd)
 static int merge_waves(int splits) { return splits > 8 ? 4 : 1; }
 
-static bool attn_streamed(const AttnArgs &a, int nb) {
-  const int groups = a.n_eh * a.splits;
-  return a.blocks_per_split > 2 * nb ||
-         (a.blocks_per_split > nb && 4 * 8 * ((groups + 7) / 8) * a.qblocks > 3 * g_attn_cus);
-}
-// Long splits whose 4-wave workgroups would each have a CU to themselves (one
-// wave per SIMD walking the split's blocks, ~1.3 us a block at HD = 256, most of
-// it the latency of its read -> MFMA -> softmax chain): 8 waves instead, two key
-// groups of four.  The two waves of a SIMD hide each other's chains until the
-// LDS reads of their fragments bound them.  Same-machine, attention us per
-// layer: 1024-wide expert at 32 / 24 environments 36.5 / 36.3 -> 28.0 / 27.0,
-// 8 (with its merge) 27.8 -> 24.6; 1536-wide at 8 / 5 28.7 / 28.0 -> 21.4 /
-// 20.5.  Beyond one workgroup per CU two 4-wave ones share a CU already.
-static bool attn_two_groups(const AttnArgs &a, int nb) {
-  return attn_streamed(a, nb) && a.n_eh * a.splits * a.qblocks <= g_attn_cus;
-}
-
 template <int HD>
 static hipError_t launch_hd(const AttnArgs &a, int batch, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-  constexpr int NB = attn_chunk_blocks<HD>();
+  constexpr int NB = attn_chunk_blocks(HD);
   if (a.qblocks != (a.rows + 63) / 64 || a.n_eh != batch * a.n_kv_heads) return hipErrorInvalidValue;
   const int groups = a.n_eh * a.splits;
   if (a.pre_attn.wgs < 0 || a.pre_comb.wgs < 0 || ((a.pre_attn.wgs || a.pre_comb.wgs) && !a.pf_sink))
@@ -477,7 +453,7 @@ static hipError_t launch_hd(const AttnArgs &a, int batch, hipStream_t s, hipEven
   // LDS reads and softmax; short splits (batch 1): NB blocks per stage, one
   // memory round trip per split.  Splits of two chunks count as long when the
   // grid takes most of the CUs (two key groups: see below).
-  const bool streamed = attn_streamed(a, NB);
+  const bool streamed = attn_streamed(g_attn_cus, groups, a.qblocks, a.blocks_per_split, NB);
   const uint32_t lds = (uint32_t)(2 * (streamed ? 1 : NB) * sizeof(AttnBlock<HD>));
   if (streamed && a.splits == 1 && a.pre_attn.wgs == 0) {
     // Without split-KV every workgroup of a group re-reads the group's whole
@@ -510,7 +486,7 @@ static hipError_t launch_hd(const AttnArgs &a, int batch, hipStream_t s, hipEven
       return hipGetLastError();
     }
   }
-  if (attn_two_groups(a, NB)) {
+  if (attn_two_groups(g_attn_cus, groups, a.qblocks, a.blocks_per_split, NB)) {
     constexpr uint32_t lds_kg = (uint32_t)(4 * sizeof(AttnBlock<HD>));
     UAD_LAUNCH((attn_kernel<HD, 1, true, 8, 2>), grid, dim3(512), lds_kg, s, ev0, end_attn, a);
   } else if (streamed)
@@ -535,7 +511,7 @@ static hipError_t launch_hd(const AttnArgs &a, int batch, hipStream_t s, hipEven
     UAD_LAUNCH((attn_combine_kernel<8, 1>), cgrid, dim3(64), 0, s, none, ev1, ac, HD);
   else if (a.splits <= 16)
     UAD_LAUNCH((attn_combine_kernel<16, 4>), cgrid, dim3(256), 0, s, none, ev1, ac, HD);
-  else if (a.splits <= 32)
+  else if (a.splits <= kAttnMaxSplits)
     UAD_LAUNCH((attn_combine_kernel<32, 4>), cgrid, dim3(256), 0, s, none, ev1, ac, HD);
   else
     return hipErrorInvalidValue;
@@ -544,7 +520,7 @@ static hipError_t launch_hd(const AttnArgs &a, int batch, hipStream_t s, hipEven
 
 template <int HD>
 static hipError_t init_hd() {
-  constexpr int NB = attn_chunk_blocks<HD>();
+  constexpr int NB = attn_chunk_blocks(HD);
   constexpr int streamed_lds = (int)(2 * sizeof(AttnBlock<HD>));
   hipError_t e = hipFuncSetAttribute((const void *)attn_kernel<HD, NB, false, 4, 1>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)(2 * NB * sizeof(AttnBlock<HD>)));
@@ -580,8 +556,6 @@ hipError_t attention_init() {
   return e;
 }
 
-int attention_max_splits(int) { return 32; }
-
 // Below kBigM rows the launches that carry the read-ahead are short, so it stops
 // at about what its workgroups read meanwhile (~2.5 TB/s in all, 40 GB/s for one
 // workgroup, 0.07 GB/s a lane of the one-wave merge workgroups); past that the
@@ -592,23 +566,14 @@ int attention_max_splits(int) { return 32; }
 // than the attention loses (1536-wide, 3 environments: gate/up 40.7 -> 31.0 us,
 // attention 23.3 -> 25.5), so no cap there.
 void attention_read_ahead_caps(const AttnArgs &a, int head_dim, int wgs, size_t *attn, size_t *merge) {
-  const int nb = attention_chunk_blocks(head_dim);
-  const bool two = attn_two_groups(a, nb);
+  const int nb = attn_chunk_blocks(head_dim);
+  const bool two = attn_two_groups(g_attn_cus, a.n_eh * a.splits, a.qblocks, a.blocks_per_split, nb);
   const int serial = two ? (a.blocks_per_split + 1) / 2 : a.blocks_per_split;
   const size_t extra = (size_t)std::max(0, serial - nb), KB = 1024;
   const size_t all = (22528 + 2560 * extra) * KB, per_wg = (288 + 56 * extra) * KB;
   const size_t lanes = (size_t)(a.rows_pad / 16) * (head_dim / 16) * 64;
   *attn = std::min(*attn, std::min(all, per_wg * (size_t)wgs));
   *merge = std::min(*merge, lanes * 480);
-}
-
-int attention_chunk_blocks(int head_dim) {
-  switch (head_dim) {
-    case 64: return attn_chunk_blocks<64>();
-    case 128: return attn_chunk_blocks<128>();
-    case 256: return attn_chunk_blocks<256>();
-  }
-  return 1;
 }
 
 hipError_t launch_attention(const AttnArgs &a, int batch, int head_dim, hipStream_t s, hipEvent_t ev0,

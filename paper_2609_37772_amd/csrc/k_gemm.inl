@@ -790,7 +790,7 @@ struct RingShape<EPI_QKV> {
 };
 template <>
 struct RingShape<EPI_RESID_F32> {
-  static constexpr int RT = 8, CT = 8, WR = 2, WC = 4, NS = 4, MinM = 2560;
+  static constexpr int RT = 8, CT = 8, WR = 2, WC = 4, NS = 4;
 };
 
 // 144 x 256 gate/up tiles, 1 x 8 waves of 144 x 32 (one gate/up pair each):
@@ -818,7 +818,7 @@ struct Ring128x128 {
 
 // 128 x 96 tiles: the residual projections where 96-column tiles are preferred
 struct RingResid96 {
-  static constexpr int RT = 8, CT = 6, WR = 4, WC = 2, NS = 4, MinM = 1024;
+  static constexpr int RT = 8, CT = 6, WR = 4, WC = 2, NS = 4;
 };
 
 // Wait until this wave's loads of all but the newest `later` stages (L
@@ -1011,135 +1011,6 @@ __global__ __launch_bounds__(512) void gemm_ring_kernel(GemmArgs g) {
 }
 
 
-// Residual projections: 96-column tiles of the register-streamed kernel when
-// they need fewer 16 x 16 output tiles per CU than 128-column ones (1536
-// wide, 2048 rows: 256 tiles of 48 instead of 192 tiles of 64 with 64 CUs
-// idle).
-static bool resid_prefers_96(const GemmArgs &g) {
-  auto per_cu = [&](int ct) {
-    const int tiles = (g.M + 16 * kBigRowTiles - 1) / (16 * kBigRowTiles) * (g.N / (16 * ct));
-    return (tiles + g_n_cu - 1) / g_n_cu * ct;
-  };
-  return g.N % 96 == 0 && per_cu(6) < per_cu(8);
-}
-
-// Output tiles of rows x cols.
-static int tiles_of(const GemmArgs &g, int rows, int cols) { return (g.M + rows - 1) / rows * (g.N / cols); }
-
-// Residual projections on 128 x 128 ring tiles: from 2560 rows, below that once
-// the tiles fill half the CUs (the register-streamed kernel's k-halves win with
-// fewer: 80-104 tiles).
-static bool ring_resid_fits(const GemmArgs &g) {
-  using S = RingShape<EPI_RESID_F32>;
-  return (g.M >= S::MinM || 2 * tiles_of(g, 128, 128) >= g_n_cu) && g.N % 128 == 0 && g.A2 == nullptr &&
-         !resid_prefers_96(g);
-}
-
-// Tile of the QKV and gate/up projections on the ring, rows * 1000 + columns, or
-// 0 for the small-M kernel.  A tile walks all of K in one workgroup, so at a few
-// hundred rows 128-row tiles leave most CUs idle and the rest waiting on their
-// own load latency; smaller tiles re-read more of the operands for the same
-// products.  Same-machine, us per launch by tile (tiles in brackets; "small" is
-// the small-M kernel, "before" what the launch took until then):
-//   QKV 1024 -> 2560      64 x 64       64 x 128    128 x 128   small / before
-//     200 rows             8.5 (160)    11.6 (80)    14.2 (40)    8.8 /  9.9
-//     400                  9.9 (280)    12.0 (140)   14.8 (80)   13.0 / 14.9
-//     800                 13.0 (520)    14.6 (260)   15.1 (140)       / 18.3
-//     1600                19.0 (1000)   17.8 (500)   20.2 (260)       / 20.2
-//     2000                24.4 (1280)   23.6 (640)   22.9 (320)       / 22.9
-//   QKV 1536 -> 2048: 384 rows 11.0 (192) 15.5 18.8, before 15.6; 1024 rows 15.2
-//     (512) 16.7 19.0, before 23.0; 2048 rows 25.8 (1024) 23.0 21.2, before 23.9
-//   gate/up 1024 -> 8192  64 x 128      128 x 128   128 x 256   small / before
-//     111 rows            10.9 (128)    12.1 (64)    18.7 (32)    9.8 / 11.4
-//     200                 11.8 (256)    12.6 (128)   19.1 (64)   16.8 / 19.5
-//     400                 13.9 (448)    13.3 (256)   19.4 (128)       / 21.9
-//     800                 25.3 (832)    19.0 (448)   20.5 (224)       / 22.8
-//     1050                29.2 (1088)   28.8 (576)   27.3 (288)       / 30.0
-//   gate/up 1536 -> 12288: 128 rows 15.7 (192) 17.3 26.7, before 26.3; 640 rows
-//     36.4 (960) 27.8 (480) 28.9 (240), before 31.4
-static int ring_tile_qkv(const GemmArgs &g) {
-  if (g.A2 || g.M <= 64 || g.N % 64 != 0 || g.q_dim % 16 != 0) return 0;
-  const int t64 = tiles_of(g, 64, 64);
-  if (16 * t64 < 9 * g_n_cu) return 0;
-  if (4 * t64 <= 11 * g_n_cu || g.N % 128 != 0) return 64064;
-  // just past one round of 128 x 128 tiles, and smaller ones fit two a CU
-  if (tiles_of(g, 128, 128) > g_n_cu && tiles_of(g, 64, 128) <= 2 * g_n_cu) return 64128;
-  return 128128;
-}
-
-static int ring_tile_geglu(const GemmArgs &g) {
-  if (g.A2 || g.M <= 64 || g.N % 128 != 0) return 0;
-  const int t = tiles_of(g, 64, 128);
-  if (16 * t < 9 * g_n_cu) return 0;
-  if (t <= g_n_cu) return 64128;
-  return tiles_of(g, 128, 128) <= 2 * g_n_cu || g.N % 256 != 0 ? 128128 : 128256;
-}
-
-// The residual projections where 96-column tiles are preferred, on the
-// 128 x 96 ring from 1024 rows once its tiles fill 3/4 of the CUs, or with
-// a long K.  1536-wide expert, same-machine (us): at 2048 and 1536 rows O 22.4 /
-// 21.8 -> 21.8 / 21.1, down 65.2 / 64.8 -> 63.7 / 62.4; at 1024 rows (128
-// tiles) down (K = 6144) 60.1 -> 58.1 but O (K = 1536) 18.0 -> 19.6, where
-// the register-streamed kernel's k-halves keep the short K ahead.
-static bool ring96_fits(const GemmArgs &g) {
-  const int tiles = (g.M + 16 * RingResid96::RT - 1) / (16 * RingResid96::RT) * (g.N / (16 * RingResid96::CT));
-  return g.M >= RingResid96::MinM && (4 * tiles >= 3 * g_n_cu || g.K >= 4096) && resid_prefers_96(g) &&
-         g.A2 == nullptr && g.K / kTileK >= 1;
-}
-
-// The residual projections on 64 x 64 ring tiles (kx: split over K), 0 when they
-// don't take them.  Short K (O, time MLP): from 9/16 of the CUs in tiles to two
-// tiles a CU.  K >= 4096 (down): fewer tiles, split over K four ways up to 2/3 of
-// the CUs and two ways up to 27/32.  Same-machine, us per launch (tiles of 64 x 64):
-//   O 2048 -> 1024     800 rows (208) 16.0 -> 13.4, 1050 (272) 19.1 -> 15.2, 1600
-//     (400) 20.2 -> 16.5, 2000 (512) 21.6 -> 20.4, 2400 (608) 25.5 -> 25.5; 400
-//     rows (112) 9.5 -> 12.9, hence the bounds
-//   O 1536 -> 1536     384 (144) 13.7 -> 11.1, 640 (240) 18.3 -> 11.4, 1024 (384)
-//     17.0 -> 13.7, 2048 (768) 23.0 -> 23.4
-//   down 4096 -> 1024  by splits 1 / 2 / 4: 300 rows (80) 14.1 -> 22.0 / 15.7 / 13.1,
-//     400 (112) 15.0 -> 22.0 / 15.8 / 13.0, 600 (160) 20.4 -> 22.3 / 18.4 / 17.0, 800
-//     (208) 26.0 -> 22.7 / 18.4 / 20.6, 1050 (272) 23.3 -> 28.5
-//   down 6144 -> 1536  256 (96) 21.3 -> 31.1 / 20.8 / 15.9, 384 (144) 30.4 -> 31.4 /
-//     23.4 / 20.7, 640 (240) 27.5 -> 40.6 / 31.5; 128 (48) 14.8 -> - / 23.6 / 15.8
-static int resid_ring64(const GemmArgs &g) {
-  if (g.A2 || g.mod_scale_next || (g.mod_gate && !g.mod_row) || g.M <= 64 || g.N % 64 != 0) return 0;
-  const int t = tiles_of(g, 64, 64);
-  if (g.K < 4096) return 16 * t >= 9 * g_n_cu && t <= 2 * g_n_cu ? 1 : 0;
-  if (16 * t < 5 * g_n_cu || 32 * t > 27 * g_n_cu || !g.kx_ws || !g.kx_cnt || t > g.kx_tiles) return 0;
-  const int kx = 3 * t <= 2 * g_n_cu ? 4 : 2;
-  return (size_t)t * kx * 64 * 64 * sizeof(float) <= g.kx_ws_bytes ? kx : 0;
-}
-
-// Split-K of the batched residual projections on the ring: kx = CUs / tiles
-// (at most 4) copies of the tile grid, each over an equal k-range of at least
-// 16 k-blocks, when the tiles fill at most half the CUs and are at least the
-// 90 the batched kernels need (64 with K >= 4096); 1 (no split) otherwise, or
-// when the context gave no workspace or it is too small.  Same-machine A/B, ms
-// per joint step: 1024-wide expert at 32 environments (1600 rows, 104 tiles)
-// 3.130 -> 2.663 (down 49.8 -> 29.1 us, O 25.3 -> 20.4 us), 1536-wide expert
-// at 8 environments (1024 rows, 128 tiles of 96 columns) 4.450 -> 3.893
-// (down 58.0 -> 36.3 us); below 90 tiles the small-M kernel kept O and the
-// time MLP ahead (1000 rows: O 16.8 -> 18.0 us split four ways) while down
-// still won (28.1 -> 23.4 us), and at 400-600 rows both lost.  Tiles filling
-// more than half the CUs (one workgroup per CU) split two ways when K >= 4096,
-// two co-resident workgroups per CU instead of one: down of the 1536-wide
-// expert at 16 environments (256 tiles of 128 x 96) 65.5 -> 54.3 us, step
-// 5.595 -> 5.333 ms; of the 1024-wide at 64 environments (200 tiles) 45.3 ->
-// 43.4 us; with O and the time MLP (K = 1536-2048) split as well the step
-// lost (O 22.1 -> 24.3 us, 26.9 -> 30.3 us).
-template <class S>
-static int resid_ksplit(const GemmArgs &g) {
-  if (!g.kx_ws || !g.kx_cnt || g.A2 || g.M < kBigM || g.N % (16 * S::CT) != 0) return 1;
-  const int tiles = (g.M + 16 * S::RT - 1) / (16 * S::RT) * (g.N / (16 * S::CT));
-  if (tiles < 90 && !(g.K >= 4096 && tiles >= 64)) return 1;
-  int kx = std::min(4, g_n_cu / std::max(tiles, 1));
-  if (kx == 1 && tiles <= g_n_cu && g.K >= 4096) kx = 2;
-  while (kx > 1 && (g.K / kTileK) / kx < 16) --kx;
-  constexpr size_t part = (size_t)kRingNW * (S::RT / S::WR) * (S::CT / S::WC) * 4 * 64 * sizeof(float);
-  if (kx > 1 && ((size_t)tiles * kx * part > g.kx_ws_bytes || tiles > g.kx_tiles)) return 1;
-  return kx;
-}
-
 template <int EPI, int NS, class S = RingShape<EPI>, bool KSPLIT = false>
 static hipError_t launch_ring_ns(const GemmArgs &g, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   const int wgs = grid_tile_wgs(g.M, 16 * S::RT, g.N / (16 * S::CT)) * (KSPLIT ? g.kx : 1);
@@ -1151,29 +1022,12 @@ static hipError_t launch_ring_ns(const GemmArgs &g, hipStream_t s, hipEvent_t ev
 // Gate/up on 256-column tiles with K <= 1024: a 2-stage ring (48 KiB of LDS):
 // same-machine at 3200 x 8192 x 1024 58.7 us against 61.5 with 3 stages; at
 // K = 1536 (2048 x 12288) 2 stages lost 84.2 -> 92.6 us, so 3 there.
-// Gate/up on the shortest of 128-, 144- and 160-row tiles that fits one round
-// of co-resident ring workgroups (two per CU), 128 when none does: the tiles
-// past the round ran as a second, mostly single-workgroup wave.  Same-machine,
-// 144 rows: 2050 rows (544 -> 480 tiles) 57.1 -> 42.5 us, step 3.484 -> 3.210
-// ms; 2300 rows 56.5 -> 42.9 us; 1536-wide at 1408 rows (528 -> 480 tiles,
-// K = 1536) 75.8 -> 59.7 us, step 5.089 -> 4.666 ms.  160 rows: 2400 rows
-// 56.6 -> 44.6 us, step 3.416 -> 3.203 ms; 2500 rows 56.1 -> 45.4 us;
-// 1536-wide at 1536 rows 75.4 -> 61.8 us, step 5.017 -> 4.676 ms.  Where
-// every shape exceeds the round the taller tiles lost (3200 rows, 800 -> 736
-// tiles of 144: 67.0 -> 69.6 us).
-static int geglu_tile_rows(const GemmArgs &g) {
-  const int tn = g.N / 256;
-  for (int rows : {128, 144, 160})
-    if ((g.M + rows - 1) / rows * tn <= 2 * g_n_cu) return rows;
-  return 128;
-}
-
-static hipError_t launch_ring_geglu(const GemmArgs &g, int tile, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-  if (tile == 64128) return launch_ring_ns<EPI_GEGLU, Ring64x128::NS, Ring64x128>(g, s, ev0, ev1);
-  if (tile == 128128) return launch_ring_ns<EPI_GEGLU, Ring128x128::NS, Ring128x128>(g, s, ev0, ev1);
-  const int rows = geglu_tile_rows(g);
-  if (rows == 160) return launch_ring_ns<EPI_GEGLU, 2, RingGeGlu160>(g, s, ev0, ev1);
-  if (rows == 144) {
+static hipError_t launch_ring_geglu(const GemmArgs &g, const ProjRoute &r, hipStream_t s, hipEvent_t ev0,
+                                    hipEvent_t ev1) {
+  if (r.rows == 64) return launch_ring_ns<EPI_GEGLU, Ring64x128::NS, Ring64x128>(g, s, ev0, ev1);
+  if (r.cols == 128) return launch_ring_ns<EPI_GEGLU, Ring128x128::NS, Ring128x128>(g, s, ev0, ev1);
+  if (r.rows == 160) return launch_ring_ns<EPI_GEGLU, 2, RingGeGlu160>(g, s, ev0, ev1);
+  if (r.rows == 144) {
     if (g.K <= 1024) return launch_ring_ns<EPI_GEGLU, 2, RingGeGlu144>(g, s, ev0, ev1);
     return launch_ring_ns<EPI_GEGLU, RingGeGlu144::NS, RingGeGlu144>(g, s, ev0, ev1);
   }
@@ -1181,10 +1035,20 @@ static hipError_t launch_ring_geglu(const GemmArgs &g, int tile, hipStream_t s, 
   return launch_ring_ns<EPI_GEGLU, RingShape<EPI_GEGLU>::NS>(g, s, ev0, ev1);
 }
 
-static hipError_t launch_ring_qkv(const GemmArgs &g, int tile, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-  if (tile == 64064) return launch_ring_ns<EPI_QKV, Ring64x64::NS, Ring64x64>(g, s, ev0, ev1);
-  if (tile == 64128) return launch_ring_ns<EPI_QKV, Ring64x128::NS, Ring64x128>(g, s, ev0, ev1);
+static hipError_t launch_ring_qkv(const GemmArgs &g, const ProjRoute &r, hipStream_t s, hipEvent_t ev0,
+                                  hipEvent_t ev1) {
+  if (r.cols == 64) return launch_ring_ns<EPI_QKV, Ring64x64::NS, Ring64x64>(g, s, ev0, ev1);
+  if (r.rows == 64) return launch_ring_ns<EPI_QKV, Ring64x128::NS, Ring64x128>(g, s, ev0, ev1);
   return launch_ring_ns<EPI_QKV, RingShape<EPI_QKV>::NS>(g, s, ev0, ev1);
+}
+
+template <class S>
+static hipError_t launch_ring_resid(const GemmArgs &g, const ProjRoute &r, hipStream_t s, hipEvent_t ev0,
+                                    hipEvent_t ev1) {
+  if (r.kx == 1) return launch_ring_ns<EPI_RESID_F32, S::NS, S>(g, s, ev0, ev1);
+  GemmArgs gk = g;
+  gk.kx = r.kx;
+  return launch_ring_ns<EPI_RESID_F32, S::NS, S, true>(gk, s, ev0, ev1);
 }
 
 template <int EPI, int NS, class S = RingShape<EPI>, bool KSPLIT = false>
@@ -1197,27 +1061,12 @@ static hipError_t ring_attr_ns() {
 template <int CT>
 constexpr size_t big_xch_bytes() { return (size_t)4 * 2 * (kBigRowTiles / 4) * (CT / 2) * 64 * sizeof(f32x4); }
 
-// Whether a launch takes the k-halves (KS = 2): its tiles fill at most one
-// round of CUs (one 4-wave workgroup per CU would leave every SIMD a single
-// wave), K >= 1536 and the k-blocks split evenly.  Not for the modulations.
-// Measured: down of the 1536-wide expert (2048 rows) 67.7 -> 65.2 us, O and down
-// of the 1024-wide at 3200 rows -2%; at K = 1024 (time-MLP out) 18.8 -> 19.6 us,
-// hence the K bound.
 template <int EPI, int CT>
-static bool big_khalves(const GemmArgs &g) {
-  if constexpr (EPI == EPI_MOD) {
-    return false;
-  } else {
-    const int tiles = (g.M + 16 * kBigRowTiles - 1) / (16 * kBigRowTiles) * (g.N / (16 * CT));
-    return tiles <= g_n_cu && g.K >= 1536 && (g.K / kTileK) % 2 == 0;
-  }
-}
-
-template <int EPI, int CT>
-static hipError_t launch_big_ct(const GemmArgs &g, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+static hipError_t launch_big_ct(const GemmArgs &g, const ProjRoute &r, hipStream_t s, hipEvent_t ev0,
+                                hipEvent_t ev1) {
   const int wgs = grid_tile_wgs(g.M, 16 * kBigRowTiles, g.N / (16 * CT));
   if constexpr (EPI != EPI_MOD) {
-    if (big_khalves<EPI, CT>(g)) {
+    if (r.halves) {
       UAD_LAUNCH((gemm_big_kernel<EPI, CT, 2>), dim3(wgs), dim3(512), (uint32_t)big_xch_bytes<CT>(), s,
                  ev0, ev1, g);
       return hipGetLastError();
@@ -1228,54 +1077,25 @@ static hipError_t launch_big_ct(const GemmArgs &g, hipStream_t s, hipEvent_t ev0
 }
 
 template <int EPI>
-static hipError_t launch_big(const GemmArgs &g, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+static hipError_t launch_big(const GemmArgs &g, const ProjRoute &r, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   if constexpr (EPI == EPI_RESID_F32)
-    if (resid_prefers_96(g)) return launch_big_ct<EPI, 6>(g, s, ev0, ev1);
-  return launch_big_ct<EPI, 8>(g, s, ev0, ev1);
+    if (r.cols == 96) return launch_big_ct<EPI, 6>(g, r, s, ev0, ev1);
+  return launch_big_ct<EPI, 8>(g, r, s, ev0, ev1);
 }
 
-// The batched kernel serves M >= kBigM when the columns divide into its tiles,
-// no second operand is used and there are enough output tiles to fill the
-// chip: each tile runs its whole K serially in one workgroup, so with few
-// tiles (and long K) the small-M kernel, which splits K over waves, is
-// faster.  Threshold from a sweep of both kernels over 200..3200 rows and
-// the projection shapes of the 1024- and 1536-wide experts (the rule picks
-// the faster kernel in 49 of 50 cases, the miss by 6%).
-static bool big_ok(int epi, const GemmArgs &g) {
-  if (epi == EPI_QKV || epi == EPI_GEGLU || g.M < kBigM || g.N % 128 != 0) return false;
-  if (epi == EPI_RESID_F32 && g.mod_scale_next) return false;
-  const int tiles = tiles_of(g, 128, 128);
-  return tiles >= 90 && !(tiles < 128 && g.K > 4096);
-}
-
-// Which kernel a residual projection takes (kx: its split over K).
-enum ResidPath { RESID_SMALL, RESID_BIG, RESID_RING, RESID_RING96, RESID_RING64 };
-static ResidPath resid_path(const GemmArgs &g, int *kx) {
-  if ((*kx = resid_ring64(g)) > 0) return RESID_RING64;
-  const bool p96 = resid_prefers_96(g);
-  *kx = p96 ? resid_ksplit<RingResid96>(g) : resid_ksplit<RingShape<EPI_RESID_F32>>(g);
-  if (*kx > 1) return p96 ? RESID_RING96 : RESID_RING;
-  if (ring96_fits(g)) return RESID_RING96;
-  if (ring_resid_fits(g)) return RESID_RING;
-  return big_ok(EPI_RESID_F32, g) ? RESID_BIG : RESID_SMALL;
-}
-
-// Sums of squares per row that the projection leaves for the norm: one per
-// output tile of the ring kernels, per wave's columns of the register-streamed
-// one, per 16 columns of the small-M one.  The consumers re-read all of them for
-// every tile.  Same-machine, 64 -> 8 a row: QKV 28.0 -> 25.0 us and gate/up 65.4 ->
-// 59.4 at 3200 rows (64 environments 3.845 -> 3.655 ms per joint step), 96 -> 16:
-// gate/up 80.9 -> 72.5 us on the 1536-wide expert (1.836 -> 1.748 ms, 8 layers).
-int resid_ssq_tiles(const GemmArgs &g) {
-  int kx;
-  switch (resid_path(g, &kx)) {
-    case RESID_RING: return g.N / (16 * RingShape<EPI_RESID_F32>::CT);
-    case RESID_RING96: return g.N / (16 * RingResid96::CT);
-    case RESID_RING64: return g.N / 64;
-    case RESID_BIG: return g.N / (resid_prefers_96(g) ? 48 : 64);
-    default: return g.N / kTileN;
+// What the rules of routes.h see of a launch.
+static Proj proj_of(int epi, const GemmArgs &g) {
+  Proj p{};
+  p.n_cu = g_n_cu; p.epi = epi; p.M = g.M; p.N = g.N; p.K = g.K; p.second = g.A2 != nullptr;
+  if (epi == EPI_QKV) p.q_dim = g.q_dim;
+  if (epi == EPI_RESID_F32) {
+    p.gate = g.mod_gate != nullptr; p.mod_row = g.mod_row != nullptr; p.scale_next = g.mod_scale_next != nullptr;
+    if (g.kx_ws && g.kx_cnt) { p.kx_ws_bytes = g.kx_ws_bytes; p.kx_tiles = g.kx_tiles; }
   }
+  return p;
 }
+
+int resid_ssq_tiles(const GemmArgs &g) { return ssq_tiles_of(proj_of(EPI_RESID_F32, g)); }
 
 template <int EPI, int CT>
 static hipError_t big_attr() {
@@ -1355,31 +1175,23 @@ hipError_t launch_gemm(int epi, const GemmArgs &g, const GemmPlan &p, hipStream_
   // the batched kernels gate by modulation row and leave the next norm to its own pass
   if (epi == EPI_RESID_F32 && g.M >= kBigM && g.mod_gate && (!g.mod_row || g.mod_scale_next))
     return hipErrorInvalidValue;
-  if (epi == EPI_GEGLU)
-    if (const int tile = ring_tile_geglu(g)) return launch_ring_geglu(g, tile, s, ev0, ev1);
-  if (epi == EPI_QKV)
-    if (const int tile = ring_tile_qkv(g)) return launch_ring_qkv(g, tile, s, ev0, ev1);
-  if (epi == EPI_RESID_F32) {
-    using S8 = RingShape<EPI_RESID_F32>;
-    GemmArgs gk = g;
-    switch (resid_path(g, &gk.kx)) {
-      case RESID_RING96:
-        if (gk.kx > 1) return launch_ring_ns<EPI_RESID_F32, RingResid96::NS, RingResid96, true>(gk, s, ev0, ev1);
-        return launch_ring_ns<EPI_RESID_F32, RingResid96::NS, RingResid96>(g, s, ev0, ev1);
-      case RESID_RING:
-        if (gk.kx > 1) return launch_ring_ns<EPI_RESID_F32, S8::NS, S8, true>(gk, s, ev0, ev1);
-        return launch_ring_ns<EPI_RESID_F32, S8::NS, S8>(g, s, ev0, ev1);
-      case RESID_RING64:
-        if (gk.kx > 1) return launch_ring_ns<EPI_RESID_F32, Ring64x64::NS, Ring64x64, true>(gk, s, ev0, ev1);
-        return launch_ring_ns<EPI_RESID_F32, Ring64x64::NS, Ring64x64>(g, s, ev0, ev1);
-      default: break;
-    }
-  }
-  if (big_ok(epi, g)) {
+  const ProjRoute r = route_projection(proj_of(epi, g));
+  if (r.kernel == PROJ_RING) {
     switch (epi) {
-      case EPI_BIAS_SILU: return launch_big<EPI_BIAS_SILU>(g, s, ev0, ev1);
-      case EPI_RESID_F32: return launch_big<EPI_RESID_F32>(g, s, ev0, ev1);
-      case EPI_MOD: return launch_big<EPI_MOD>(g, s, ev0, ev1);
+      case EPI_GEGLU: return launch_ring_geglu(g, r, s, ev0, ev1);
+      case EPI_QKV: return launch_ring_qkv(g, r, s, ev0, ev1);
+      case EPI_RESID_F32:
+        if (r.rows == 64) return launch_ring_resid<Ring64x64>(g, r, s, ev0, ev1);
+        if (r.cols == 96) return launch_ring_resid<RingResid96>(g, r, s, ev0, ev1);
+        return launch_ring_resid<RingShape<EPI_RESID_F32>>(g, r, s, ev0, ev1);
+    }
+    return hipErrorInvalidValue;
+  }
+  if (r.kernel == PROJ_STREAMED) {
+    switch (epi) {
+      case EPI_BIAS_SILU: return launch_big<EPI_BIAS_SILU>(g, r, s, ev0, ev1);
+      case EPI_RESID_F32: return launch_big<EPI_RESID_F32>(g, r, s, ev0, ev1);
+      case EPI_MOD: return launch_big<EPI_MOD>(g, r, s, ev0, ev1);
     }
     return hipErrorInvalidValue;
   }

@@ -125,70 +125,14 @@ hipEvent_t pool_event(uad_ctx *c) {
   return e;
 }
 
-// CUs the attention launch has to leave free for the weight read-ahead of its
-// extra workgroups (below that the read-ahead is not issued).
-constexpr int kReadAheadMinCus = 32;
-
-// The most key splits that any call with these sizes takes: the workspace and
-// the limit of the no-allocation step are sized by it.  It fills one round of
-// workgroups (256) with query blocks x splits, one chunk (one memory round
-// trip) per split when that fits.
-int attn_splits_max(const uad_ctx *c, int B, int H, int n_blocks) {
-  const int qblocks = ((c->Hq / c->Hkv) * H + 63) / 64;
-  const int wgs = qblocks * B * c->Hkv;
-  const int nb = attention_chunk_blocks(c->hd);
-  int per = nb;
-  if ((long)wgs * ((n_blocks + nb - 1) / nb) > 256) {
-    for (int sp = std::max(1, 256 / wgs);; --sp) {
-      per = (n_blocks + sp - 1) / sp;
-      const int splits = (n_blocks + per - 1) / per;
-      if (sp == 1 || B * H < kBigM || 8 * ((B * c->Hkv * splits + 7) / 8) * qblocks <= c->n_cu - kReadAheadMinCus)
-        break;
-    }
-  }
-  const int smax = attention_max_splits(c->hd);
-  if ((n_blocks + per - 1) / per > smax) per = (n_blocks + smax - 1) / smax;
-  if (per > n_blocks) per = n_blocks;
-  return (n_blocks + per - 1) / per;
+AttnSizes attn_sizes(const uad_ctx *c, int B, int H, int n_blocks) {
+  return AttnSizes{c->n_cu, c->Hq / c->Hkv, c->Hkv, c->hd, B, H, n_blocks};
 }
-
-// Key splits of a call and the 32-key blocks of each.  One chunk per split
-// while the grid (its groups padded to a multiple of the 8 XCDs) fills at most
-// half the CUs: the others read weights ahead.  Beyond that two chunks or more
-// per split (longer splits run as two key groups inside the workgroup), as many
-// splits as leave kReadAheadMinCus CUs to the read-ahead, without which gate/up
-// streams its weights from HBM (~27.5 instead of ~22 us at 300-850 rows).
-// Same-machine, 1024-wide expert of 6 layers, us per joint step, 816 + 50 keys
-// (28 blocks), by splits:
-//   environments   14     10      7      5      4      3      2      1
-//        1         241    247    241    250    255    262    278    311
-//        2         350    325    325    334    335    341    357    389
-//        3         395    394    358    368    368    373    391    420
-//        4         442    453    409    417    417    427    442    464
-//        6         599    580    553    499    492    506    513    537
-//        8         674    665    601    606    544    548    562    573
-//       12         834    832    722    719    715    723    660    672
-//       20        1082   1065    888    894    872    859    879    783
-int attn_splits_nb(const uad_ctx *c, int B, int H, int n_blocks, int *bps) {
-  const int qblocks = ((c->Hq / c->Hkv) * H + 63) / 64;
-  const int nb = attention_chunk_blocks(c->hd);
-  auto grid = [&](int sp) { return 8L * (((long)B * c->Hkv * sp + 7) / 8) * qblocks; };
-  const int most = attn_splits_max(c, B, H, n_blocks);
-  int sp = std::min(most, (n_blocks + nb - 1) / nb);
-  if (2 * grid(sp) > c->n_cu) {
-    sp = std::min(most, (n_blocks + 2 * nb - 1) / (2 * nb));
-    while (sp > 1 && grid(sp) > c->n_cu - kReadAheadMinCus) --sp;
-  }
-  *bps = (n_blocks + sp - 1) / sp;
-  return (n_blocks + *bps - 1) / *bps;
-}
-
-int attn_splits(const uad_ctx *c, int B, int H, int P, int *bps) { return attn_splits_nb(c, B, H, (P + H + 31) / 32, bps); }
 
 // Split-KV partial rows (x head_dim) that a call with B environments, chunk H
 // and prefix P may write.
 size_t attn_part_rows(const uad_ctx *c, int B, int H, int P) {
-  const int sp = attn_splits_max(c, B, H, (P + H + 31) / 32);
+  const int sp = attn_splits_max(attn_sizes(c, B, H, (P + H + 31) / 32));
   if (sp <= 1) return 0;
   const size_t rows_pad = (size_t)((c->Hq / c->Hkv) * H + 63) / 64 * 64;
   return (size_t)sp * B * c->Hkv * rows_pad;
@@ -371,7 +315,7 @@ uad_status uad_create(const uad_model_config *cfg, int32_t device, void *hip_str
   for (int B = 1; B <= m.max_batch; ++B)
     for (int H = 1; H <= m.max_chunk; ++H)
       for (int nb = (H + 31) / 32; nb <= (m.max_prefix + H + 31) / 32; ++nb) {
-        const int sp = attn_splits_max(c, B, H, nb);
+        const int sp = attn_splits_max(attn_sizes(c, B, H, nb));
         if (sp > 1) {
           const size_t rows_pad = (size_t)((c->Hq / c->Hkv) * H + 63) / 64 * 64;
           part = std::max(part, (size_t)sp * B * c->Hkv * rows_pad);
@@ -885,7 +829,7 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
     at.q = c->q; at.ldq = c->q_dim; at.s_alloc = c->s_alloc; at.n_keys = c->prefix_len + H;
     at.chunk = H; at.n_heads = c->Hq; at.n_kv_heads = c->Hkv; at.group = c->Hq / c->Hkv;
     at.rows = at.group * H; at.rows_pad = (at.rows + 63) / 64 * 64;
-    at.splits = attn_splits(c, B, H, c->prefix_len, &at.blocks_per_split);
+    at.splits = attn_splits(attn_sizes(c, B, H, (c->prefix_len + H + 31) / 32), &at.blocks_per_split);
     if (!scratch && attn_part_rows(c, B, H, c->prefix_len) > c->attn_part_elems)
       return fail(c, UAD_E_SHAPE, "split-KV partials exceed the workspace sized at uad_create");
     at.qblocks = (at.rows + 63) / 64; at.n_eh = B * c->Hkv;

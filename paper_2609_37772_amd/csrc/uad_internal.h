@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "../../include/uad.h"
+#include "routes.h"
 
 namespace uad {
 
@@ -53,12 +54,6 @@ constexpr int kMaxTrSteps = 64;  // longest canonical schedule N* of the release
 // fp32 elements of one split-K partial tile (a 128 x 128 output tile); the
 // context holds two per CU
 constexpr size_t kKxPartialFloats = 128 * 128;
-constexpr int kTileN = 16;
-constexpr int kTileK = 32;
-// token rows from which the register-streamed 128-row kernels, the split of the
-// large residual tiles and the adaptive norms by class apply (the ring's smaller
-// tiles go by tile count)
-constexpr int kBigM = 256;
 constexpr int kBlockElems = kTileN * kTileK;  // 512 fp16 = 1 KiB
 
 // Device status word of a context (bits, cleared and reported by
@@ -149,14 +144,6 @@ __host__ __device__ __forceinline__ size_t vt_index(size_t eh, int s, int c, int
 // ---------------------------------------------------------------------------
 // Kernel argument blocks
 // ---------------------------------------------------------------------------
-enum Epilogue : int {
-  EPI_BIAS_SILU = 0,   // out = fp16 silu(acc + bias), fragment order
-  EPI_RESID_F32 = 1,   // h = (bias | h) + acc; per-tile sum of squares; next operand fp16(h * gain_next)
-  EPI_GEGLU = 3,       // out = fp16 gelu_tanh(rstd*acc_gate) * rstd*acc_up (interleaved gate/up)
-  EPI_QKV = 4,         // rstd*acc: q -> bf16 q buffer; k, v -> per-layer K / V^T store
-  EPI_MOD = 5,         // adaptive-norm modulations of every norm site (see uad_ctx::mod)
-};
-
 struct GemmPlan {
   int T;        // 16-column weight tiles per workgroup
   int mgroups;  // row groups (grid.z); group z owns 16-row tiles [z*MT/mgroups, (z+1)*MT/mgroups)
@@ -344,8 +331,6 @@ hipError_t gemm_init();                  // once per context: raise the batched 
 // lowers the read-ahead of the attention (by `wgs` workgroups) and of the split
 // merge to the weight bytes that they can read while those run
 void attention_read_ahead_caps(const AttnArgs &a, int head_dim, int wgs, size_t *attn, size_t *merge);
-int attention_chunk_blocks(int head_dim);  // 32-key blocks loaded per round trip
-int attention_max_splits(int head_dim);    // split-KV partials the combine accepts
 // env_map (compacted steps): token m of the step reads x and t of token
 // env_map[m / chunk] * chunk + m % chunk (null: token m)
 hipError_t launch_temb(const float *x, const float *t, int M, int Da, int d, const float *w_in,

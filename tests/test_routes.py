@@ -1,0 +1,34 @@
+"""The dispatch rules on the CPU: the GPU tests' sizes take the kernels that
+those tests name."""
+import pytest
+
+from tests import routes as R
+
+D, F, QD, NQKV = 512, 4096, 2048, 2560  # the expert of test_gpu_ring_tiles
+
+
+@pytest.mark.parametrize("rows,gateup,qkv,o,down", [
+    (133, (64, 128), None, None, None),
+    (255, (64, 128), (64, 64), None, None),
+    (637, (128, 128), (64, 64), None, (64, 64, 4)),
+    (1281, (128, 256), (128, 128), (64, 64, 1), (64, 64, 4)),
+    (1581, (128, 256), (64, 128), (64, 64, 1), (64, 64, 2)),
+    (1749, (128, 256), (128, 128), (64, 64, 1), None),
+])
+def test_ring_tile_sizes(rows, gateup, qkv, o, down):
+    def ring(epi, N, K, q_dim=0):
+        r = R.projection(epi, rows, N, K, q_dim=q_dim)
+        return r[1:] if r[0] == R.RING else None
+    assert (ring(R.GEGLU, 2 * F, D) or (None,) * 2)[:2] == (gateup or (None,) * 2)
+    assert (ring(R.QKV, NQKV, D, QD) or (None,) * 2)[:2] == (qkv or (None,) * 2)
+    assert (ring(R.RESID, D, QD) or (None,) * 3)[:3] == (o or (None,) * 3)
+    assert (ring(R.RESID, D, F) or (None,) * 3)[:3] == (down or (None,) * 3)
+
+
+@pytest.mark.parametrize("hd,heads,hkv,B,H,keys,splits", [  # the sizes of test_gpu_attention_groups
+    (256, 2, 1, 130, 16, 5 * 32, 1), (256, 2, 1, 130, 16, 6 * 32 - 31, 1), (128, 4, 2, 70, 9, 9 * 32 - 5, 1),
+    (64, 4, 4, 40, 20, 10 * 32 - 1, 1), (256, 2, 1, 40, 16, 25 * 32 - 7, 5), (128, 2, 1, 30, 16, 70 * 32 - 3, 7),
+])
+def test_two_key_group_sizes(hd, heads, hkv, B, H, keys, splits):
+    got, per, two, most = R.attention(heads, hkv, hd, B, H, keys)
+    assert two == 1 and got == splits <= most and got * per >= (keys + 31) // 32
