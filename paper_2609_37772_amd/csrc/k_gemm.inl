@@ -1172,9 +1172,6 @@ GemmPlan plan_gemm(int epi, int M, int N, int K) {
 hipError_t launch_gemm(int epi, const GemmArgs &g, const GemmPlan &p, hipStream_t s, hipEvent_t ev0,
                        hipEvent_t ev1) {
   if (g.m_alloc < g.M || g.m_alloc % 16 != 0) return hipErrorInvalidValue;  // operand rows allocated
-  // the batched kernels gate by modulation row and leave the next norm to its own pass
-  if (epi == EPI_RESID_F32 && g.M >= kBigM && g.mod_gate && (!g.mod_row || g.mod_scale_next))
-    return hipErrorInvalidValue;
   const ProjRoute r = route_projection(proj_of(epi, g));
   if (r.kernel == PROJ_RING) {
     switch (epi) {

@@ -131,7 +131,7 @@ inline bool ring96_fits(const Proj &g) {
 //   down 6144 -> 1536  256 (96) 21.3 -> 31.1 / 20.8 / 15.9, 384 (144) 30.4 -> 31.4 /
 //     23.4 / 20.7, 640 (240) 27.5 -> 40.6 / 31.5; 128 (48) 14.8 -> - / 23.6 / 15.8
 inline int resid_ring64(const Proj &g) {
-  if (g.second || g.scale_next || (g.gate && !g.mod_row) || g.M <= 64 || g.N % 64 != 0) return 0;
+  if (g.second || g.M <= 64 || g.N % 64 != 0) return 0;
   const int t = tiles_of(g, 64, 64);
   if (g.K < 4096) return 16 * t >= 9 * g.n_cu && t <= 2 * g.n_cu ? 1 : 0;
   if (16 * t < 5 * g.n_cu || 32 * t > 27 * g.n_cu || t > g.kx_tiles) return 0;
@@ -204,7 +204,6 @@ inline bool big_khalves(const Proj &g, int cols) {
 // the faster kernel in 49 of 50 cases, the miss by 6%).
 inline bool big_ok(const Proj &g) {
   if (g.epi == EPI_QKV || g.epi == EPI_GEGLU || g.M < kBigM || g.N % 128 != 0) return false;
-  if (g.epi == EPI_RESID_F32 && g.scale_next) return false;
   const int tiles = tiles_of(g, 128, 128);
   return tiles >= 90 && !(tiles < 128 && g.K > 4096);
 }
@@ -217,6 +216,9 @@ inline ProjRoute route_projection(const Proj &g) {
     const int t = ring_tile_geglu(g);
     return tile(t == 128256 ? geglu_tile_rows(g) * 1000 + 256 : t);
   }
+  // the ring and register-streamed epilogues gate by modulation row and leave an
+  // adaptive next norm to a pass of its own
+  if (g.epi == EPI_RESID_F32 && (g.scale_next || (g.gate && !g.mod_row))) return tile(0);
   const int cols = g.epi == EPI_RESID_F32 && resid_prefers_96(g) ? 96 : 128;
   if (g.epi == EPI_RESID_F32) {
     if (const int kx = resid_ring64(g)) return ProjRoute{PROJ_RING, 64, 64, kx, false};

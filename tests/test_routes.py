@@ -32,3 +32,17 @@ def test_ring_tile_sizes(rows, gateup, qkv, o, down):
 def test_two_key_group_sizes(hd, heads, hkv, B, H, keys, splits):
     got, per, two, most = R.attention(heads, hkv, hd, B, H, keys)
     assert two == 1 and got == splits <= most and got * per >= (keys + 31) // 32
+
+
+@pytest.mark.parametrize("n_cu", [32, 64, 128, 256])
+def test_unmapped_modulations_stay_on_the_small_kernel(n_cu):
+    """Only the small-M kernel takes a residual projection's gate by token row
+    (mod_row null) or forms the next operand from a modulation: the ring and
+    register-streamed kernels read mod_row for every gated row.  On a chip cut
+    into partitions a few rows fill half the CUs."""
+    for d in range(32, 2049, 32):
+        for rows in (*range(1, 256, 9), 63, 64, 65, 128, 129, 192, 193, 255, 256, 1400, 3200):
+            for K in (d, 2048, 4096):
+                for scale_next in (False, True):
+                    r = R.projection(R.RESID, rows, d, K, n_cu, gate=True, scale_next=scale_next)
+                    assert r[0] == R.SMALL, (n_cu, d, rows, K, r)
