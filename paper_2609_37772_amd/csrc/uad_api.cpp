@@ -593,14 +593,29 @@ uad_status uad_load_weights(uad_ctx *c, const uad_tensor *ts, int32_t n) {
   return UAD_OK;
 }
 
-// Whether this context's kernels can read a caller's device pointer in place
-// (memory of this device or managed memory; not another device's).
-static bool reads_directly(const uad_ctx *c, const void *p) {
-  hipPointerAttribute_t pa{};
-  const bool ok = hipPointerGetAttributes(&pa, p) == hipSuccess &&
-                  ((pa.type == hipMemoryTypeDevice && pa.device == c->device) || pa.type == hipMemoryTypeManaged);
-  (void)hipGetLastError();
-  return ok;
+// How the kernels of this context get at `bytes` of a caller's device memory: in
+// place (memory of this device or managed memory), by copies (anything else,
+// another device's say), or not at all: the allocation ends before the bytes do.
+// A copy refuses such a range; a kernel would read past its end.  Adjacent
+// allocations count as one.
+enum SourceKind { SOURCE_READ, SOURCE_COPY, SOURCE_SHORT };
+static SourceKind source_kind(const uad_ctx *c, const void *p, size_t bytes) {
+  SourceKind kind = SOURCE_READ;
+  const char *at = (const char *)p, *const end = at + bytes;
+  while (at < end) {
+    hipPointerAttribute_t pa{};
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&pa, at) != hipSuccess ||
+        (pa.type != hipMemoryTypeDevice && pa.type != hipMemoryTypeManaged) ||
+        hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)at) != hipSuccess || (const char *)base + size <= at) {
+      (void)hipGetLastError();
+      return at == p ? SOURCE_COPY : SOURCE_SHORT;
+    }
+    if (pa.type == hipMemoryTypeDevice && pa.device != c->device) kind = SOURCE_COPY;
+    at = (const char *)base + size;
+  }
+  return kind;
 }
 
 uad_status uad_set_prefix_kv(uad_ctx *c, const void *k, const void *v, int32_t dtype, int32_t batch,
@@ -612,12 +627,22 @@ uad_status uad_set_prefix_kv(uad_ctx *c, const void *k, const void *v, int32_t d
   if (batch > c->cfg.max_batch) return fail(c, UAD_E_SHAPE, "uad_set_prefix_kv: batch > max_batch");
   if (prefix_len > c->cfg.max_prefix) return fail(c, UAD_E_SHAPE, "uad_set_prefix_kv: prefix_len > max_prefix");
   (void)hipSetDevice(c->device);
+  const size_t esz = dtype == UAD_DTYPE_F32 ? 4 : 2;
+  const size_t src_bytes = (size_t)c->L * batch * prefix_len * c->Hkv * c->hd * esz;
+  bool in_place = prefix_len == 0;
+  if (on_device && !in_place) {
+    const SourceKind kk = source_kind(c, k, src_bytes), kv = source_kind(c, v, src_bytes);
+    if (kk == SOURCE_SHORT || kv == SOURCE_SHORT)
+      return fail(c, UAD_E_HIP, "uad_set_prefix_kv: the allocation of k or v ends before its " +
+                                    std::to_string(src_bytes) + " bytes");
+    in_place = kk == SOURCE_READ && kv == SOURCE_READ;
+  }
   // queued steps (a release's tail, say) may still read the K/V being replaced
   hipError_t se = hipStreamSynchronize(c->stream);
   if (se != hipSuccess) return hip_fail(c, se, "uad_set_prefix_kv: hipStreamSynchronize");
   const int L = c->L, Hkv = c->Hkv, hd = c->hd, P = prefix_len;
   const bool f32 = dtype == UAD_DTYPE_F32;
-  const size_t esz = f32 ? 4 : 2, row = (size_t)Hkv * hd;  // elements per key
+  const size_t row = (size_t)Hkv * hd;  // elements per key
   PrefixArgs a{};
   a.n_keys = P; a.n_kv_heads = Hkv; a.s_alloc = c->s_alloc; a.n_blk = c->s_alloc / 32; a.n_env = batch; a.n_layers = L;
   a.dst_layer = c->kv_layer_elems; a.kc = c->kcache; a.vtc = c->vtcache;
@@ -625,7 +650,7 @@ uad_status uad_set_prefix_kv(uad_ctx *c, const void *k, const void *v, int32_t d
   // All on the null stream, as the copies of a caller's buffers always were:
   // ordered after what the caller queued there.
   hipError_t e = hipSuccess;
-  if (P == 0 || (on_device && reads_directly(c, k) && reads_directly(c, v))) {
+  if (in_place) {
     a.k = k; a.v = v;
     e = launch_prefix_pack(a, hd, f32, nullptr);
   } else {

@@ -1,0 +1,98 @@
+"""uad_set_prefix_kv's host code against a stand-in for the HIP runtime
+(tests/stub): which sources are read in place, what is refused before anything
+is written, and what an error on the way leaves behind."""
+import concurrent.futures as cf
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+import paper_2609_37772_amd as U
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+OK, STATE, HIP = 0, 3, 5
+L, B, P, HKV, HD = 2, 2, 70, 2, 64
+BYTES = L * B * P * HKV * HD * 4
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = str(tmp_path_factory.mktemp("stub"))
+    srcs = [os.path.join(ROOT, p) for p in ("paper_2609_37772_amd/csrc/uad_api.cpp",
+                                            "paper_2609_37772_amd/csrc/schedule.cpp", "tests/stub/hip_stub.cpp")]
+
+    def compile_one(src):
+        obj = os.path.join(d, os.path.basename(src) + ".o")
+        subprocess.run([HIPCC, "-x", "hip", "--offload-arch=gfx950", "--offload-host-only", "-O1", "-fPIC", "-std=c++17",
+                        "-c", src, "-o", obj], check=True)
+        return obj
+    with cf.ThreadPoolExecutor(3) as ex:
+        objs = list(ex.map(compile_one, srcs))
+    # the device code that host-only objects refer to does not exist
+    names = subprocess.run(["nm", "-u", *objs], capture_output=True, text=True, check=True).stdout.split()
+    fat = ["-Wl,--defsym,%s=0" % n for n in names if n.startswith("__hip_fatbin")]
+    so = os.path.join(d, "libstub.so")
+    subprocess.run(["g++", "-shared", "-o", so, *objs, "-Wl,-z,defs", "-Wl,-Bsymbolic", *fat], check=True)
+    lib = ctypes.CDLL(so)
+    lib.stub_log.restype = lib.uad_last_error.restype = ctypes.c_char_p
+    lib.stub_map.argtypes = [ctypes.c_void_p, ctypes.c_size_t]
+    return lib
+
+
+@pytest.fixture
+def ctx(lib):
+    cfg = U._binding.uad_model_config(L, 128, 2, HKV, HD, 256, 7, B, 8, P + 10, 1e-6, 0)
+    c = ctypes.c_void_p()
+    assert lib.uad_create(ctypes.byref(cfg), 0, None, ctypes.byref(c)) == OK
+    yield c
+    lib.uad_destroy(c)
+
+
+class Memory:
+    """`n` bytes in the middle of nothing: the runtime knows only what was mapped."""
+
+    def __init__(self, lib, n):
+        self.lib, self.a, self.maps = lib, np.zeros(n, np.uint8), []
+        self.p = self.a.ctypes.data
+
+    def map(self, at, n):
+        self.lib.stub_map(self.p + at, n)
+        self.maps.append(self.p + at)
+        return self
+
+    def unmap(self):
+        for p in self.maps:
+            self.lib.stub_map(p, 0)
+
+
+def set_prefix(lib, c, k, v, on_device, fail_in=-1):
+    lib.stub_reset(fail_in)
+    st = lib.uad_set_prefix_kv(c, ctypes.c_void_p(k), ctypes.c_void_p(v), 0, B, P, on_device)
+    return st, lib.stub_log().decode().split()
+
+
+@pytest.mark.parametrize("pieces", [[BYTES], [BYTES + 100], [4096, BYTES - 4096], [BYTES // 2, 64, BYTES]])
+def test_covered_device_source_is_read_in_place(lib, ctx, pieces):
+    k, v = Memory(lib, BYTES + 8192), Memory(lib, 3 * BYTES)
+    k.map(0, BYTES)
+    at = 0
+    for n in pieces:
+        v.map(at, n)
+        at += n
+    st, log = set_prefix(lib, ctx, k.p, v.p, 1)
+    assert st == OK and "copy" not in log and log.count("pack") == 1
+    k.unmap(), v.unmap()
+
+
+@pytest.mark.parametrize("short", [1, 4, BYTES // 2 + 4, BYTES // L])
+def test_device_source_shorter_than_the_prefix_is_refused(lib, ctx, short):
+    """The device kernel would read past the allocation; the copies that it took
+    the place of were refused."""
+    k, v = Memory(lib, BYTES).map(0, BYTES), Memory(lib, BYTES).map(0, BYTES - short)
+    for pair in ((k.p, v.p), (v.p, k.p)):
+        st, log = set_prefix(lib, ctx, *pair, 1)
+        assert st == HIP and not {"copy", "pack"} & set(log)
+    k.unmap(), v.unmap()
