@@ -648,9 +648,13 @@ uad_status uad_set_prefix_kv(uad_ctx *c, const void *k, const void *v, int32_t d
   a.dst_layer = c->kv_layer_elems; a.kc = c->kcache; a.vtc = c->vtcache;
   a.src_env = (size_t)P * row; a.src_layer = batch * a.src_env;
   // All on the null stream, as the copies of a caller's buffers always were:
-  // ordered after what the caller queued there.
+  // ordered after what the caller queued there.  Every way out waits for what
+  // was queued, since that uses the caller's memory, and an error leaves no
+  // prefix (the stores may hold parts of both).
   hipError_t e = hipSuccess;
+  void *own = nullptr;
   if (in_place) {
+    c->prefix_set = false;
     a.k = k; a.v = v;
     e = launch_prefix_pack(a, hd, f32, nullptr);
   } else {
@@ -659,13 +663,13 @@ uad_status uad_set_prefix_kv(uad_ctx *c, const void *k, const void *v, int32_t d
     // 32-key blocks of one where an environment does not fit.
     size_t half = c->kx_ws_bytes / 2 & ~(size_t)15;
     char *sk = (char *)c->kx_ws;
-    void *own = nullptr;  // hundreds of wide KV heads: one block exceeds the workspace
     const size_t env_bytes = a.src_env * esz, blk_bytes = 32 * row * esz;
-    if (blk_bytes > half) {
+    if (blk_bytes > half) {  // hundreds of wide KV heads: one block exceeds the workspace
       half = blk_bytes;
-      if ((e = hipMalloc(&own, 2 * half)) != hipSuccess) return hip_fail(c, e, "uad_set_prefix_kv: hipMalloc(staging)");
+      e = hipMalloc(&own, 2 * half);
       sk = (char *)own;
     }
+    if (e == hipSuccess) c->prefix_set = false;
     char *sv = sk + half;
     a.k = sk; a.v = sv; a.src_layer = 0; a.n_layers = 1;
     const int envs = (int)std::min<size_t>(batch, half / env_bytes);  // 0: part of one
@@ -691,12 +695,10 @@ uad_status uad_set_prefix_kv(uad_ctx *c, const void *k, const void *v, int32_t d
         }
       }
     }
-    if (own) {
-      (void)hipStreamSynchronize(nullptr);
-      (void)hipFree(own);
-    }
   }
-  if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+  const hipError_t done = hipStreamSynchronize(nullptr);
+  if (e == hipSuccess) e = done;
+  if (own) (void)hipFree(own);
   if (e != hipSuccess) return hip_fail(c, e, "uad_set_prefix_kv");
   c->prefix_len = P;
   c->prefix_batch = batch;

@@ -38,6 +38,8 @@ void __hipUnregisterFatBinary(void **) {}
 void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
 void __hipRegisterFunction(void **, const void *, char *, const char *, unsigned, void *, void *, void *, void *, int *) {}
 
+int stub_prefix_set(const uad_ctx *c) { return c->prefix_set; }
+
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
 const char *hipGetErrorString(hipError_t e) { return e == hipSuccess ? "success" : "stub error"; }

@@ -96,3 +96,19 @@ def test_device_source_shorter_than_the_prefix_is_refused(lib, ctx, short):
         st, log = set_prefix(lib, ctx, *pair, 1)
         assert st == HIP and not {"copy", "pack"} & set(log)
     k.unmap(), v.unmap()
+
+
+@pytest.mark.parametrize("on_device,fail_in", [(0, 0), (0, 1), (0, 2), (0, 4), (1, 0)])
+def test_error_on_the_way_waits_and_leaves_no_prefix(lib, ctx, on_device, fail_in):
+    """An error after copies or kernels were queued: they still use the caller's
+    memory until the wait, and the stores hold parts of two prefixes."""
+    k, v = Memory(lib, BYTES), Memory(lib, BYTES)
+    if on_device:
+        k.map(0, BYTES), v.map(0, BYTES)
+    assert set_prefix(lib, ctx, k.p, v.p, on_device)[0] == OK
+    st, log = set_prefix(lib, ctx, k.p, v.p, on_device, fail_in)
+    assert st == HIP and log[-1] == "sync" and len(log) == fail_in + 3  # the stream's wait, the calls, the wait
+    assert b"stub error" in lib.uad_last_error(ctx)
+    assert lib.stub_prefix_set(ctx) == 0
+    assert set_prefix(lib, ctx, k.p, v.p, on_device)[0] == OK and lib.stub_prefix_set(ctx) == 1
+    k.unmap(), v.unmap()
