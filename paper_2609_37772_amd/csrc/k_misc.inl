@@ -622,23 +622,26 @@ static hipError_t launch_prefix_hd(const PrefixArgs &a, bool f32, hipStream_t s)
 }
 
 hipError_t launch_prefix_pack(const PrefixArgs &a, int head_dim, bool f32, hipStream_t s) {
-  if (a.n_env < 1 || a.n_blk < 1 || a.n_layers < 1 || (a.blk0 + a.n_blk) * 32 > a.s_alloc ||
-      (int64_t)a.n_env * a.n_kv_heads * a.n_blk >= (int64_t)1 << 24)  // grid.x threads stay below 2^32
-    return hipErrorInvalidValue;
+  if (a.n_env < 1 || a.n_blk < 1 || a.n_layers < 1 || (a.blk0 + a.n_blk) * 32 > a.s_alloc) return hipErrorInvalidValue;
   const size_t esz = f32 ? 4 : 2;
   constexpr int kMaxZ = 32768;
   for (int l = 0; l < a.n_layers; l += kMaxZ) {
-    PrefixArgs p = a;
-    p.n_layers = a.n_layers - l < kMaxZ ? a.n_layers - l : kMaxZ;
-    p.k = (const char *)a.k + l * a.src_layer * esz;
-    p.v = (const char *)a.v + l * a.src_layer * esz;
-    p.kc = a.kc + l * a.dst_layer;
-    p.vtc = a.vtc + l * a.dst_layer;
-    hipError_t e = hipErrorInvalidValue;
-    if (head_dim == 64) e = launch_prefix_hd<64>(p, f32, s);
-    else if (head_dim == 128) e = launch_prefix_hd<128>(p, f32, s);
-    else if (head_dim == 256) e = launch_prefix_hd<256>(p, f32, s);
-    if (e != hipSuccess) return e;
+    const int r = for_pack_launches(a.n_env, a.n_kv_heads, a.n_blk, [&](int env, int envs, int blk, int blks) {
+      PrefixArgs p = a;
+      p.n_layers = a.n_layers - l < kMaxZ ? a.n_layers - l : kMaxZ;
+      p.env0 = a.env0 + env; p.n_env = envs;
+      p.blk0 = a.blk0 + blk; p.n_blk = blks;
+      const size_t src = (l * a.src_layer + env * a.src_env) * esz;
+      p.k = (const char *)a.k + src;
+      p.v = (const char *)a.v + src;
+      p.kc = a.kc + l * a.dst_layer;
+      p.vtc = a.vtc + l * a.dst_layer;
+      if (head_dim == 64) return (int)launch_prefix_hd<64>(p, f32, s);
+      if (head_dim == 128) return (int)launch_prefix_hd<128>(p, f32, s);
+      if (head_dim == 256) return (int)launch_prefix_hd<256>(p, f32, s);
+      return (int)hipErrorInvalidValue;
+    });
+    if (r) return (hipError_t)r;
   }
   return hipSuccess;
 }

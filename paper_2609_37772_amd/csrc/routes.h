@@ -243,6 +243,24 @@ inline int ssq_tiles_of(const Proj &g) {
 }
 
 // ---------------------------------------------------------------------------
+// Prefix repacking
+// ---------------------------------------------------------------------------
+// Cuts n_env environments x n_kv_heads x n_blk 32-key blocks into launches whose
+// 256-thread workgroups fit a grid (its threads stay below 2^32): whole
+// environments, or blocks of one.  f(first environment, environments, first
+// block, blocks) returns 0 to go on; the result is its last value.
+template <class F>
+int for_pack_launches(int n_env, int n_kv_heads, int n_blk, F f) {
+  constexpr int most = (1 << 24) - 1;
+  const int blks = std::min(n_blk, std::max(1, most / n_kv_heads));
+  const int envs = blks < n_blk ? 1 : std::max(1, most / (n_kv_heads * blks));
+  for (int e = 0; e < n_env; e += envs)
+    for (int q = 0; q < n_blk; q += blks)
+      if (const int r = f(e, std::min(envs, n_env - e), q, std::min(blks, n_blk - q))) return r;
+  return 0;
+}
+
+// ---------------------------------------------------------------------------
 // Attention
 // ---------------------------------------------------------------------------
 // Blocks per chunk (one memory round trip); two chunks are resident (double

@@ -29,6 +29,15 @@ extern "C" void attention(const int *a, int *out) {  // n_cu group n_kv_heads he
   out[2] = attn_two_groups(s.n_cu, groups, s.qblocks(), out[1], nb);
   out[3] = attn_splits_max(s);
 }
+extern "C" int pack_launches(const int *a, int *out) {  // n_env n_kv_heads n_blk -> (env envs blk blks)*, how many
+  int n = 0;
+  for_pack_launches(a[0], a[1], a[2], [&](int e, int ne, int q, int nq) {
+    const int v[4] = {e, ne, q, nq};
+    std::copy(v, v + 4, out + 4 * n);
+    return (int)(++n == 64);
+  });
+  return n;
+}
 """
 
 
@@ -56,3 +65,10 @@ def projection(epi, M, N, K, n_cu=256, q_dim=0, second=False, gate=False, mod_ro
 def attention(heads, n_kv_heads, head_dim, B, H, keys, n_cu=256):
     """(key splits, 32-key blocks of each, two key groups, most splits)."""
     return _call("attention", (n_cu, heads // n_kv_heads, n_kv_heads, head_dim, B, H, keys), 4)
+
+
+def pack_launches(n_env, n_kv_heads, n_blk):
+    """The launches of a prefix repacking: (first environment, environments, first block, blocks)."""
+    a, out = (ctypes.c_int * 3)(n_env, n_kv_heads, n_blk), (ctypes.c_int * 256)()
+    n = _lib().pack_launches(a, out)
+    return [tuple(out[4 * i:4 * i + 4]) for i in range(n)]

@@ -46,3 +46,17 @@ def test_unmapped_modulations_stay_on_the_small_kernel(n_cu):
                 for scale_next in (False, True):
                     r = R.projection(R.RESID, rows, d, K, n_cu, gate=True, scale_next=scale_next)
                     assert r[0] == R.SMALL, (n_cu, d, rows, K, r)
+
+
+@pytest.mark.parametrize("n_env,hkv,n_blk,launches", [
+    (64, 1, 27, 1), (64, 64, 4095, 1), (64, 64, 4096, 2), (512, 128, 2048, 9), (3, 4096, 4096, 6), (1, 1, 1 << 24, 2),
+])
+def test_prefix_pack_launches_cover_any_size(n_env, hkv, n_blk, launches):
+    """Every (environment, block) once, each launch below 2^24 workgroups."""
+    got = R.pack_launches(n_env, hkv, n_blk)
+    assert len(got) == launches
+    assert all(e * hkv * b < 1 << 24 for _, e, _, b in got)
+    assert sum(e * b for _, e, _, b in got) == n_env * n_blk
+    spans = sorted((e0, q0) for e0, _, q0, _ in got)
+    assert len(set(spans)) == launches and max(e0 + e for e0, e, _, _ in got) == n_env
+    assert max(q0 + b for _, _, q0, b in got) == n_blk
