@@ -761,6 +761,10 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
   const size_t MA = c->m_alloc;
   const bool prof = c->prof_on && !scratch;
   hipError_t e = hipSuccess;
+  const bool by_class = !c->dbg && ada_by_class(c, M, pre != nullptr);
+  // the adaptive-norm embedding takes no compaction map, and by class the row map
+  // has its place in the final kernel's arguments
+  if (c->ada && env_map) return fail(c, UAD_E_STATE, "adaptive norms: a compacted step");
   // measurement hook: the launch records a start/stop event pair taken from
   // the kernel's own dispatch packet (ea_/eb_ are nullptr when not profiling)
 #define UAD_CHECK_CLS(cls, call)                       \
@@ -785,7 +789,6 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
       x.kx_ws = c->kx_ws; x.kx_cnt = c->kx_cnt; x.kx_ws_bytes = c->kx_ws_bytes; x.kx_tiles = c->n_cu;
     };
     const int n_mod = c->n_mod;
-    const bool ada_batched = ada_by_class(c, M, pre != nullptr);
     if (!c->ada) {
       UAD_CHECK_CLS(K_TEMB, launch_temb(x, t, M, c->Da, d, c->action_in_w, c->action_in_b, c->freqs, c->a_te, c->status, s,
                                         ea_, eb_, env_map, H));
@@ -808,7 +811,7 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
       UAD_CHECK_CLS(K_TEMB, launch_temb_ada(x, nullptr, M, c->Da, d, c->action_in_w, c->action_in_b, c->freqs,
                                             c->a_te, c->h, c->ssq, (int)MA, c->status, s, ea_, eb_, pre->mod, n_mod,
                                             c->a_n));
-    } else if (ada_batched) {
+    } else if (by_class) {
       // batched adaptive norms: h_0, then the time MLP and the modulations of the
       // step's distinct flow times; token m's are row mod_cls[m]
       UAD_CHECK_CLS(K_TEMB, launch_temb_ada(x, nullptr, M, c->Da, d, c->action_in_w, c->action_in_b, c->freqs,
@@ -891,7 +894,7 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
       const float *mod_base = pre ? pre->mod : c->mod;
       const op_t *shift_base = pre ? pre->shift : c->mod_shift_ops;
       const size_t shift_stride = pre ? pre->shift_stride : MA * d;
-      if (ada_batched) {
+      if (by_class) {
         const float *ml = c->mod + (size_t)l * 6 * d;
         UAD_CHECK_CLS(K_ADA_NORM, launch_ada_norm(c->h, M, d, c->cfg.rms_eps, ml, ml + d, n_mod, c->mod_cls, c->a_n,
                                                   c->status, s, ea_, eb_));
@@ -930,7 +933,7 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
       if (c->ada) {
         const float *ml = mod_base + (size_t)l * 6 * d;
         o.mod_ld = n_mod; o.mod_gate = ml + 2 * d; o.mod_scale_next = ml + 3 * d; o.gain_next = nullptr;
-        if (ada_batched) { o.mod_row = c->mod_cls; o.mod_scale_next = nullptr; }
+        if (by_class) { o.mod_row = c->mod_cls; o.mod_scale_next = nullptr; }
       }
       UAD_CHECK_CLS(K_GEMM_O, launch_gemm(EPI_RESID_F32, o, po, s, ea_, eb_));
       ssq_tiles = resid_ssq_tiles(o);
@@ -938,7 +941,7 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
       gu.status = c->status;
       gu.M = M; gu.A = c->a_n; gu.W = lp.wgu; gu.N = 2 * F; gu.K = d;
       gu.out = c->a_g; gu.ldo = F; norm_fields(gu); gu.use_rstd = 1;
-      if (ada_batched) {
+      if (by_class) {
         const float *ml = c->mod + (size_t)l * 6 * d + 3 * d;
         UAD_CHECK_CLS(K_ADA_NORM, launch_ada_norm(c->h, M, d, c->cfg.rms_eps, ml, ml + d, n_mod, c->mod_cls, c->a_n,
                                                   c->status, s, ea_, eb_));
@@ -956,7 +959,7 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
         const float *ml = mod_base + (size_t)l * 6 * d;
         dn.mod_ld = n_mod; dn.mod_gate = ml + 5 * d; dn.gain_next = nullptr;
         dn.mod_scale_next = (l + 1 < c->L) ? ml + 6 * d : nullptr;
-        if (ada_batched) { dn.mod_row = c->mod_cls; dn.mod_scale_next = nullptr; }
+        if (by_class) { dn.mod_row = c->mod_cls; dn.mod_scale_next = nullptr; }
       }
       UAD_CHECK_CLS(K_GEMM_DOWN, launch_gemm(EPI_RESID_F32, dn, pd, s, ea_, eb_));
       ssq_tiles = resid_ssq_tiles(dn);
@@ -968,8 +971,6 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
   f.is_last_step = is_last; f.step = step; f.v_out = v_out; f.released = released; f.release_step = release_step;
   f.debug_field = c->dbg ? 1 : 0; f.dbg_alpha = c->dbg_alpha; f.dbg_beta = c->dbg_beta;
   f.vsum = vsum; f.vsum_tokens = vsum_tokens; f.chunk = H; f.env_map = env_map;
-  const bool by_class = !c->dbg && ada_by_class(c, M, pre != nullptr);
-  if (by_class && env_map) return fail(c, UAD_E_STATE, "adaptive norms: a compacted step");
   if (c->ada) {
     f.mod_scale = (pre ? pre->mod : c->mod) + (size_t)c->L * 6 * d; f.mod_shift = f.mod_scale + d;
     f.mod_ld = c->n_mod;

@@ -38,6 +38,9 @@ void __hipUnregisterFatBinary(void **) {}
 void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
 void __hipRegisterFunction(void **, const void *, char *, const char *, unsigned, void *, void *, void *, void *, int *) {}
 
+// a context that may step, and environments evaluated at a step of its last budgets
+void stub_ready(uad_ctx *c) { c->weights_loaded = c->prefix_set = true; c->prefix_batch = c->cfg.max_batch; }
+void stub_set_active(uad_ctx *c, int step, int n) { c->bud_active[step] = (uint16_t)n; }
 int stub_prefix_set(const uad_ctx *c) { return c->prefix_set; }
 
 hipError_t hipSetDevice(int) { return hipSuccess; }

@@ -1,6 +1,7 @@
-"""uad_set_prefix_kv's host code against a stand-in for the HIP runtime
-(tests/stub): which sources are read in place, what is refused before anything
-is written, and what an error on the way leaves behind."""
+"""The library's host code against a stand-in for the HIP runtime (tests/stub).
+uad_set_prefix_kv: which sources are read in place, what is refused before
+anything is written, and what an error on the way leaves behind.  Steps: what is
+refused before any work is enqueued."""
 import concurrent.futures as cf
 import ctypes
 import os
@@ -42,11 +43,16 @@ def lib(tmp_path_factory):
     return lib
 
 
-@pytest.fixture
-def ctx(lib):
-    cfg = U._binding.uad_model_config(L, 128, 2, HKV, HD, 256, 7, B, 8, P + 10, 1e-6, 0)
+def create(lib, batch=B, chunk=8, flags=0):
+    cfg = U._binding.uad_model_config(L, 128, 2, HKV, HD, 256, 7, batch, chunk, P + 10, 1e-6, flags)
     c = ctypes.c_void_p()
     assert lib.uad_create(ctypes.byref(cfg), 0, None, ctypes.byref(c)) == OK
+    return c
+
+
+@pytest.fixture
+def ctx(lib):
+    c = create(lib)
     yield c
     lib.uad_destroy(c)
 
@@ -112,3 +118,17 @@ def test_error_on_the_way_waits_and_leaves_no_prefix(lib, ctx, on_device, fail_i
     assert lib.stub_prefix_set(ctx) == 0
     assert set_prefix(lib, ctx, k.p, v.p, on_device)[0] == OK and lib.stub_prefix_set(ctx) == 1
     k.unmap(), v.unmap()
+
+
+@pytest.mark.parametrize("batch,chunk", [(3, 8), (20, 16)])  # below and from the row count of the by-class norms
+def test_compacted_adaptive_norm_step_is_refused_before_any_work(lib, batch, chunk):
+    c = create(lib, batch, chunk, flags=1)
+    lib.stub_ready(c)
+    x, bud = np.zeros((batch, chunk, 7), np.float32), np.full((batch, chunk), 2, np.int32)
+    args = (c, ctypes.c_void_p(x.ctypes.data), ctypes.c_void_p(bud.ctypes.data), batch, chunk, None, None, None)
+    assert lib.uad_denoise_budgets(*args) == OK  # every environment at every step
+    lib.stub_set_active(c, 0, batch - 1)
+    lib.stub_reset(-1)
+    assert lib.uad_denoise_budgets(*args) == STATE
+    assert lib.stub_log() == b""
+    lib.uad_destroy(c)
