@@ -35,16 +35,34 @@ def gemm_bytes(M, N, K, out_bytes, extra=0):
     return N * K * 2 + M * K * 2 + out_bytes + extra
 
 
-def kernel_bytes(wl, M):
-    """Algorithmic HBM bytes per launch of each kernel class for M tokens of workload wl."""
+# Token rows from which the library computes the adaptive norms' conditioning
+# per distinct flow time of a step (below: per token, once per schedule).
+CLASS_ROWS = 256
+
+
+def conditioning_rows(M, times):
+    """Rows that one launch of the adaptive norms' time MLP and modulation product
+    has to compute, for a schedule's flow times (one row of M tokens per joint
+    step): the distinct times of a step, on average, or every token of every step."""
+    if M < CLASS_ROWS:
+        return M * len(times)
+    return sum(len(set(row)) for row in times) / len(times)
+
+
+def kernel_bytes(wl, M, cond=None):
+    """Algorithmic HBM bytes per launch of each kernel class for M tokens of
+    workload wl; cond: rows of the adaptive norms' conditioning (default M)."""
     s = wl.shape
     d, F, qd, kvd = s.d_model, s.d_ff, s.n_heads * s.head_dim, s.n_kv_heads * s.head_dim
     nqkv = qd + 2 * kvd
     keys = wl.prefix + wl.chunk
     ada = getattr(s, "conditioning", "input") == "adarms"
+    C = M if cond is None or not ada else cond
     out = {} if not ada else {
-        # every norm site's (scale, shift, gate) per token, fp32 out
-        "gemm_mod": gemm_bytes(M, (6 * s.n_layers + 2) * d, d, M * (6 * s.n_layers + 2) * d * 4),
+        # every norm site's (scale, shift, gate) per row, fp32 out
+        "gemm_mod": gemm_bytes(C, (6 * s.n_layers + 2) * d, d, C * (6 * s.n_layers + 2) * d * 4),
+        # the residual stream in, the operand out; the rows' scales and shifts
+        "ada_norm": M * d * (4 + 2) + C * 2 * d * 4,
     }
     return out | {
         "gemm_qkv": gemm_bytes(M, nqkv, d, M * nqkv * 2),
@@ -52,24 +70,25 @@ def kernel_bytes(wl, M):
         "gemm_o": gemm_bytes(M, d, qd, M * d * 4 * 2),
         "gemm_gateup": gemm_bytes(M, 2 * F, d, M * F * 2),
         "gemm_down": gemm_bytes(M, d, F, M * d * 4 * 2),
-        "gemm_time_in": gemm_bytes(M, d, d if ada else 2 * d, M * d * 2),
-        "gemm_time_out": gemm_bytes(M, d, d, M * d * (2 if ada else 4)),
+        "gemm_time_in": gemm_bytes(C, d, d if ada else 2 * d, C * d * 2),
+        "gemm_time_out": gemm_bytes(C, d, d, C * d * (2 if ada else 4)),
     }
 
 
-def kernel_flops(wl, M):
+def kernel_flops(wl, M, cond=None):
     s = wl.shape
     d, F, qd, kvd = s.d_model, s.d_ff, s.n_heads * s.head_dim, s.n_kv_heads * s.head_dim
     keys = wl.prefix + wl.chunk
     ada = getattr(s, "conditioning", "input") == "adarms"
-    return ({"gemm_mod": 2 * M * d * (6 * s.n_layers + 2) * d} if ada else {}) | {
+    C = M if cond is None or not ada else cond
+    return ({"gemm_mod": 2 * C * d * (6 * s.n_layers + 2) * d, "ada_norm": 7 * M * d} if ada else {}) | {
         "gemm_qkv": 2 * M * d * (qd + 2 * kvd),
         "attention": 4 * wl.batch * s.n_heads * wl.chunk * keys * s.head_dim,
         "gemm_o": 2 * M * qd * d,
         "gemm_gateup": 2 * M * d * 2 * F,
         "gemm_down": 2 * M * F * d,
-        "gemm_time_in": 2 * M * (1 if ada else 2) * d * d,
-        "gemm_time_out": 2 * M * d * d,
+        "gemm_time_in": 2 * C * (1 if ada else 2) * d * d,
+        "gemm_time_out": 2 * C * d * d,
     }
 
 
@@ -80,11 +99,16 @@ def step_bytes(wl):
     return W.weight_param_count(s) * 2 + wl.batch * s.n_layers * wl.prefix * s.n_kv_heads * s.head_dim * 2 * 2
 
 
-def step_flops(wl):
+def step_flops(wl, cond=None):
+    """Algorithmic flops of one joint step; cond: rows of the adaptive norms'
+    conditioning per step (default: every token)."""
     import uad_workloads as W
     s = wl.shape
     M = wl.batch * wl.chunk
     att = 4 * wl.batch * s.n_heads * wl.chunk * (wl.prefix + wl.chunk) * s.head_dim * s.n_layers
+    if getattr(s, "conditioning", "input") == "adarms" and cond is not None:
+        n_cond = (6 * s.n_layers + 4) * s.d_model * s.d_model
+        return 2 * M * (W.weight_param_count(s) - n_cond) + 2 * cond * n_cond + att
     return 2 * M * W.weight_param_count(s) + att
 
 
@@ -472,13 +496,8 @@ def measure(ex, wl, budgets, noise, steps_req, warmup_req, sched_reps, U, np, to
     run(max(n, (steps // n) * n))
     prof = U.uad_profile_read(ex.ctx)
     U.uad_profile_enable(ex.ctx, False)
-    kb, kf = kernel_bytes(wl, M), kernel_flops(wl, M)
-    if getattr(s, "conditioning", "input") == "adarms" and M <= 256:
-        # schedule-level conditioning: the time MLP and the modulation GEMM run
-        # once per schedule over the rows of all its n steps
-        kbn, kfn = kernel_bytes(wl, M * n), kernel_flops(wl, M * n)
-        for c in ("gemm_mod", "gemm_time_in", "gemm_time_out"):
-            kb[c], kf[c] = kbn[c], kfn[c]
+    cond = conditioning_rows(M, tg.reshape(n, -1).tolist())
+    kb, kf = kernel_bytes(wl, M, cond), kernel_flops(wl, M, cond)
     per_kernel = {}
     for name, (ms, cnt) in prof.items():
         if cnt == 0:
@@ -516,7 +535,8 @@ def measure(ex, wl, budgets, noise, steps_req, warmup_req, sched_reps, U, np, to
         roof["prefetch_bytes_per_launch"] = 2 * (d * qd + 2 * F * d + d * F + nqkv * d)
     log(f"[bench] {wl.name}: dominant kernel {dom}: {dom_us:.2f} us/launch, {roof['achieved']} {roof['unit']}")
     return {"steps_per_s": sps, "ms_per_step": ms_step, "steps": steps, "warmup": warm, "n": n,
-            "roofline": roof, "kernels": per_kernel, "schedule_time": sched_stats}
+            "roofline": roof, "kernels": per_kernel, "schedule_time": sched_stats,
+            "cond_rows_per_step": cond / n if M < CLASS_ROWS else cond}
 
 
 def device_inputs(wl, U, W, np, torch):
@@ -559,7 +579,7 @@ def batched_leg(name, a, U, W, np, torch):
     comp = time_budget_schedules(ex, wl, budgets, noise, max(3, min(a.sched_reps, 20)), np, torch)
     ex.close()
     torch.cuda.empty_cache()
-    fl = step_flops(wl)
+    fl = step_flops(wl, meas["cond_rows_per_step"])
     ms = meas["ms_per_step"]
     # algorithmic work of a schedule: every environment for as many joint steps
     # as its largest budget (a finished environment does no more work)
@@ -728,13 +748,14 @@ def main():
     sps, ms_step, steps = meas["steps_per_s"], meas["ms_per_step"], meas["steps"]
     roof, per_kernel, sched_stats, n = meas["roofline"], meas["kernels"], meas["schedule_time"], meas["n"]
     sb = step_bytes(wl)
+    fl = step_flops(wl, meas["cond_rows_per_step"])
     copy_gbs = streaming_copy_gbs(torch)
     step_roof = {"bytes_per_step": sb, "achieved_gbs": round(sb / (ms_step * 1e-3) / 1e9, 1),
                  "hbm_frac": round(sb / (ms_step * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
                  "hbm_copy_gbs": round(copy_gbs, 1),
                  "copy_frac": round(sb / (ms_step * 1e-3) / 1e9 / copy_gbs, 4),
-                 "flops_per_step": step_flops(wl),
-                 "mfma_frac": round(step_flops(wl) / (ms_step * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFS, 4)}
+                 "flops_per_step": fl,
+                 "mfma_frac": round(fl / (ms_step * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFS, 4)}
 
     out = {
         "metric": "denoise steps/sec + action-availability latency (ms) at B=1; % HBM/MFMA roofline",

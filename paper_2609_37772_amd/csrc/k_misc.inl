@@ -695,11 +695,11 @@ __global__ __launch_bounds__(256) void time_feat_kernel(const float *__restrict_
 }
 
 hipError_t launch_time_features(const float *t, int M, int m_alloc, int n_steps, int d, const float *freqs,
-                                op_t *te, unsigned *status, hipStream_t s) {
+                                op_t *te, unsigned *status, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   if (M < 1 || m_alloc < M || m_alloc % 16 != 0 || n_steps < 1 || d % 64 != 0) return hipErrorInvalidValue;
   const int rows = n_steps * m_alloc;
-  hipLaunchKernelGGL(time_feat_kernel, dim3(rows, (d / 2 + 255) / 256), dim3(256), 0, s, t, M, m_alloc, rows, d,
-                     freqs, te, status);
+  UAD_LAUNCH(time_feat_kernel, dim3(rows, (d / 2 + 255) / 256), dim3(256), 0, s, ev0, ev1, t, M, m_alloc, rows, d,
+             freqs, te, status);
   return hipGetLastError();
 }
 
@@ -710,9 +710,9 @@ hipError_t launch_time_classes(const float *t, int M, int32_t *cls, float *cls_t
 }
 
 hipError_t launch_class_features(const float *cls_t, const int *n_cls, int M, int d, const float *freqs, op_t *te,
-                                 unsigned *status, hipStream_t s) {
-  hipLaunchKernelGGL(class_feat_kernel, dim3(M, (d / 2 + 255) / 256), dim3(256), 0, s, cls_t, n_cls, d, freqs, te,
-                     status);
+                                 unsigned *status, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+  UAD_LAUNCH(class_feat_kernel, dim3(M, (d / 2 + 255) / 256), dim3(256), 0, s, ev0, ev1, cls_t, n_cls, d, freqs, te,
+             status);
   return hipGetLastError();
 }
 

@@ -110,9 +110,10 @@ struct Carve {
 
 // Kernel classes reported by the measurement hook.
 enum KClass { K_TEMB, K_GEMM_TIME_IN, K_GEMM_TIME_OUT, K_GEMM_QKV, K_ATTENTION, K_GEMM_O, K_GEMM_GATEUP,
-              K_GEMM_DOWN, K_FINAL, K_GEMM_MOD, K_ADA_NORM, K_NCLASS };
+              K_GEMM_DOWN, K_FINAL, K_GEMM_MOD, K_ADA_NORM, K_TIME_CLASSES, K_TIME_FEATURES, K_NCLASS };
 const char *kClassNames[K_NCLASS] = {"temb", "gemm_time_in", "gemm_time_out", "gemm_qkv", "attention",
-                                     "gemm_o", "gemm_gateup", "gemm_down", "final_euler", "gemm_mod", "ada_norm"};
+                                     "gemm_o", "gemm_gateup", "gemm_down", "final_euler", "gemm_mod", "ada_norm",
+                                     "time_classes", "time_features"};
 
 hipEvent_t pool_event(uad_ctx *c) {
   if (!c->ev_pool.empty()) {
@@ -816,9 +817,9 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
       // step's distinct flow times; token m's are row mod_cls[m]
       UAD_CHECK_CLS(K_TEMB, launch_temb_ada(x, nullptr, M, c->Da, d, c->action_in_w, c->action_in_b, c->freqs,
                                             c->a_te, c->h, c->ssq, (int)MA, c->status, s, ea_, eb_));
-      UAD_CHECK_CLS(K_ADA_NORM, launch_time_classes(t, M, c->mod_cls, c->cls_t, c->n_cls, s, ea_, eb_));
-      e = launch_class_features(c->cls_t, c->n_cls, M, d, c->freqs, c->a_te, c->status, s);
-      if (e != hipSuccess) return hip_fail(c, e, "launch_class_features");
+      UAD_CHECK_CLS(K_TIME_CLASSES, launch_time_classes(t, M, c->mod_cls, c->cls_t, c->n_cls, s, ea_, eb_));
+      UAD_CHECK_CLS(K_TIME_FEATURES, launch_class_features(c->cls_t, c->n_cls, M, d, c->freqs, c->a_te, c->status, s,
+                                                           ea_, eb_));
       GemmArgs g{};
       g.status = c->status; g.m_dev = c->n_cls;
       g.M = M; g.m_alloc = (int)MA; g.A = c->a_te; g.W = c->t1_w; g.N = d; g.K = d; g.out = c->a_z; g.ldo = d;
@@ -1042,8 +1043,8 @@ static uad_status enqueue_ada_schedule(uad_ctx *c, hipStream_t s, const GraphKey
     if (e != hipSuccess) return hip_fail(c, e, #call); \
     if (c->prof_on) c->prof_pending.push_back({cls, ea_, eb_}); \
   } while (0)
-  e = launch_time_features(k.t, M, (int)c->m_alloc, k.n_steps, d, c->freqs, c->pre_te, c->status, s);
-  if (e != hipSuccess) return hip_fail(c, e, "launch_time_features");
+  UAD_PRE_CLS(K_TIME_FEATURES, launch_time_features(k.t, M, (int)c->m_alloc, k.n_steps, d, c->freqs, c->pre_te,
+                                                    c->status, s, ea_, eb_));
   GemmArgs g{};
   g.status = c->status;
   g.M = rows; g.m_alloc = rows; g.A = c->pre_te; g.W = c->t1_w; g.N = d; g.K = d; g.out = c->pre_z; g.ldo = d;

@@ -345,14 +345,16 @@ hipError_t launch_temb_ada(const float *x, const float *t, int M, int Da, int d,
                            const float *mod_a0 = nullptr, int mod_ld = 0, op_t *next = nullptr);
 // sinusoidal time features of n_steps x m_alloc rows (rows past M in a step: time 0)
 hipError_t launch_time_features(const float *t, int M, int m_alloc, int n_steps, int d, const float *freqs,
-                                op_t *te, unsigned *status, hipStream_t s);
+                                op_t *te, unsigned *status, hipStream_t s, hipEvent_t ev0 = nullptr,
+                                hipEvent_t ev1 = nullptr);
 // distinct flow times of M tokens: *n_cls of them at cls_t, token m's index at
 // cls[m]; beyond kMaxTimeClasses every token is its own class
 hipError_t launch_time_classes(const float *t, int M, int32_t *cls, float *cls_t, int *n_cls, hipStream_t s,
                                hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // time features of the *n_cls first rows of cls_t (at most M)
 hipError_t launch_class_features(const float *cls_t, const int *n_cls, int M, int d, const float *freqs, op_t *te,
-                                 unsigned *status, hipStream_t s);
+                                 unsigned *status, hipStream_t s, hipEvent_t ev0 = nullptr,
+                                 hipEvent_t ev1 = nullptr);
 // next = fp16(RMS(h) (1 + scale[row]) + shift[row]), row = mod_row[m], fragment order
 hipError_t launch_ada_norm(const float *h, int M, int d, float eps, const float *scale, const float *shift, int mod_ld,
                            const int32_t *mod_row, op_t *next, unsigned *status, hipStream_t s,

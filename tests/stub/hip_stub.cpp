@@ -109,13 +109,15 @@ hipError_t launch_temb(const float *, const float *, int, int, int, const float 
 hipError_t launch_temb_ada(const float *, const float *, int, int, int, const float *, const float *, const float *,
                            op_t *, float *, float *, int, unsigned *, hipStream_t, hipEvent_t, hipEvent_t,
                            const float *, int, op_t *) { return step("temb"); }
-hipError_t launch_time_features(const float *, int, int, int, int, const float *, op_t *, unsigned *, hipStream_t) {
+hipError_t launch_time_features(const float *, int, int, int, int, const float *, op_t *, unsigned *, hipStream_t,
+                                hipEvent_t, hipEvent_t) {
   return step("features");
 }
 hipError_t launch_time_classes(const float *, int, int32_t *, float *, int *, hipStream_t, hipEvent_t, hipEvent_t) {
   return step("classes");
 }
-hipError_t launch_class_features(const float *, const int *, int, int, const float *, op_t *, unsigned *, hipStream_t) {
+hipError_t launch_class_features(const float *, const int *, int, int, const float *, op_t *, unsigned *, hipStream_t,
+                                 hipEvent_t, hipEvent_t) {
   return step("features");
 }
 hipError_t launch_ada_norm(const float *, int, int, float, const float *, const float *, int, const int32_t *, op_t *,

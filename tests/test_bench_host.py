@@ -135,6 +135,29 @@ def test_algorithmic_work_tables():
     assert bench.step_bytes(wl) == W.weight_param_count(s) * 2 + s.n_layers * wl.prefix * s.head_dim * 2 * 2
 
 
+def test_adaptive_norm_conditioning_is_charged_for_the_rows_it_computes():
+    """From 256 token rows on the time MLP and the modulations run on a step's
+    distinct flow times; below that on every token, once per schedule."""
+    import dataclasses
+    wl = dataclasses.replace(W.get_workload("pi05_b1_adarms"), batch=64)
+    s, M = wl.shape, 64 * wl.chunk
+    times = [[1.0] * M, [0.9, 0.75, 0.5] + [0.25] * (M - 3)]
+    assert bench.conditioning_rows(M, times) == 2.5
+    assert bench.conditioning_rows(255, [[1.0] * 255] * 4) == 4 * 255
+    assert bench.conditioning_rows(256, [[1.0] * 256] * 4) == 1
+    n_mod = (6 * s.n_layers + 2) * s.d_model
+    kb, kf = bench.kernel_bytes(wl, M, 2.5), bench.kernel_flops(wl, M, 2.5)
+    assert kf["gemm_mod"] == 2 * 2.5 * s.d_model * n_mod and kf["gemm_time_in"] == 2 * 2.5 * s.d_model ** 2
+    assert kb["gemm_mod"] == n_mod * s.d_model * 2 + 2.5 * s.d_model * 2 + 2.5 * n_mod * 4
+    assert kb["ada_norm"] == M * s.d_model * 6 + 2.5 * 2 * s.d_model * 4
+    assert kf["gemm_qkv"] == bench.kernel_flops(wl, M)["gemm_qkv"]
+    # the step: conditioning weights for 2.5 rows, all others for every token
+    cond = (n_mod + 2 * s.d_model) * s.d_model
+    assert bench.step_flops(wl) - bench.step_flops(wl, 2.5) == 2 * (M - 2.5) * cond
+    pi0 = W.get_workload("pi0_b1")
+    assert bench.kernel_bytes(pi0, 50, 3) == bench.kernel_bytes(pi0, 50) and bench.step_flops(pi0, 3) == bench.step_flops(pi0)
+
+
 def test_more_than_one_gpu_is_refused():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True,
                        timeout=120)
