@@ -1076,13 +1076,6 @@ static hipError_t launch_big_ct(const GemmArgs &g, const ProjRoute &r, hipStream
   return hipGetLastError();
 }
 
-template <int EPI>
-static hipError_t launch_big(const GemmArgs &g, const ProjRoute &r, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-  if constexpr (EPI == EPI_RESID_F32)
-    if (r.cols == 96) return launch_big_ct<EPI, 6>(g, r, s, ev0, ev1);
-  return launch_big_ct<EPI, 8>(g, r, s, ev0, ev1);
-}
-
 // What the rules of routes.h see of a launch.
 static Proj proj_of(int epi, const GemmArgs &g) {
   Proj p{};
@@ -1125,7 +1118,6 @@ hipError_t gemm_init() {
   if (e == hipSuccess) e = ring_attr_ns<EPI_RESID_F32, RingShape<EPI_RESID_F32>::NS, RingShape<EPI_RESID_F32>, true>();
   if (e == hipSuccess) e = ring_attr_ns<EPI_RESID_F32, RingResid96::NS, RingResid96, true>();
   if (e == hipSuccess) e = big_attr<EPI_BIAS_SILU, 8>();
-  if (e == hipSuccess) e = big_attr<EPI_RESID_F32, 8>();
   if (e == hipSuccess) e = big_attr<EPI_RESID_F32, 6>();
   return e;
 }
@@ -1186,9 +1178,9 @@ hipError_t launch_gemm(int epi, const GemmArgs &g, const GemmPlan &p, hipStream_
   }
   if (r.kernel == PROJ_STREAMED) {
     switch (epi) {
-      case EPI_BIAS_SILU: return launch_big<EPI_BIAS_SILU>(g, r, s, ev0, ev1);
-      case EPI_RESID_F32: return launch_big<EPI_RESID_F32>(g, r, s, ev0, ev1);
-      case EPI_MOD: return launch_big<EPI_MOD>(g, r, s, ev0, ev1);
+      case EPI_BIAS_SILU: return launch_big_ct<EPI_BIAS_SILU, 8>(g, r, s, ev0, ev1);
+      case EPI_RESID_F32: return launch_big_ct<EPI_RESID_F32, 6>(g, r, s, ev0, ev1);
+      case EPI_MOD: return launch_big_ct<EPI_MOD, 8>(g, r, s, ev0, ev1);
     }
     return hipErrorInvalidValue;
   }

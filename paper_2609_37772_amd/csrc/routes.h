@@ -46,10 +46,9 @@ struct ProjRoute {
 // Output tiles of rows x cols.
 inline int tiles_of(const Proj &g, int rows, int cols) { return (g.M + rows - 1) / rows * (g.N / cols); }
 
-// Residual projections: 96-column tiles of the register-streamed kernel when
-// they need fewer 16 x 16 output tiles per CU than 128-column ones (1536
-// wide, 2048 rows: 256 tiles of 48 instead of 192 tiles of 64 with 64 CUs
-// idle).
+// Residual projections: 96-column tiles when they need fewer 16 x 16 output
+// tiles per CU than 128-column ones (1536 wide, 2048 rows: 256 tiles of 48
+// instead of 192 tiles of 64 with 64 CUs idle).
 inline bool resid_prefers_96(const Proj &g) {
   auto per_cu = [&](int ct) {
     return (tiles_of(g, 128, 16 * ct) + g.n_cu - 1) / g.n_cu * ct;
@@ -57,9 +56,8 @@ inline bool resid_prefers_96(const Proj &g) {
   return g.N % 96 == 0 && per_cu(6) < per_cu(8);
 }
 
-// Residual projections on 128 x 128 ring tiles: from 2560 rows, below that once
-// the tiles fill half the CUs (the register-streamed kernel's k-halves win with
-// fewer: 80-104 tiles).
+// Residual projections on 128 x 128 ring tiles (after the 64 x 64 ones and the
+// splits): from 2560 rows, below that once the tiles fill half the CUs.
 inline bool ring_resid_fits(const Proj &g) {
   return (g.M >= 2560 || 2 * tiles_of(g, 128, 128) >= g.n_cu) && g.N % 128 == 0 && !g.second &&
          !resid_prefers_96(g);
@@ -107,10 +105,11 @@ inline int ring_tile_geglu(const Proj &g) {
 
 // The residual projections where 96-column tiles are preferred, on the
 // 128 x 96 ring from 1024 rows once its tiles fill 3/4 of the CUs, or with
-// a long K.  1536-wide expert, same-machine (us): at 2048 and 1536 rows O 22.4 /
-// 21.8 -> 21.8 / 21.1, down 65.2 / 64.8 -> 63.7 / 62.4; at 1024 rows (128
-// tiles) down (K = 6144) 60.1 -> 58.1 but O (K = 1536) 18.0 -> 19.6, where
-// the register-streamed kernel's k-halves keep the short K ahead.
+// a long K.  1536-wide expert, same-machine against the register-streamed kernel
+// (us): at 2048 and 1536 rows O 22.4 / 21.8 -> 21.8 / 21.1, unsplit down 65.2 /
+// 64.8 -> 63.7 / 62.4; at 1024 rows (128 tiles) down (K = 6144) 60.1 -> 58.1 but O
+// (K = 1536) 18.0 -> 19.6.  Short K below 3/4 of the CUs: the 64 x 64 tiles up to
+// two a CU, then the register-streamed kernel (1345 to 1408 rows at 1536 columns).
 inline bool ring96_fits(const Proj &g) {
   return g.M >= 1024 && (4 * tiles_of(g, 128, 96) >= 3 * g.n_cu || g.K >= 4096) && resid_prefers_96(g) &&
          !g.second && g.K / kTileK >= 1;
@@ -139,23 +138,21 @@ inline int resid_ring64(const Proj &g) {
   return (size_t)t * kx * 64 * 64 * sizeof(float) <= g.kx_ws_bytes ? kx : 0;
 }
 
-// Split-K of the batched residual projections on the ring: kx = CUs / tiles
-// (at most 4) copies of the tile grid, each over an equal k-range of at least
-// 16 k-blocks, when the tiles fill at most half the CUs and are at least the
-// 90 the batched kernels need (64 with K >= 4096); 1 (no split) otherwise, or
-// when the context gave no workspace or it is too small.  Same-machine A/B, ms
-// per joint step: 1024-wide expert at 32 environments (1600 rows, 104 tiles)
-// 3.130 -> 2.663 (down 49.8 -> 29.1 us, O 25.3 -> 20.4 us), 1536-wide expert
-// at 8 environments (1024 rows, 128 tiles of 96 columns) 4.450 -> 3.893
-// (down 58.0 -> 36.3 us); below 90 tiles the small-M kernel kept O and the
-// time MLP ahead (1000 rows: O 16.8 -> 18.0 us split four ways) while down
-// still won (28.1 -> 23.4 us), and at 400-600 rows both lost.  Tiles filling
-// more than half the CUs (one workgroup per CU) split two ways when K >= 4096,
-// two co-resident workgroups per CU instead of one: down of the 1536-wide
-// expert at 16 environments (256 tiles of 128 x 96) 65.5 -> 54.3 us, step
-// 5.595 -> 5.333 ms; of the 1024-wide at 64 environments (200 tiles) 45.3 ->
-// 43.4 us; with O and the time MLP (K = 1536-2048) split as well the step
-// lost (O 22.1 -> 24.3 us, 26.9 -> 30.3 us).
+// Split-K of the residual projections on 128-row ring tiles: kx = CUs / tiles (at
+// most 4) copies of the tile grid, each over an equal k-range of at least 16
+// k-blocks, when the tiles fill at most half the CUs and are at least 64 (90 with
+// K < 4096); 1 (no split) otherwise, or when the context gave no workspace or it
+// is too small.  With K < 4096 the 64 x 64 tiles come first, so that only widths
+// without them (288, 480 and the like: a multiple of 96 but not of 64) split
+// here.  Same-machine: down (K = 4096) of the 1024-wide expert at 1600 rows (104
+// tiles) 49.8 -> 29.1 us, at 1000 rows 28.1 -> 23.4; of the 1536-wide (K = 6144)
+// at 1024 rows (128 tiles of 96 columns) 58.0 -> 36.3.  Tiles filling more than
+// half the CUs (one workgroup per CU) split two ways when K >= 4096, two
+// co-resident workgroups per CU instead of one: down of the 1536-wide expert at
+// 16 environments (256 tiles of 128 x 96) 65.5 -> 54.3 us, step 5.595 -> 5.333
+// ms; of the 1024-wide at 64 environments (200 tiles) 45.3 -> 43.4 us; with O and
+// the time MLP (K = 1536-2048) split as well the step lost (O 22.1 -> 24.3 us,
+// 26.9 -> 30.3 us).
 inline int resid_ksplit(const Proj &g, int cols) {
   if (g.second || g.M < kBigM || g.N % cols != 0) return 1;
   const int tiles = tiles_of(g, 128, cols);
@@ -185,25 +182,26 @@ inline int geglu_tile_rows(const Proj &g) {
   return 128;
 }
 
-// Whether a launch takes the k-halves (KS = 2): its tiles fill at most one
-// round of CUs (one 4-wave workgroup per CU would leave every SIMD a single
-// wave), K >= 1536 and the k-blocks split evenly.  Not for the modulations.
-// Measured: down of the 1536-wide expert (2048 rows) 67.7 -> 65.2 us, O and down
-// of the 1024-wide at 3200 rows -2%; at K = 1024 (time-MLP out) 18.8 -> 19.6 us,
-// hence the K bound.
+// Whether a launch of the register-streamed kernel takes the k-halves (KS = 2):
+// its tiles fill at most one round of CUs (one 4-wave workgroup per CU would leave
+// every SIMD a single wave), K >= 1536 and the k-blocks split evenly.  Not for the
+// modulations.  Measured on launches that are the ring's now: down of the
+// 1536-wide expert (2048 rows) 67.7 -> 65.2 us, O and down of the 1024-wide at
+// 3200 rows -2%; at K = 1024 (time-MLP out) 18.8 -> 19.6 us, hence the K bound.
 inline bool big_khalves(const Proj &g, int cols) {
   return g.epi != EPI_MOD && tiles_of(g, 128, cols) <= g.n_cu && g.K >= 1536 && (g.K / kTileK) % 2 == 0;
 }
 
-// The batched kernel serves M >= kBigM when the columns divide into its tiles,
-// no second operand is used and there are enough output tiles to fill the
-// chip: each tile runs its whole K serially in one workgroup, so with few
-// tiles (and long K) the small-M kernel, which splits K over waves, is
-// faster.  Threshold from a sweep of both kernels over 200..3200 rows and
-// the projection shapes of the 1024- and 1536-wide experts (the rule picks
-// the faster kernel in 49 of 50 cases, the miss by 6%).
+// The register-streamed kernel: the time MLP in, the modulations, and the
+// residual projections on 96-column tiles that the ring leaves, from kBigM rows
+// when there are enough output tiles to fill the chip: each tile runs its whole K
+// serially in one workgroup, so with few tiles (and long K) the small-M kernel,
+// which splits K over waves, is faster.  The threshold is from a sweep over
+// 200..3200 rows when every batched projection ran here (the faster kernel in 49
+// of 50 cases, the miss by 6%).
 inline bool big_ok(const Proj &g) {
   if (g.epi == EPI_QKV || g.epi == EPI_GEGLU || g.M < kBigM || g.N % 128 != 0) return false;
+  if (g.epi == EPI_RESID_F32 && !resid_prefers_96(g)) return false;
   const int tiles = tiles_of(g, 128, 128);
   return tiles >= 90 && !(tiles < 128 && g.K > 4096);
 }

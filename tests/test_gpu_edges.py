@@ -310,14 +310,14 @@ def test_batched_final_projection_ragged_rows_and_outputs(gpu, Da):
                          ids=["w1024_1600rows", "w1024_1100rows_3way", "w1536_1024rows", "w1536_1000rows",
                               "w1024_3200rows_down", "w1536_2048rows_down"])
 def test_split_k_residual_projections(gpu, width, B, H):
-    """Residual projections split over K (tiles filling at most half the CUs:
-    1600 rows x 1024 columns = 104 tiles of 128 x 128, two ways; 1100 rows =
-    72 tiles, down (K = 4096) three ways over uneven k-ranges of 42 and 43
-    blocks; 1024 and 1000 rows x 1536 = 128 tiles of 128 x 96, two ways; the
-    1600-, 1100- and 1000-row cases end in a ragged row panel), and only down
-    (K >= 4096), two ways, where the tiles fill more than half the CUs (3200
-    rows x 1024 = 200 tiles, 2048 rows x 1536 = 256 tiles of 96 columns),
-    2 layers of the pi0-scale and large experts' widths:
+    """Down (K >= 4096) split over K: tiles filling at most half the CUs (1600
+    rows x 1024 columns = 104 tiles of 128 x 128, two ways; 1100 rows = 72
+    tiles, three ways over uneven k-ranges of 42 and 43 blocks; 1024 and 1000
+    rows x 1536 = 128 tiles of 128 x 96, two ways; the 1600-, 1100- and 1000-row
+    cases end in a ragged row panel) and more (3200 rows x 1024 = 200 tiles,
+    2048 rows x 1536 = 256 tiles of 96 columns, two ways).  O and the time MLP
+    out run whole, on 64 x 64 tiles in the first four cases.  2 layers of the
+    pi0-scale and large experts' widths:
     step-0 velocities of every environment against the oracle, the same step
     24 times more bit for bit (the partials are added in split order whatever
     the arrival order), then a whole schedule's released actions and final

@@ -60,3 +60,27 @@ def test_prefix_pack_launches_cover_any_size(n_env, hkv, n_blk, launches):
     spans = sorted((e0, q0) for e0, _, q0, _ in got)
     assert len(set(spans)) == launches and max(e0 + e for e0, e, _, _ in got) == n_env
     assert max(q0 + b for _, _, q0, b in got) == n_blk
+
+
+@pytest.mark.parametrize("n_cu", [32, 64, 128, 256])
+def test_residual_routes_are_the_compiled_ones(n_cu):
+    """Every residual route has its kernel, and every kernel a route."""
+    seen = set()
+    for d in (256, 288, 384, 1024, 1536, 1920, 2048):
+        for rows in (*range(1, 400, 7), *range(400, 6400, 31)):
+            for K in (32, 1024, 1536, 2048, 4096, 6144):
+                seen.add(R.projection(R.RESID, rows, d, K, n_cu)[:3])
+    ring = {(R.RING, 64, 64), (R.RING, 128, 96), (R.RING, 128, 128)}
+    assert seen == ring | {(R.SMALL, 0, 0), (R.STREAMED, 128, 96)}
+
+
+@pytest.mark.parametrize("width,rows,o,down", [  # the sizes of the split-K cases of test_gpu_edges
+    (1024, 1600, (64, 64, 1), (128, 128, 2)), (1024, 1100, (64, 64, 1), (128, 128, 3)),
+    (1536, 1024, (64, 64, 1), (128, 96, 2)), (1536, 1000, (64, 64, 1), (128, 96, 2)),
+    (1024, 3200, (128, 128, 1), (128, 128, 2)), (1536, 2048, (128, 96, 1), (128, 96, 2)),
+])
+def test_split_k_sizes(width, rows, o, down):
+    q_dim, F = (2048, 4096) if width == 1024 else (1536, 6144)
+    for K, want in ((width, o), (q_dim, o), (F, down)):  # time MLP out, O, down
+        r = R.projection(R.RESID, rows, width, K)
+        assert r[0] == R.RING and r[1:4] == want
