@@ -97,10 +97,11 @@ def test_adarms_time_changes_velocity(gpu):
 
 @pytest.mark.parametrize("batch", [8, 24])
 def test_adarms_batched_sampled_envs(gpu, batch):
-    """8 / 24 environments, M = 400 / 1200 rows: the batched projection kernel
-    serves the time MLP, the modulation GEMM and the gated residual epilogues
-    (at 1200 rows the embedding kernel also takes 16 tokens per workgroup).
-    Sampled environments against the oracle run alone: one teacher-forced
+    """8 / 24 environments, M = 400 / 1200 rows: conditioning per distinct flow
+    time, norms as passes of their own.  The time MLP runs on the small-M kernel,
+    the modulations on the register-streamed one; at 400 rows O on the small-M
+    kernel and down on split 64 x 64 ring tiles, at 1200 on 64 x 64 and split
+    128 x 128 ones (the embedding kernel also takes 16 tokens per workgroup).  Sampled environments against the oracle run alone: one teacher-forced
     step, then the free-running UAD schedule."""
     c = case("pi05_b1_adarms", batch=batch)
     B, H = c.budgets.shape

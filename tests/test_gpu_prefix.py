@@ -27,11 +27,12 @@ def offset_by_one(a):
 
 # head dim, KV heads, batch, chunk, prefix: ragged 32-key blocks, one key, whole
 # blocks, no prefix, and 9000 keys x 2 heads x 256 fp32 (over half the 32 MiB
-# staging workspace: an environment goes up in runs of 32-key blocks)
+# staging workspace: an environment goes up in runs of 32-key blocks); 520 heads:
+# one fp32 block exceeds the workspace (a buffer of the call's own)
 @pytest.mark.parametrize("hd,hkv,B,H,P", [(64, 4, 2, 5, 33), (128, 2, 3, 16, 64), (256, 1, 2, 7, 1), (64, 2, 1, 3, 0),
-                                           (256, 2, 1, 4, 9000)])
+                                           (256, 2, 1, 4, 9000), (256, 520, 1, 3, 33)])
 def test_prefix_sources_agree(gpu, hd, hkv, B, H, P):
-    shape = W.ModelShape(2, 128, 4, hkv, hd, 256, 7)
+    shape = W.ModelShape(2, 128, max(4, hkv), hkv, hd, 256, 7)
     wl = dataclasses.replace(W.get_workload("tiny"), shape=shape, batch=B, chunk=H, prefix=P)
     weights = W.make_weights(wl)
     g = np.random.default_rng(hd + P)

@@ -84,3 +84,31 @@ def test_split_k_sizes(width, rows, o, down):
     for K, want in ((width, o), (q_dim, o), (F, down)):  # time MLP out, O, down
         r = R.projection(R.RESID, rows, width, K)
         assert r[0] == R.RING and r[1:4] == want
+
+
+@pytest.mark.parametrize("d,heads,hd,F,rows,time_mlp,o,down", [  # the sizes of test_gpu_adarms_batched.WIDE
+    (1024, 8, 256, 4096, 3200, (R.STREAMED, 128, 128, 1, 0), (R.RING, 128, 128, 1, 0), (R.RING, 128, 128, 2, 0)),
+    (1536, 12, 128, 6144, 1408, (R.STREAMED, 128, 128, 1, 1), (R.STREAMED, 128, 96, 1, 1), (R.RING, 128, 96, 2, 0)),
+    (1536, 4, 64, 2048, 1397, (R.STREAMED, 128, 128, 1, 1), (R.STREAMED, 128, 96, 1, 0), (R.STREAMED, 128, 96, 1, 1)),
+    (1536, 12, 128, 6144, 2048, (R.STREAMED, 128, 128, 1, 1), (R.RING, 128, 96, 1, 0), (R.RING, 128, 96, 2, 0)),
+])
+def test_batched_adaptive_norm_sizes(d, heads, hd, F, rows, time_mlp, o, down):
+    assert R.projection(R.SILU, rows, d, d) == time_mlp
+    assert R.projection(R.MOD, rows, 14 * d, d)[0] == R.STREAMED
+    assert R.projection(R.RESID, rows, d, heads * hd, gate=True, mod_row=True) == o
+    assert R.projection(R.RESID, rows, d, F, gate=True, mod_row=True) == down
+
+
+def test_pi05_batched_sizes():
+    """The 8- and 24-environment cases of test_gpu_adarms."""
+    for rows, o, down in ((400, (R.SMALL, 0, 0, 1), (R.RING, 64, 64, 4)), (1200, (R.RING, 64, 64, 1), (R.RING, 128, 128, 3))):
+        assert R.projection(R.SILU, rows, 1024, 1024)[0] == R.SMALL
+        assert R.projection(R.MOD, rows, 110 * 1024, 1024)[0] == R.STREAMED
+        assert R.projection(R.RESID, rows, 1024, 2048, gate=True, mod_row=True)[:4] == o
+        assert R.projection(R.RESID, rows, 1024, 4096, gate=True, mod_row=True)[:4] == down
+
+
+def test_split_short_k_sizes():
+    """A width without 64 x 64 tiles: the short K splits too (test_gpu_ring_tiles)."""
+    for K in (288, 1024):
+        assert R.projection(R.RESID, 3750, 288, K)[:4] == ((R.RING, 128, 96, 2) if K == 1024 else (R.SMALL, 0, 0, 1))
