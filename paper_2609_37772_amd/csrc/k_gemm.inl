@@ -47,8 +47,11 @@ __device__ __forceinline__ float silu(float z) {
 // accumulated value v (and, for GeGLU, the matching up-projection value u);
 // rs is the row's rstd (1 when unused).  EPI_RESID_F32 takes the residual h0,
 // the next operand's scale sc and the branch gate gt, and must be called by
-// the 16 lanes of a row together (sum of squares via shuffles).
-template <int EPI>
+// the 16 lanes of a row together (sum of squares via shuffles).  BY_CLASS
+// (EPI_MOD): modulations only, no operands of a step's norms.  (A test of the
+// shift operands' pointer and their address from two 32-bit factors cost every
+// element: 98.8 -> 101.6 us at 240 rows, 26624 columns, K = 1024.)
+template <int EPI, bool BY_CLASS>
 __device__ __forceinline__ void epilogue_elem(const GemmArgs &g, int row, bool row_ok, int tile, int ln, float v,
                                               float u, float rs, float h0, float sc, float gt, unsigned &bad) {
   if (EPI == EPI_MOD) {
@@ -61,13 +64,12 @@ __device__ __forceinline__ void epilogue_elem(const GemmArgs &g, int row, bool r
       ((float *)g.out)[(size_t)row * g.ldo + col] = mv;
       const int per_layer = 6 * g.d_model;
       const int l = col / per_layer;
-      if (l < g.n_layers) {
+      if (!BY_CLASS && l < g.n_layers) {
         const int r6 = col - l * per_layer;
         const int part = r6 / g.d_model, j = r6 - part * g.d_model;
         const int KBd = g.d_model / kTileK;
-        if (g.mod_shift_ops && (part == 1 || part == 4))
-          store_op(g.mod_shift_ops + (size_t)(2 * l + (part == 4)) * g.m_alloc * g.d_model + afrag_index(row, j, KBd),
-                   mv, bad);
+        if (part == 1 || part == 4)
+          store_op(g.mod_shift_ops + (size_t)(2 * l + (part == 4)) * g.shift_stride + afrag_index(row, j, KBd), mv, bad);
         else if (part == 0 && l == 0 && g.next)
           store_op(g.next + afrag_index(row, j, KBd), g.h_in[(size_t)row * g.d_model + j] * (1.0f + mv), bad);
       }
@@ -346,7 +348,7 @@ __global__ __launch_bounds__(512) void gemm_kernel(GemmArgs g) {
       }
     }
     const float rs = (!DUAL && kRstd && g.use_rstd && row_ok) ? rstd_s[rl] : 1.0f;
-    epilogue_elem<EPI>(g, row, row_ok, tile0 + t, ln, v, u, rs, h0, sc, gt, bad);
+    epilogue_elem<EPI, MAP && EPI == EPI_MOD>(g, row, row_ok, tile0 + t, ln, v, u, rs, h0, sc, gt, bad);
   }
   flush_range(g.status, bad);
 }
@@ -630,8 +632,7 @@ __device__ __forceinline__ void big_epilogue(const GemmArgs &g, f32x4 (&acc)[TA]
           const int r6 = col - l * per_layer;
           const int part = r6 / g.d_model, jc = r6 - part * g.d_model;
           if (g.mod_shift_ops && (part == 1 || part == 4))
-            st4h(g.mod_shift_ops + (size_t)(2 * l + (part == 4)) * g.m_alloc * g.d_model + afrag_index(row, jc, KBd),
-                 mv, bad);
+            st4h(g.mod_shift_ops + (size_t)(2 * l + (part == 4)) * g.shift_stride + afrag_index(row, jc, KBd), mv, bad);
         }
       }
     }

@@ -849,7 +849,7 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
       GemmArgs gm{};
       gm.status = c->status;
       gm.M = M; gm.m_alloc = (int)MA; gm.A = c->a_te; gm.W = c->w_mod; gm.N = n_mod; gm.K = d; gm.out = c->mod; gm.ldo = n_mod;
-      gm.bias = c->b_mod; gm.mod_shift_ops = c->mod_shift_ops; gm.h_in = c->h;
+      gm.bias = c->b_mod; gm.mod_shift_ops = c->mod_shift_ops; gm.shift_stride = MA * d; gm.h_in = c->h;
       gm.d_model = d; gm.n_layers = c->L; gm.next = c->a_n;
       UAD_CHECK_CLS(K_GEMM_MOD, launch_gemm(EPI_MOD, gm, plan_gemm(EPI_MOD, M, n_mod, d), s, ea_, eb_));
     }
@@ -1058,7 +1058,7 @@ static uad_status enqueue_ada_schedule(uad_ctx *c, hipStream_t s, const GraphKey
   GemmArgs gm{};
   gm.status = c->status;
   gm.M = rows; gm.m_alloc = rows; gm.A = c->pre_te; gm.W = c->w_mod; gm.N = c->n_mod; gm.K = d; gm.out = c->pre_mod;
-  gm.ldo = c->n_mod; gm.bias = c->b_mod; gm.mod_shift_ops = c->pre_shift;
+  gm.ldo = c->n_mod; gm.bias = c->b_mod; gm.mod_shift_ops = c->pre_shift; gm.shift_stride = (size_t)rows * d;
   gm.h_in = nullptr; gm.next = nullptr; gm.d_model = d; gm.n_layers = c->L;
   UAD_PRE_CLS(K_GEMM_MOD, launch_gemm(EPI_MOD, gm, plan_gemm(EPI_MOD, rows, c->n_mod, d), s, ea_, eb_));
 #undef UAD_PRE_CLS

@@ -199,7 +199,8 @@ struct GemmArgs {
     };
     struct {  // EPI_MOD: fp32 [M][N] row-major (out), the shifts as fp16 operands, and
               // the first attention norm's operand fp16(h * (1 + scale))
-      op_t *mod_shift_ops;    // [L][2][m_alloc*d] fragment order (nullptr: not kept)
+      op_t *mod_shift_ops;    // [L][2][shift_stride] fragment order (nullptr: not kept)
+      size_t shift_stride;    // elements per shift operand
       const float *h_in;      // [M][d] residual stream
       int d_model, n_layers;
     };
