@@ -509,7 +509,7 @@ static hipError_t launch_hd(const AttnArgs &a, int batch, hipStream_t s, hipEven
     UAD_LAUNCH((attn_combine_kernel<4, 1>), cgrid, dim3(64), 0, s, none, ev1, ac, HD);
   else if (a.splits <= 8)
     UAD_LAUNCH((attn_combine_kernel<8, 1>), cgrid, dim3(64), 0, s, none, ev1, ac, HD);
-  else if (a.splits <= 16)
+  else if (a.splits <= kAttnMerge16)
     UAD_LAUNCH((attn_combine_kernel<16, 4>), cgrid, dim3(256), 0, s, none, ev1, ac, HD);
   else if (a.splits <= kAttnMaxSplits)
     UAD_LAUNCH((attn_combine_kernel<32, 4>), cgrid, dim3(256), 0, s, none, ev1, ac, HD);

@@ -265,6 +265,7 @@ int for_pack_launches(int n_env, int n_kv_heads, int n_blk, F f) {
 // buffer), 2 * NB * 32 * HD * 4 bytes of LDS.
 constexpr int attn_chunk_blocks(int head_dim) { return head_dim == 256 ? 2 : 4; }
 constexpr int kAttnMaxSplits = 32;  // split-KV partials the merge accepts
+constexpr int kAttnMerge16 = 16;    // ... that its instance for up to 16 holds
 
 // CUs the attention launch has to leave free for the weight read-ahead of its
 // extra workgroups (below that the read-ahead is not issued).
@@ -274,6 +275,7 @@ constexpr int kReadAheadMinCus = 32;
 struct AttnSizes {
   int n_cu, group, n_kv_heads, head_dim;  // group: query heads per KV head
   int B, H, n_blocks;
+  bool small_gateup;  // gate/up runs on the small-M kernel (attn_splits)
   int qblocks() const { return (group * H + 63) / 64; }  // 64-row query blocks of an (environment, KV head)
 };
 
@@ -305,6 +307,19 @@ inline int attn_splits_max(const AttnSizes &a) {
 // per split (longer splits run as two key groups inside the workgroup), as many
 // splits as leave kReadAheadMinCus CUs to the read-ahead, without which gate/up
 // streams its weights from HBM (~27.5 instead of ~22 us at 300-850 rows).
+//
+// Gate/up on the small-M kernel (up to 128 rows of the 1024-wide expert, every
+// adaptive-norm step by token) does not gain that: one chunk, else two, per split
+// where the grid fits one round of the CUs, whether or not any are left.  Not one
+// chunk past 16 splits, where the merge takes its longer form.  Same-machine, us
+// per joint step of 4 layers, as above -> so:
+//   adaptive norms  4 x 60 + 816  420.1 -> 413.8 (6 splits -> 7)   5 x 48 + 900  422.4 -> 414.0 (6 -> 8)
+//                   2 x 60 + 816  304.5 -> 300.8 (7 -> 14)         8 x 12 + 900  277.8 -> 272.8 (8 -> 15)
+//                   5 x 36 + 256  356.0 -> 349.7 (3 -> 5)          4 x 32 + 816  309.2 -> 303.1 (7 -> 14)
+//   input           2 x 56 + 700  223.4 -> 220.0 (6 -> 12)         4 x 32 + 640  229.7 -> 226.4 (6 -> 11)
+// Over one round both lose (adaptive norms, one chunk: 3 x 44 + 816 312 -> 334, 6 x 20 +
+// 816 309 -> 327; two: 5 x 50 + 1000 435 -> 461), as do 17 splits (1 x 50 + 1000 213.7 ->
+// 215.8).
 // Same-machine, 1024-wide expert of 6 layers, us per joint step, 816 + 50 keys
 // (28 blocks), by splits:
 //   environments   14     10      7      5      4      3      2      1
@@ -321,9 +336,13 @@ inline int attn_splits(const AttnSizes &a, int *bps) {
   auto grid = [&](int sp) { return 8L * (((long)a.B * a.n_kv_heads * sp + 7) / 8) * a.qblocks(); };
   const int most = attn_splits_max(a);
   int sp = std::min(most, (a.n_blocks + nb - 1) / nb);
-  if (2 * grid(sp) > a.n_cu) {
+  // whole chunks per split in one round, for which the read-ahead is given up
+  auto one_round = [&](int chunks) {
+    return a.small_gateup && sp * chunks * nb >= a.n_blocks && grid(sp) <= a.n_cu;
+  };
+  if (2 * grid(sp) > a.n_cu && !(one_round(1) && sp <= kAttnMerge16)) {
     sp = std::min(most, (a.n_blocks + 2 * nb - 1) / (2 * nb));
-    while (sp > 1 && grid(sp) > a.n_cu - kReadAheadMinCus) --sp;
+    while (sp > 1 && grid(sp) > a.n_cu - kReadAheadMinCus && !one_round(2)) --sp;
   }
   *bps = (a.n_blocks + sp - 1) / sp;
   return (a.n_blocks + *bps - 1) / *bps;

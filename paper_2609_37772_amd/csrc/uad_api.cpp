@@ -126,8 +126,8 @@ hipEvent_t pool_event(uad_ctx *c) {
   return e;
 }
 
-AttnSizes attn_sizes(const uad_ctx *c, int B, int H, int n_blocks) {
-  return AttnSizes{c->n_cu, c->Hq / c->Hkv, c->Hkv, c->hd, B, H, n_blocks};
+AttnSizes attn_sizes(const uad_ctx *c, int B, int H, int n_blocks, bool small_gateup = false) {
+  return AttnSizes{c->n_cu, c->Hq / c->Hkv, c->Hkv, c->hd, B, H, n_blocks, small_gateup};
 }
 
 // Split-KV partial rows (x head_dim) that a call with B environments, chunk H
@@ -860,7 +860,11 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
     at.q = c->q; at.ldq = c->q_dim; at.s_alloc = c->s_alloc; at.n_keys = c->prefix_len + H;
     at.chunk = H; at.n_heads = c->Hq; at.n_kv_heads = c->Hkv; at.group = c->Hq / c->Hkv;
     at.rows = at.group * H; at.rows_pad = (at.rows + 63) / 64 * 64;
-    at.splits = attn_splits(attn_sizes(c, B, H, (c->prefix_len + H + 31) / 32), &at.blocks_per_split);
+    Proj gateup{};
+    gateup.n_cu = c->n_cu; gateup.epi = EPI_GEGLU; gateup.M = M; gateup.N = 2 * F; gateup.K = d;
+    gateup.second = c->ada && !by_class;
+    at.splits = attn_splits(attn_sizes(c, B, H, (c->prefix_len + H + 31) / 32,
+                                       route_projection(gateup).kernel == PROJ_SMALL), &at.blocks_per_split);
     if (!scratch && attn_part_rows(c, B, H, c->prefix_len) > c->attn_part_elems)
       return fail(c, UAD_E_SHAPE, "split-KV partials exceed the workspace sized at uad_create");
     at.qblocks = (at.rows + 63) / 64; at.n_eh = B * c->Hkv;

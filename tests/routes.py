@@ -21,8 +21,8 @@ extern "C" void projection(const int *a, int *out) {  // n_cu epi M N K q_dim se
   const ProjRoute r = route_projection(p);
   out[0] = r.kernel; out[1] = r.rows; out[2] = r.cols; out[3] = r.kx; out[4] = r.halves;
 }
-extern "C" void attention(const int *a, int *out) {  // n_cu group n_kv_heads head_dim B H keys
-  AttnSizes s{a[0], a[1], a[2], a[3], a[4], a[5], (a[6] + 31) / 32};
+extern "C" void attention(const int *a, int *out) {  // n_cu group n_kv_heads head_dim B H keys small_gateup
+  AttnSizes s{a[0], a[1], a[2], a[3], a[4], a[5], (a[6] + 31) / 32, a[7] != 0};
   const int nb = attn_chunk_blocks(s.head_dim);
   out[0] = attn_splits(s, &out[1]);
   const int groups = s.B * s.n_kv_heads * out[0];
@@ -62,9 +62,9 @@ def projection(epi, M, N, K, n_cu=256, q_dim=0, second=False, gate=False, mod_ro
     return _call("projection", (n_cu, epi, M, N, K, q_dim, second, gate, mod_row, scale_next), 5)
 
 
-def attention(heads, n_kv_heads, head_dim, B, H, keys, n_cu=256):
+def attention(heads, n_kv_heads, head_dim, B, H, keys, n_cu=256, small_gateup=False):
     """(key splits, 32-key blocks of each, two key groups, most splits)."""
-    return _call("attention", (n_cu, heads // n_kv_heads, n_kv_heads, head_dim, B, H, keys), 4)
+    return _call("attention", (n_cu, heads // n_kv_heads, n_kv_heads, head_dim, B, H, keys, small_gateup), 4)
 
 
 def pack_launches(n_env, n_kv_heads, n_blk):

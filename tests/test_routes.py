@@ -30,8 +30,31 @@ def test_ring_tile_sizes(rows, gateup, qkv, o, down):
     (64, 4, 4, 40, 20, 10 * 32 - 1, 1), (256, 2, 1, 40, 16, 25 * 32 - 7, 5), (128, 2, 1, 30, 16, 70 * 32 - 3, 7),
 ])
 def test_two_key_group_sizes(hd, heads, hkv, B, H, keys, splits):
-    got, per, two, most = R.attention(heads, hkv, hd, B, H, keys)
+    small = R.projection(R.GEGLU, B * H, 2 * 256, 128)[0] == R.SMALL
+    got, per, two, most = R.attention(heads, hkv, hd, B, H, keys, small_gateup=small)
     assert two == 1 and got == splits <= most and got * per >= (keys + 31) // 32
+
+
+@pytest.mark.parametrize("B,H,prefix,small,other", [  # eight query heads of 256 on one KV head
+    (4, 60, 816, 7, 6), (2, 60, 816, 14, 7), (8, 12, 900, 15, 8), (5, 36, 256, 5, 3), (2, 56, 700, 12, 6),
+    (3, 44, 816, 7, 7), (1, 50, 1000, 9, 9), (5, 50, 1000, 6, 6), (1, 50, 816, 14, 14),
+])
+def test_key_splits_go_by_what_gateup_gains(B, H, prefix, small, other):
+    """CUs are left to the weight read-ahead only where gate/up gains by it."""
+    for flag, want in ((True, small), (False, other)):
+        splits, per, _, most = R.attention(8, 1, 256, B, H, prefix + H, small_gateup=flag)
+        assert splits == want <= most and splits * per >= (prefix + H + 31) // 32
+
+
+@pytest.mark.parametrize("n_cu", [32, 64, 128, 256])
+def test_key_splits_fit_the_workspace(n_cu):
+    for heads, hkv, hd in ((8, 1, 256), (12, 2, 128), (4, 4, 64)):
+        for B in (1, 2, 3, 5, 8, 17, 64):
+            for H in (1, 10, 37, 64):
+                for keys in range(H, 1200, 53):
+                    for flag in (False, True):
+                        splits, per, _, most = R.attention(heads, hkv, hd, B, H, keys, n_cu, flag)
+                        assert 1 <= splits <= most <= 32 and (splits - 1) * per < (keys + 31) // 32 <= splits * per
 
 
 @pytest.mark.parametrize("n_cu", [32, 64, 128, 256])
