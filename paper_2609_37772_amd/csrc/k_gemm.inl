@@ -633,6 +633,8 @@ __device__ __forceinline__ void big_epilogue(const GemmArgs &g, f32x4 (&acc)[TA]
           const int part = r6 / g.d_model, jc = r6 - part * g.d_model;
           if (g.mod_shift_ops && (part == 1 || part == 4))
             st4h(g.mod_shift_ops + (size_t)(2 * l + (part == 4)) * g.shift_stride + afrag_index(row, jc, KBd), mv, bad);
+          else if (part == 0 && l == 0 && g.next)
+            st4h(g.next + afrag_index(row, jc, KBd), ld4(g.h_in + (size_t)row * g.d_model + jc) * (mv + 1.0f), bad);
         }
       }
     }

@@ -12,8 +12,8 @@ namespace uad {
 constexpr int kTileN = 16;
 constexpr int kTileK = 32;
 // token rows from which the register-streamed 128-row kernels, the split of the
-// large residual tiles and the adaptive norms by class apply (the ring's smaller
-// tiles go by tile count)
+// large residual tiles and (ada_by_class) the adaptive norms by class apply (the
+// ring's smaller tiles go by tile count)
 constexpr int kBigM = 256;
 
 enum Epilogue : int {
@@ -227,6 +227,29 @@ inline ProjRoute route_projection(const Proj &g) {
   }
   if (!big_ok(g)) return tile(0);
   return ProjRoute{PROJ_STREAMED, 128, cols, 1, big_khalves(g, cols)};
+}
+
+// Whether gate/up (d_model to F) of M rows runs on the small-M kernel; second: with
+// the adaptive norms' second operand.
+inline bool gateup_small(int n_cu, int M, int d, int F, bool second) {
+  Proj g{};
+  g.n_cu = n_cu; g.epi = EPI_GEGLU; g.M = M; g.N = 2 * F; g.K = d; g.second = second;
+  return route_projection(g).kernel == PROJ_SMALL;
+}
+
+// Adaptive norms by class, past kBigM rows: the modulations of the step's distinct
+// flow times only, and the norms as passes of their own, so that QKV and gate/up
+// take one operand.  Up to there the passes (~5 us each) cost more than the second
+// operand does, and a schedule computes its conditioning once.  Same-machine, 6
+// layers of the 1024-wide expert, us per joint step: 64 environments 2680 -> 1346
+// (gate/up 160 -> 56, QKV 60 -> 24, modulations 477 -> 33, two norms 13), 32 1779 ->
+// 948, 16 1128 -> 804, 8 759 -> 634, 6 696 -> 612.  kBigM rows exactly (4 row groups of
+// the small-M kernel) go by class where gate/up then takes the ring: 4 layers, 4 x 64
+// + 1024, us per step and per 10-step schedule by token -> by class: 1024-wide 385 ->
+// 322, 3813 -> 3022; 768 270 -> 257, 2690 -> 2394; 512 205 -> 224, 1821 -> 2107; 256 209 ->
+// 214, 1820 -> 2023.
+inline bool ada_by_class(int n_cu, int M, int d, int F) {
+  return M > kBigM || (M == kBigM && !gateup_small(n_cu, M, d, F, false));
 }
 
 // Sums of squares per row that the projection leaves for the norm: one per

@@ -742,16 +742,9 @@ struct StepScratch {
   float *mlpart;
 };
 
-// Adaptive norms from kBigM rows on: the modulations of the step's distinct flow
-// times only (a token's are row mod_cls[token]), and the norms as passes of
-// their own, so that QKV and gate/up take one operand.  Below that the passes
-// (~5 us each) cost more than the second operand does.  Same-machine, 6 layers of the
-// 1024-wide expert, us per joint step: 64 environments 2680 -> 1346 (gate/up 160
-// -> 56, QKV 60 -> 24, modulations 477 -> 33, two norms 13), 32 1779 -> 948, 16
-// 1128 -> 804, 8 759 -> 634, 6 696 -> 612.
-static bool ada_by_class(const uad_ctx *c, int M, bool schedule_level) {
-  return c->ada && !schedule_level && M >= kBigM;
-}
+// Whether a step's adaptive norms go by flow-time class (a token's modulations are
+// row mod_cls[token]); else by token.
+static bool norms_by_class(const uad_ctx *c, int M) { return c->ada && ada_by_class(c->n_cu, M, c->d, c->F); }
 
 static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float *t, const float *dt,
                                const uint8_t *mask, const uint8_t *next_mask, int is_last, int step, float *v_out,
@@ -762,7 +755,7 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
   const size_t MA = c->m_alloc;
   const bool prof = c->prof_on && !scratch;
   hipError_t e = hipSuccess;
-  const bool by_class = !c->dbg && ada_by_class(c, M, pre != nullptr);
+  const bool by_class = !c->dbg && !pre && norms_by_class(c, M);
   // the adaptive-norm embedding takes no compaction map, and by class the row map
   // has its place in the final kernel's arguments
   if (c->ada && env_map) return fail(c, UAD_E_STATE, "adaptive norms: a compacted step");
@@ -860,11 +853,8 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
     at.q = c->q; at.ldq = c->q_dim; at.s_alloc = c->s_alloc; at.n_keys = c->prefix_len + H;
     at.chunk = H; at.n_heads = c->Hq; at.n_kv_heads = c->Hkv; at.group = c->Hq / c->Hkv;
     at.rows = at.group * H; at.rows_pad = (at.rows + 63) / 64 * 64;
-    Proj gateup{};
-    gateup.n_cu = c->n_cu; gateup.epi = EPI_GEGLU; gateup.M = M; gateup.N = 2 * F; gateup.K = d;
-    gateup.second = c->ada && !by_class;
     at.splits = attn_splits(attn_sizes(c, B, H, (c->prefix_len + H + 31) / 32,
-                                       route_projection(gateup).kernel == PROJ_SMALL), &at.blocks_per_split);
+                                       gateup_small(c->n_cu, M, d, F, c->ada && !by_class)), &at.blocks_per_split);
     if (!scratch && attn_part_rows(c, B, H, c->prefix_len) > c->attn_part_elems)
       return fail(c, UAD_E_SHAPE, "split-KV partials exceed the workspace sized at uad_create");
     at.qblocks = (at.rows + 63) / 64; at.n_eh = B * c->Hkv;
@@ -986,11 +976,11 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
   return UAD_OK;
 }
 
-// Schedule-level conditioning applies below kBigM rows (projections bound by
-// the weight stream, where the modulation matrix would be read once per step)
+// Schedule-level conditioning applies where the norms go by token (projections bound
+// by the weight stream, where the modulation matrix would be read once per step)
 // when the buffers for n_steps x m_alloc rows are in place.
 static bool ada_schedule_level(const uad_ctx *c, size_t M, int n_steps) {
-  return c->ada && !c->dbg && M < kBigM && (size_t)n_steps * c->m_alloc <= c->pre_rows;
+  return c->ada && !c->dbg && !norms_by_class(c, (int)M) && (size_t)n_steps * c->m_alloc <= c->pre_rows;
 }
 
 // Grow the schedule-level conditioning buffers to `rows` rows (no-op when they
@@ -1271,7 +1261,7 @@ uad_status uad_denoise_schedule(uad_ctx *c, float *x, const float *t_sched, cons
   if (st != UAD_OK) return st;
   if (n_steps < 1) return fail(c, UAD_E_INVALID, "uad_denoise_schedule: n_steps must be >= 1");
   (void)hipSetDevice(c->device);
-  if (c->ada && !c->dbg && (size_t)batch * chunk < kBigM) ensure_ada_rows(c, (size_t)n_steps * c->m_alloc);
+  if (c->ada && !c->dbg && !norms_by_class(c, batch * chunk)) ensure_ada_rows(c, (size_t)n_steps * c->m_alloc);
   GraphKey k{};
   k.kind = 0;
   k.is_schedule = true;
@@ -1403,7 +1393,7 @@ uad_status uad_denoise_release(uad_ctx *c, float *x, int32_t batch, int32_t chun
       host_dev = (float *)pa.devicePointer;
     (void)hipGetLastError();  // pageable memory: the query's error is expected
   }
-  if (c->ada && !c->dbg && M < kBigM) ensure_ada_rows(c, (size_t)Nstar * c->m_alloc);
+  if (c->ada && !c->dbg && !norms_by_class(c, (int)M)) ensure_ada_rows(c, (size_t)Nstar * c->m_alloc);
   GraphKey k{};
   k.kind = 1;
   k.x = x; k.B = batch; k.H = chunk; k.n_steps = Nstar; k.step_ticks = step_ticks;

@@ -29,6 +29,7 @@ extern "C" void attention(const int *a, int *out) {  // n_cu group n_kv_heads he
   out[2] = attn_two_groups(s.n_cu, groups, s.qblocks(), out[1], nb);
   out[3] = attn_splits_max(s);
 }
+extern "C" int by_class(int n_cu, int M, int d, int F) { return ada_by_class(n_cu, M, d, F); }
 extern "C" int pack_launches(const int *a, int *out) {  // n_env n_kv_heads n_blk -> (env envs blk blks)*, how many
   int n = 0;
   for_pack_launches(a[0], a[1], a[2], [&](int e, int ne, int q, int nq) {
@@ -65,6 +66,11 @@ def projection(epi, M, N, K, n_cu=256, q_dim=0, second=False, gate=False, mod_ro
 def attention(heads, n_kv_heads, head_dim, B, H, keys, n_cu=256, small_gateup=False):
     """(key splits, 32-key blocks of each, two key groups, most splits)."""
     return _call("attention", (n_cu, heads // n_kv_heads, n_kv_heads, head_dim, B, H, keys, small_gateup), 4)
+
+
+def ada_by_class(M, d, F, n_cu=256):
+    """Whether the adaptive norms of a step of M rows go by flow-time class."""
+    return bool(_lib().by_class(n_cu, M, d, F))
 
 
 def pack_launches(n_env, n_kv_heads, n_blk):

@@ -1,13 +1,15 @@
-"""Batched steps of the adaptive-norm expert (over 256 token rows): the
+"""Batched steps of the adaptive-norm expert (256 token rows and more): the
 modulations of the distinct flow times only, the norms as passes of their own.
-The row counts on either side of the bound, all tokens at one time, a few times in an irregular order, every token its own
-(272 rows), more distinct times than the class table takes (1120 rows), widths
+The row counts on either side of the bound, all tokens at one time, a few times in
+an irregular order, every token its own (272 rows), more distinct times than the class table takes (1120 rows), widths
 that are not multiples of 64 or 256, and ragged last row tiles; sampled
 environments against the oracle, the no-allocation step bit for bit.  Then the
 experts' own widths on each kernel of the products (tests/test_routes.py has the
 rules): the row count known on the device only in the register-streamed kernel,
 whole and in k-halves, and the gates by class in the ring and streamed residual
-epilogues.  The widths from 1024 up have the bar of the other parity tests.  The
+epilogues.  And a schedule of 256 rows on either side of the rule for exactly that
+many: a narrow expert by token, conditioned once for the schedule, and a wider one
+by class.  The widths from 1024 up have the bar of the other parity tests.  The
 small ones need a closer one: with modulations of 0.02 sqrt(d) their layers move
 the velocity so little that a token with its neighbour's flow time shows only
 2.6e-3 (oracle, 96 wide) to 6.7e-2; the errors are 6e-5 to 3.6e-4."""
@@ -32,8 +34,8 @@ def _check(shape, B, H, times, label, bar):
     wl = dataclasses.replace(W.get_workload("tiny_adarms"), shape=shape, batch=B, chunk=H, prefix=P)
     weights = W.make_weights(wl)
     g = np.random.default_rng(d + times)
-    k, v = (W.round_to_bf16(g.standard_normal((2, B, P, shape.n_kv_heads, shape.head_dim), dtype=np.float32))
-            for _ in range(2))
+    kv = (shape.n_layers, B, P, shape.n_kv_heads, shape.head_dim)
+    k, v = (W.round_to_bf16(g.standard_normal(kv, dtype=np.float32)) for _ in range(2))
     x0 = np.stack([W.make_noise(wl, b) for b in range(B)])
     t = (((np.arange(B * H, dtype=np.int64) * 7919) % times + 1) / np.float32(times)).astype(np.float32).reshape(B, H)
     assert len(np.unique(t)) == times
@@ -60,7 +62,8 @@ def _check(shape, B, H, times, label, bar):
 
 
 @pytest.mark.parametrize("d,B,H,times", [
-    (256, 16, 16, 3), (256, 15, 17, 3), (256, 17, 16, 1), (256, 17, 16, 272), (96, 19, 14, 5), (320, 70, 16, 1120), (512, 65, 17, 9), (512, 65, 17, 1024),
+    (256, 16, 16, 3), (256, 15, 17, 3), (256, 17, 16, 1), (256, 17, 16, 272), (96, 19, 14, 5),
+    (320, 70, 16, 1120), (512, 65, 17, 9), (512, 65, 17, 1024),
 ])
 def test_batched_times(gpu, d, B, H, times):
     _check(W.ModelShape(2, d, 4, 2, 64, 2 * d, 7, conditioning="adarms"), B, H, times, "times", SMALL_BAR)
@@ -78,3 +81,37 @@ WIDE = [
 @pytest.mark.parametrize("d,heads,hkv,hd,F,B,H,times", WIDE)
 def test_batched_wide(gpu, d, heads, hkv, hd, F, B, H, times):
     _check(W.ModelShape(2, d, heads, hkv, hd, F, 7, conditioning="adarms"), B, H, times, "wide", BAR)
+
+
+@pytest.mark.parametrize("d,layers", [(256, 4), (768, 2)])
+def test_schedule_at_the_bound(gpu, d, layers):
+    shape = W.ModelShape(layers, d, 4, 2, 64, 4 * d, 7, conditioning="adarms")
+    _check(shape, 16, 16, 5, "bound", SMALL_BAR)
+    B, H, P = 16, 16, 40
+    wl = dataclasses.replace(W.get_workload("tiny_adarms"), shape=shape, batch=B, chunk=H, prefix=P)
+    weights = W.make_weights(wl)
+    g = np.random.default_rng(d)
+    k, v = (W.round_to_bf16(g.standard_normal((layers, B, P, 2, 64), dtype=np.float32)) for _ in range(2))
+    x0 = np.stack([W.make_noise(wl, b) for b in range(B)]).astype(np.float32)
+    bud = np.full((B, H), 5, np.int32)
+    bud[:, :3] = 2
+    ex = U.ActionExpert(shape, B, H, P)
+    try:
+        ex.load_weights(weights)
+        ex.set_prefix_kv(W.bf16_bits(k), W.bf16_bits(v), B, P)
+        n, t, dt, mask = ex.schedule_tables(bud)
+        got = []
+        for _ in range(2):
+            x = torch.from_numpy(x0).cuda()
+            rel = torch.zeros_like(x)
+            ex.schedule(x, t, dt, mask, rel)
+            torch.cuda.synchronize()
+            got.append(rel.cpu().numpy())
+        assert got[0].tobytes() == got[1].tobytes()
+        for b in (0, B - 1):
+            r = O.denoise_schedule(O.build_model(shape, weights, [k[:, b]], [v[:, b]]), x0[b:b + 1], bud[b:b + 1])
+            e = rel_err(got[0][b], r["released"][0])
+            log(f"[adarms schedule d={d}] env {b}: released rel err {e:.2e}")
+            assert e <= SMALL_BAR
+    finally:
+        ex.close()

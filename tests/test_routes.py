@@ -135,3 +135,19 @@ def test_split_short_k_sizes():
     """A width without 64 x 64 tiles: the short K splits too (test_gpu_ring_tiles)."""
     for K in (288, 1024):
         assert R.projection(R.RESID, 3750, 288, K)[:4] == ((R.RING, 128, 96, 2) if K == 1024 else (R.SMALL, 0, 0, 1))
+
+
+@pytest.mark.parametrize("d,F,at_256", [(256, 1024, False), (512, 2048, False), (768, 3072, True), (1024, 4096, True),
+                                        (1536, 6144, True)])
+def test_adaptive_norms_by_class(d, F, at_256):
+    """256 rows go by class where gate/up then takes the ring; by token the small-M
+    kernel has its last whole row groups, and a schedule conditions once."""
+    assert [R.ada_by_class(M, d, F) for M in (1, 255, 256, 257, 3200)] == [False, False, at_256, True, True]
+    assert (R.projection(R.GEGLU, 256, 2 * F, d)[0] == R.RING) == at_256
+
+
+def test_adaptive_norm_bound_sizes():
+    """The sizes of test_gpu_adarms_batched.test_schedule_at_the_bound."""
+    assert not R.ada_by_class(256, 256, 1024) and R.ada_by_class(256, 768, 3072)
+    assert R.projection(R.MOD, 256, 26 * 256, 256)[0] == R.STREAMED  # by token: the first norm's operand formed there
+    assert R.projection(R.RESID, 256, 256, 1024, gate=True, scale_next=True)[0] == R.SMALL
