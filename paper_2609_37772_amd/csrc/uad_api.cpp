@@ -126,6 +126,10 @@ hipEvent_t pool_event(uad_ctx *c) {
   return e;
 }
 
+// Elements per shift operand of the adaptive norms: steps by token have up to
+// kBigM rows.
+size_t shift_stride(const uad_ctx *c) { return std::min<size_t>(c->m_alloc, kBigM) * c->d; }
+
 AttnSizes attn_sizes(const uad_ctx *c, int B, int H, int n_blocks, bool small_gateup = false) {
   return AttnSizes{c->n_cu, c->Hq / c->Hkv, c->Hkv, c->hd, B, H, n_blocks, small_gateup};
 }
@@ -333,7 +337,7 @@ uad_status uad_create(const uad_model_config *cfg, int32_t device, void *hip_str
          o_ml = a.take<float>(std::max<size_t>(part, 1) * 2), o_ssq = a.take<float>((size_t)(d / 16) * M),
          o_trx0 = a.take<float>(M * Da), o_trv = a.take<float>(M * Da), o_trt = a.take<float>(kMaxTrSteps * M),
          o_trdt = a.take<float>(kMaxTrSteps * M), o_trm = a.take<uint8_t>(kMaxTrSteps * M),
-         o_mod = a.take<float>(M * c->n_mod), o_mshift = a.take<uint16_t>(c->ada ? (size_t)2 * c->L * M * d : 0),
+         o_mod = a.take<float>(M * c->n_mod), o_mshift = a.take<uint16_t>(c->ada ? 2 * c->L * shift_stride(c) : 0),
          o_pf = a.take<unsigned>(64), o_status = a.take<unsigned>(1),
          o_budt = a.take<float>(kMaxTrSteps * M), o_buddt = a.take<float>(kMaxTrSteps * M),
          o_budm = a.take<uint8_t>(kMaxTrSteps * M), o_budmap = a.take<int32_t>((size_t)kMaxTrSteps * m.max_batch),
@@ -842,7 +846,7 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
       GemmArgs gm{};
       gm.status = c->status;
       gm.M = M; gm.m_alloc = (int)MA; gm.A = c->a_te; gm.W = c->w_mod; gm.N = n_mod; gm.K = d; gm.out = c->mod; gm.ldo = n_mod;
-      gm.bias = c->b_mod; gm.mod_shift_ops = c->mod_shift_ops; gm.shift_stride = MA * d; gm.h_in = c->h;
+      gm.bias = c->b_mod; gm.mod_shift_ops = c->mod_shift_ops; gm.shift_stride = shift_stride(c); gm.h_in = c->h;
       gm.d_model = d; gm.n_layers = c->L; gm.next = c->a_n;
       UAD_CHECK_CLS(K_GEMM_MOD, launch_gemm(EPI_MOD, gm, plan_gemm(EPI_MOD, M, n_mod, d), s, ea_, eb_));
     }
@@ -888,14 +892,14 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
       norm_fields(q); q.use_rstd = 1;
       const float *mod_base = pre ? pre->mod : c->mod;
       const op_t *shift_base = pre ? pre->shift : c->mod_shift_ops;
-      const size_t shift_stride = pre ? pre->shift_stride : MA * d;
+      const size_t per_shift = pre ? pre->shift_stride : shift_stride(c);
       if (by_class) {
         const float *ml = c->mod + (size_t)l * 6 * d;
         UAD_CHECK_CLS(K_ADA_NORM, launch_ada_norm(c->h, M, d, c->cfg.rms_eps, ml, ml + d, n_mod, c->mod_cls, c->a_n,
                                                   c->status, s, ea_, eb_));
         q.use_rstd = 0;
       } else if (c->ada) {
-        q.A2 = shift_base + (size_t)(2 * l) * shift_stride;
+        q.A2 = shift_base + (size_t)(2 * l) * per_shift;
       }
       UAD_CHECK_CLS(K_GEMM_QKV, launch_gemm(EPI_QKV, q, pq, s, ea_, eb_));
       at.kc = kc; at.vtc = vtc;
@@ -942,7 +946,7 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
                                                   c->status, s, ea_, eb_));
         gu.use_rstd = 0;
       } else if (c->ada) {
-        gu.A2 = shift_base + (size_t)(2 * l + 1) * shift_stride;
+        gu.A2 = shift_base + (size_t)(2 * l + 1) * per_shift;
       }
       UAD_CHECK_CLS(K_GEMM_GATEUP, launch_gemm(EPI_GEGLU, gu, pg, s, ea_, eb_));
       GemmArgs dn{};

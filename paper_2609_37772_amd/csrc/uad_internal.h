@@ -461,7 +461,7 @@ struct uad_ctx {
   uad::op_t *w_mod = nullptr;         // packed [n_mod][d]
   float *b_mod = nullptr;             // [n_mod]
   float *mod = nullptr;               // [m_alloc][n_mod] per token: per layer (a,b,g)_attn (a,b,g)_mlp, then (a,b)_final
-  uad::op_t *mod_shift_ops = nullptr; // [L][2][m_alloc*d] shifts as fp16 operands
+  uad::op_t *mod_shift_ops = nullptr; // [L][2][shift_stride] shifts as fp16 operands (steps by token)
   // batched steps: the modulations of a step's distinct flow times only
   int32_t *mod_cls = nullptr;         // [m_alloc] token's row of mod
   float *cls_t = nullptr;             // [m_alloc] the distinct flow times

@@ -1,6 +1,7 @@
 // A HIP runtime in host memory, for tests of the library's host code without a
 // GPU: "device" allocations are entries of a table, copies are memcpy, kernels
 // are not run.  stub_log() returns what was called since the last stub_reset().
+#include <algorithm>
 #include <cstdlib>
 #include <cstring>
 #include <map>
@@ -13,6 +14,7 @@ namespace {
 std::map<char *, size_t> g_alloc;  // base -> bytes
 std::ostringstream g_log;
 std::string g_text;
+char *g_a2_end = nullptr;  // end of the second operands of projections
 int g_fail_in = -1;  // the n-th asynchronous copy or kernel from now fails (-1: none)
 
 hipError_t step(const char *what) {
@@ -28,7 +30,7 @@ const std::pair<char *const, size_t> *find(const void *p) {
 }  // namespace
 
 extern "C" {
-void stub_reset(int fail_in) { g_log.str(""); g_fail_in = fail_in; }
+void stub_reset(int fail_in) { g_log.str(""); g_fail_in = fail_in; g_a2_end = nullptr; }
 const char *stub_log() { g_text = g_log.str(); return g_text.c_str(); }
 // a "device" allocation at a given place (null: removed)
 void stub_map(void *p, size_t bytes) { if (bytes) g_alloc[(char *)p] = bytes; else g_alloc.erase((char *)p); }
@@ -42,6 +44,9 @@ void __hipRegisterFunction(void **, const void *, char *, const char *, unsigned
 void stub_ready(uad_ctx *c) { c->weights_loaded = c->prefix_set = true; c->prefix_batch = c->cfg.max_batch; }
 void stub_set_active(uad_ctx *c, int step, int n) { c->bud_active[step] = (uint16_t)n; }
 int stub_prefix_set(const uad_ctx *c) { return c->prefix_set; }
+// bytes of the adaptive norms' shift operands, and the end of what steps read of them
+size_t stub_shift_bytes(const uad_ctx *c) { return (char *)c->pf_sink - (char *)c->mod_shift_ops; }
+size_t stub_shift_end(const uad_ctx *c) { return g_a2_end ? g_a2_end - (char *)c->mod_shift_ops : 0; }
 
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
@@ -102,7 +107,10 @@ int resid_ssq_tiles(const GemmArgs &g) { return g.N / kTileN; }
 hipError_t attention_init() { return hipSuccess; }
 hipError_t gemm_init() { return hipSuccess; }
 void attention_read_ahead_caps(const AttnArgs &, int, int, size_t *, size_t *) {}
-hipError_t launch_gemm(int, const GemmArgs &, const GemmPlan &, hipStream_t, hipEvent_t, hipEvent_t) { return step("gemm"); }
+hipError_t launch_gemm(int, const GemmArgs &g, const GemmPlan &, hipStream_t, hipEvent_t, hipEvent_t) {
+  if (g.A2) g_a2_end = std::max(g_a2_end, (char *)(g.A2 + (size_t)(g.M + 15) / 16 * 16 * g.K));
+  return step("gemm");
+}
 hipError_t launch_attention(const AttnArgs &, int, int, hipStream_t, hipEvent_t, hipEvent_t) { return step("attention"); }
 hipError_t launch_temb(const float *, const float *, int, int, int, const float *, const float *, const float *, op_t *,
                        unsigned *, hipStream_t, hipEvent_t, hipEvent_t, const int32_t *, int) { return step("temb"); }

@@ -1,7 +1,7 @@
 """The library's host code against a stand-in for the HIP runtime (tests/stub).
 uad_set_prefix_kv: which sources are read in place, what is refused before
 anything is written, and what an error on the way leaves behind.  Steps: what is
-refused before any work is enqueued."""
+refused before any work is enqueued, and the memory that the adaptive norms keep."""
 import concurrent.futures as cf
 import ctypes
 import os
@@ -39,6 +39,7 @@ def lib(tmp_path_factory):
     subprocess.run(["g++", "-shared", "-o", so, *objs, "-Wl,-z,defs", "-Wl,-Bsymbolic", *fat], check=True)
     lib = ctypes.CDLL(so)
     lib.stub_log.restype = lib.uad_last_error.restype = ctypes.c_char_p
+    lib.stub_shift_bytes.restype = lib.stub_shift_end.restype = ctypes.c_size_t
     lib.stub_map.argtypes = [ctypes.c_void_p, ctypes.c_size_t]
     return lib
 
@@ -131,4 +132,21 @@ def test_compacted_adaptive_norm_step_is_refused_before_any_work(lib, batch, chu
     lib.stub_reset(-1)
     assert lib.uad_denoise_budgets(*args) == STATE
     assert lib.stub_log() == b""
+    lib.uad_destroy(c)
+
+
+@pytest.mark.parametrize("batch,chunk,by_token", [(1, 9, True), (15, 17, True), (16, 16, True), (17, 16, False),
+                                                  (64, 50, False)])
+def test_shift_operands_are_kept_for_steps_by_token_only(lib, batch, chunk, by_token):
+    """They take rows up to 256: larger steps go by flow-time class without them."""
+    c = create(lib, batch, chunk, flags=1)
+    lib.stub_ready(c)
+    lib.stub_reset(-1)
+    x = np.zeros((batch, chunk, 7), np.float32)
+    p = ctypes.c_void_p(x.ctypes.data)
+    assert lib.uad_denoise_step(c, p, p, p, p, None, batch, chunk) == OK
+    M, row = batch * chunk, 128 * 2
+    kept = min((M + 63) // 64 * 64, 256)
+    assert lib.stub_shift_bytes(c) == 2 * L * kept * row
+    assert lib.stub_shift_end(c) == (((2 * L - 1) * kept + (M + 15) // 16 * 16) * row if by_token else 0)
     lib.uad_destroy(c)
