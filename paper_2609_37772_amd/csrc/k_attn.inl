@@ -437,7 +437,7 @@ __global__ __launch_bounds__(64 * W) void attn_combine_kernel(AttnArgs a, int hd
 static int g_attn_cus = 256;  // compute units of the device (set by attention_init)
 
 // waves per workgroup of the split merge (see launch_hd)
-static int merge_waves(int splits) { return splits > 8 ? 4 : 1; }
+static int merge_waves(int splits) { return splits > kAttnMerge8 ? 4 : 1; }
 
 template <int HD>
 static hipError_t launch_hd(const AttnArgs &a, int batch, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
@@ -507,9 +507,9 @@ static hipError_t launch_hd(const AttnArgs &a, int batch, hipStream_t s, hipEven
   const dim3 cgrid(a.rows_pad / 16, HD / (16 * W), batch * a.n_kv_heads + (ac.pre_comb.wgs ? 1 : 0));
   if (a.splits <= 4)
     UAD_LAUNCH((attn_combine_kernel<4, 1>), cgrid, dim3(64), 0, s, none, ev1, ac, HD);
-  else if (a.splits <= 8)
+  else if (a.splits <= kAttnMerge8)
     UAD_LAUNCH((attn_combine_kernel<8, 1>), cgrid, dim3(64), 0, s, none, ev1, ac, HD);
-  else if (a.splits <= kAttnMerge16)
+  else if (a.splits <= 16)
     UAD_LAUNCH((attn_combine_kernel<16, 4>), cgrid, dim3(256), 0, s, none, ev1, ac, HD);
   else if (a.splits <= kAttnMaxSplits)
     UAD_LAUNCH((attn_combine_kernel<32, 4>), cgrid, dim3(256), 0, s, none, ev1, ac, HD);

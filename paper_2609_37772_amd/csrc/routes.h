@@ -288,7 +288,7 @@ int for_pack_launches(int n_env, int n_kv_heads, int n_blk, F f) {
 // buffer), 2 * NB * 32 * HD * 4 bytes of LDS.
 constexpr int attn_chunk_blocks(int head_dim) { return head_dim == 256 ? 2 : 4; }
 constexpr int kAttnMaxSplits = 32;  // split-KV partials the merge accepts
-constexpr int kAttnMerge16 = 16;    // ... that its instance for up to 16 holds
+constexpr int kAttnMerge8 = 8;      // ... up to which it runs one wave a workgroup
 
 // CUs the attention launch has to leave free for the weight read-ahead of its
 // extra workgroups (below that the read-ahead is not issued).
@@ -332,17 +332,18 @@ inline int attn_splits_max(const AttnSizes &a) {
 // streams its weights from HBM (~27.5 instead of ~22 us at 300-850 rows).
 //
 // Gate/up on the small-M kernel (up to 128 rows of the 1024-wide expert, every
-// adaptive-norm step by token) does not gain that: one chunk, else two, per split
-// where the grid fits one round of the CUs, whether or not any are left.  Not one
-// chunk past 16 splits, where the merge takes its longer form.  Same-machine, us
-// per joint step of 4 layers, as above -> so:
-//   adaptive norms  4 x 60 + 816  420.1 -> 413.8 (6 splits -> 7)   5 x 48 + 900  422.4 -> 414.0 (6 -> 8)
-//                   2 x 60 + 816  304.5 -> 300.8 (7 -> 14)         8 x 12 + 900  277.8 -> 272.8 (8 -> 15)
-//                   5 x 36 + 256  356.0 -> 349.7 (3 -> 5)          4 x 32 + 816  309.2 -> 303.1 (7 -> 14)
-//   input           2 x 56 + 700  223.4 -> 220.0 (6 -> 12)         4 x 32 + 640  229.7 -> 226.4 (6 -> 11)
-// Over one round both lose (adaptive norms, one chunk: 3 x 44 + 816 312 -> 334, 6 x 20 +
-// 816 309 -> 327; two: 5 x 50 + 1000 435 -> 461), as do 17 splits (1 x 50 + 1000 213.7 ->
-// 215.8).
+// adaptive-norm step by token) gains less from that: as many splits as there may be
+// where the merge holds them in its 8-split form, whether or not CUs are left, and one
+// chunk per split up to 5/8 of the CUs.  Same-machine, us per joint step of 18 layers,
+// as in the other steps -> so (few layers stay in the memory-side cache and say little):
+//   at most 8, adaptive norms: 4 x 60 + 816 1941 -> 1912 (6 splits -> 7), 5 x 42 + 700 1847 ->
+//     1816 (6 -> 8), 9 x 25 + 501 1924 -> 1890 (5 -> 6), 3 x 48 + 300 1414 -> 1392 (3 -> 6); 8 x 25
+//     + 501 1774 -> 1785 (5 -> 6), 3 x 50 + 400 1499 -> 1505 (4 -> 8); nine: 3 x 64 + 1000 1697
+//     -> 1730 (7 -> 9)
+//   one chunk, 144 and 160 workgroups, adaptive norms: 3 x 32 + 640 1230 -> 1217, 3 x 20 + 816
+//     961 -> 948; input: 3 x 32 929 -> 915, 8 x 16 + 512 1041 -> 1027; 168 and 192: 4 x 20 +
+//     816 1161 -> 1174, 5 x 25 + 501 1411 -> 1449; input: 2 x 56 + 700 977 -> 988, 7 x 18 + 500
+//     1037 -> 1077
 // Same-machine, 1024-wide expert of 6 layers, us per joint step, 816 + 50 keys
 // (28 blocks), by splits:
 //   environments   14     10      7      5      4      3      2      1
@@ -359,13 +360,11 @@ inline int attn_splits(const AttnSizes &a, int *bps) {
   auto grid = [&](int sp) { return 8L * (((long)a.B * a.n_kv_heads * sp + 7) / 8) * a.qblocks(); };
   const int most = attn_splits_max(a);
   int sp = std::min(most, (a.n_blocks + nb - 1) / nb);
-  // whole chunks per split in one round, for which the read-ahead is given up
-  auto one_round = [&](int chunks) {
-    return a.small_gateup && sp * chunks * nb >= a.n_blocks && grid(sp) <= a.n_cu;
-  };
-  if (2 * grid(sp) > a.n_cu && !(one_round(1) && sp <= kAttnMerge16)) {
+  if (a.small_gateup && most <= kAttnMerge8 && grid(most) <= a.n_cu) {
+    sp = most;
+  } else if (16 * grid(sp) > (a.small_gateup ? 10 : 8) * a.n_cu) {
     sp = std::min(most, (a.n_blocks + 2 * nb - 1) / (2 * nb));
-    while (sp > 1 && grid(sp) > a.n_cu - kReadAheadMinCus && !one_round(2)) --sp;
+    while (sp > 1 && grid(sp) > a.n_cu - kReadAheadMinCus) --sp;
   }
   *bps = (a.n_blocks + sp - 1) / sp;
   return (a.n_blocks + *bps - 1) / *bps;

@@ -36,8 +36,11 @@ def test_two_key_group_sizes(hd, heads, hkv, B, H, keys, splits):
 
 
 @pytest.mark.parametrize("B,H,prefix,small,other", [  # eight query heads of 256 on one KV head
-    (4, 60, 816, 7, 6), (2, 60, 816, 14, 7), (8, 12, 900, 15, 8), (5, 36, 256, 5, 3), (2, 56, 700, 12, 6),
-    (3, 44, 816, 7, 7), (1, 50, 1000, 9, 9), (5, 50, 1000, 6, 6), (1, 50, 816, 14, 14),
+    (4, 60, 816, 7, 6), (5, 48, 900, 8, 6), (6, 42, 700, 6, 5),  # all that there may be, up to eight
+    (5, 42, 700, 8, 6), (8, 24, 300, 6, 3),
+    (3, 64, 1000, 7, 7), (7, 28, 1000, 7, 7),                    # nine: CUs left to the read-ahead
+    (3, 32, 640, 11, 6), (3, 37, 501, 9, 5),                     # one chunk on 5/8 of the CUs
+    (2, 56, 700, 6, 6), (2, 60, 816, 7, 7), (1, 50, 816, 14, 14),
 ])
 def test_key_splits_go_by_what_gateup_gains(B, H, prefix, small, other):
     """CUs are left to the weight read-ahead only where gate/up gains by it."""
