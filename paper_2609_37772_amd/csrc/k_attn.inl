@@ -558,8 +558,7 @@ hipError_t attention_init() {
 
 // Below kBigM rows the launches that carry the read-ahead are short, so it stops
 // at about what its workgroups read meanwhile (~2.5 TB/s in all, 40 GB/s for one
-// workgroup, 0.07 GB/s a lane of the one-wave merge workgroups); past that the
-// launch waits for it.  Same-machine, us per joint step: 1536-wide expert of 4
+// workgroup; the merge's: merge_read_ahead); past that the launch waits for it.  Same-machine, us per joint step: 1536-wide expert of 4
 // layers at one environment 302 -> 256 (chunk 50, 1024 keys) and 300 -> 279
 // (chunk 90, 300 keys); 1024-wide at 12 environments of 17 tokens 453 -> 427.
 // From kBigM rows on the batched gate/up gains more from the whole read-ahead
@@ -571,9 +570,8 @@ void attention_read_ahead_caps(const AttnArgs &a, int head_dim, int wgs, size_t 
   const int serial = two ? (a.blocks_per_split + 1) / 2 : a.blocks_per_split;
   const size_t extra = (size_t)std::max(0, serial - nb), KB = 1024;
   const size_t all = (22528 + 2560 * extra) * KB, per_wg = (288 + 56 * extra) * KB;
-  const size_t lanes = (size_t)(a.rows_pad / 16) * (head_dim / 16) * 64;
   *attn = std::min(*attn, std::min(all, per_wg * (size_t)wgs));
-  *merge = std::min(*merge, lanes * 480);
+  *merge = std::min(*merge, merge_read_ahead(a.rows_pad, head_dim, a.splits));
 }
 
 hipError_t launch_attention(const AttnArgs &a, int batch, int head_dim, hipStream_t s, hipEvent_t ev0,

@@ -370,6 +370,17 @@ inline int attn_splits(const AttnSizes &a, int *bps) {
   return (a.n_blocks + *bps - 1) / *bps;
 }
 
+// Bytes that the extra workgroups of the split merge read ahead below kBigM rows: what
+// a lane reads while the merge runs, twice that where more than 16 partials take its
+// longer form.  Same-machine, us per joint step of 18 layers, input-conditioned, with
+// no bound -> with 480 bytes a lane: 16 splits 24 + 1000 716 -> 691, 14 splits 20 + 816
+// 712 -> 687, 48 to 50 + 816 no change (11.8 of 13.6 MB at 48, all at 49); past 16
+// splits with 480 and 960: 28 + 1000 712 -> 738, 711; 2 x 32 + 1000 765 -> 787, 766; 10 +
+// 1020 738 -> 715, 711.
+constexpr size_t merge_read_ahead(int rows_pad, int head_dim, int splits) {
+  return (size_t)(rows_pad / 16) * (head_dim / 16) * 64 * (splits > 16 ? 960 : 480);
+}
+
 // Whether a launch of n_eh x splits groups and qblocks query blocks streams its
 // keys a block at a time.
 inline bool attn_streamed(int n_cu, int groups, int qblocks, int bps, int nb) {

@@ -29,6 +29,7 @@ extern "C" void attention(const int *a, int *out) {  // n_cu group n_kv_heads he
   out[2] = attn_two_groups(s.n_cu, groups, s.qblocks(), out[1], nb);
   out[3] = attn_splits_max(s);
 }
+extern "C" long merge_bytes(int rows_pad, int head_dim, int splits) { return merge_read_ahead(rows_pad, head_dim, splits); }
 extern "C" int by_class(int n_cu, int M, int d, int F) { return ada_by_class(n_cu, M, d, F); }
 extern "C" int pack_launches(const int *a, int *out) {  // n_env n_kv_heads n_blk -> (env envs blk blks)*, how many
   int n = 0;
@@ -66,6 +67,13 @@ def projection(epi, M, N, K, n_cu=256, q_dim=0, second=False, gate=False, mod_ro
 def attention(heads, n_kv_heads, head_dim, B, H, keys, n_cu=256, small_gateup=False):
     """(key splits, 32-key blocks of each, two key groups, most splits)."""
     return _call("attention", (n_cu, heads // n_kv_heads, n_kv_heads, head_dim, B, H, keys, small_gateup), 4)
+
+
+def merge_read_ahead(rows, head_dim, splits):
+    """Bytes that the split merge may read ahead (below 256 token rows)."""
+    fn = _lib().merge_bytes
+    fn.restype = ctypes.c_long
+    return fn((rows + 63) // 64 * 64, head_dim, splits)
 
 
 def ada_by_class(M, d, F, n_cu=256):

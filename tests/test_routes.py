@@ -49,6 +49,17 @@ def test_key_splits_go_by_what_gateup_gains(B, H, prefix, small, other):
         assert splits == want <= most and splits * per >= (prefix + H + 31) // 32
 
 
+@pytest.mark.parametrize("H,keys,whole", [(28, 1028, True), (17, 1027, False), (24, 1024, False), (48, 864, False),
+                                          (49, 865, True), (50, 866, True)])
+def test_merge_reads_ahead_for_as_long_as_it_runs(H, keys, whole):
+    """Batch 1 of the 1024-wide expert: down and the next layer's QKV are 13.6 MB.
+    Past 16 splits the merge runs longer and reads twice as much meanwhile."""
+    splits = R.attention(8, 1, 256, 1, H, keys, small_gateup=True)[0]
+    got = R.merge_read_ahead(8 * H, 256, splits)
+    assert (splits > 16) == (keys > 1024) and got == (8 * H + 63) // 64 * 4 * 1024 * (960 if splits > 16 else 480)
+    assert (got >= 2 * 1024 * (4096 + 2560)) == whole
+
+
 @pytest.mark.parametrize("n_cu", [32, 64, 128, 256])
 def test_key_splits_fit_the_workspace(n_cu):
     for heads, hkv, hd in ((8, 1, 256), (12, 2, 128), (4, 4, 64)):
