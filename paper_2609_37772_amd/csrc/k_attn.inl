@@ -86,8 +86,8 @@ __device__ __forceinline__ void prefetch_share(const Prefetch &pf, int wg, unsig
 // LOWREG: the K fragments of each 16-key half and the V fragments of each
 // half of the output columns are read just before their MFMAs (fewer live
 // registers: two waves per SIMD at HD = 256) instead of all up front.
-// NW waves (16 query rows each) per workgroup; NW > 4 only without split-KV
-// (a.qblocks counts blocks of 16 * NW rows).
+// NW waves per workgroup, NW / KG of 16 query rows; more than 4 row tiles only
+// without split-KV (a.qblocks counts blocks of 16 * NW / KG rows).
 // KG key groups: wave w takes row tile w % (NW / KG) and every KG-th run of NB
 // blocks from run w / (NW / KG) on; the groups' results are merged through LDS
 // at the end, each group finishing its share of the output columns.

@@ -17,8 +17,9 @@
 //   * per-wave partial tiles are reduced through LDS in fixed wave order
 //     (deterministic, no atomics).
 // RMSNorm is folded into the GEMMs: the residual GEMMs (time-MLP out, O, down)
-// update h for their columns, write the per-16-column sum of squares of every
-// row and the next operand fp16(h * gain_next); the GEMMs that consume a
+// update h for their columns, write every row's sum of squares over 16 columns (the
+// batched kernels: over a wave's columns or an output tile) and the next operand
+// fp16(h * gain_next); the GEMMs that consume a
 // normalised input (QKV, gate/up) scale their accumulators by
 // rstd[row] = (sum of those sums / d + eps)^-1/2, since
 // RMSNorm(h) W^T = rstd * ((h * gain) W^T).
@@ -801,10 +802,10 @@ struct RingShape<EPI_RESID_F32> {
 struct RingGeGlu144 {
   static constexpr int RT = 9, CT = 16, WR = 1, WC = 8, NS = 3;
 };
-// 160 x 256 gate/up tiles, 2 x 4 waves of 80 x 64 (two stages only: two
+// 160 x 256 gate/up tiles, 2 x 4 waves of 80 x 64 (two stages at any K: two
 // workgroups' three stages and row statistics exceed the 160 KiB of LDS)
 struct RingGeGlu160 {
-  static constexpr int RT = 10, CT = 16, WR = 2, WC = 4, NS = 3;
+  static constexpr int RT = 10, CT = 16, WR = 2, WC = 4, NS = 2;
 };
 
 // Tiles for a few hundred rows, where 128-row tiles leave CUs idle: 64 x 64 (2 x 4

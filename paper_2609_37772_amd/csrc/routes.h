@@ -126,7 +126,9 @@ inline bool ring96_fits(const Proj &g) {
 //     17.0 -> 13.7, 2048 (768) 23.0 -> 23.4
 //   down 4096 -> 1024  by splits 1 / 2 / 4: 300 rows (80) 14.1 -> 22.0 / 15.7 / 13.1,
 //     400 (112) 15.0 -> 22.0 / 15.8 / 13.0, 600 (160) 20.4 -> 22.3 / 18.4 / 17.0, 800
-//     (208) 26.0 -> 22.7 / 18.4 / 20.6, 1050 (272) 23.3 -> 28.5
+//     (208) 26.0 -> 22.7 / 18.4 / 20.6, 1050 (272) 23.3 -> 28.5; nothing measured between:
+//     833 to 896 rows (224) are past the bound and below 64 tiles of 128 x 128, so on the
+//     small-M kernel, probably behind the two-way split
 //   down 6144 -> 1536  256 (96) 21.3 -> 31.1 / 20.8 / 15.9, 384 (144) 30.4 -> 31.4 /
 //     23.4 / 20.7, 640 (240) 27.5 -> 40.6 / 31.5; 128 (48) 14.8 -> - / 23.6 / 15.8
 inline int resid_ring64(const Proj &g) {

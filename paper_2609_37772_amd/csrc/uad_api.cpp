@@ -330,7 +330,7 @@ uad_status uad_create(const uad_model_config *cfg, int32_t device, void *hip_str
   const size_t M = c->m_alloc;
   Carve a;
   // GEMM inputs (te, z, n, o, g) are fp16 in fragment order, M rows each;
-  // ssq holds the per-16-column sums of squares of h (RMSNorm folded into the GEMMs)
+  // ssq holds each row's sums of squares of h, at most one per 16 columns (RMSNorm folded into the GEMMs)
   size_t o_h = a.take<float>(M * d), o_te = a.take<uint16_t>(M * 2 * d), o_z = a.take<uint16_t>(M * d),
          o_n = a.take<uint16_t>(M * d), o_o = a.take<uint16_t>(M * c->q_dim), o_g = a.take<uint16_t>(M * F),
          o_q = a.take<uint16_t>(M * c->q_dim), o_op = a.take<uint16_t>(std::max<size_t>(part, 1) * c->hd),
@@ -811,7 +811,8 @@ static uad_status enqueue_step(uad_ctx *c, hipStream_t s, float *x, const float 
                                             c->a_n));
     } else if (by_class) {
       // batched adaptive norms: h_0, then the time MLP and the modulations of the
-      // step's distinct flow times; token m's are row mod_cls[m]
+      // step's distinct flow times; token m's are row mod_cls[m].  Kernels and grids
+      // go by M: the host does not know *n_cls, and row groups past it return at once
       UAD_CHECK_CLS(K_TEMB, launch_temb_ada(x, nullptr, M, c->Da, d, c->action_in_w, c->action_in_b, c->freqs,
                                             c->a_te, c->h, c->ssq, (int)MA, c->status, s, ea_, eb_));
       UAD_CHECK_CLS(K_TIME_CLASSES, launch_time_classes(t, M, c->mod_cls, c->cls_t, c->n_cls, s, ea_, eb_));
